@@ -386,10 +386,10 @@ skel_status skel_map_overlap2d_reduce_backward(skel_map_op map_op, const double 
  * in: F32 with n elements (the vectors back to back); offsets: I64 with
  * nseg + 1 nondecreasing entries in [0, n]; out: F32 with nseg elements.
  * Empty segments give the identity.  The plain variant issues one Reduce per
- * segment; the persistent variant reduces every segment in one launch over
- * (segment, chunk) work items and combines each segment's partials in a fixed
- * order (deterministic).  The persistent variant checks the offsets on the
- * device: if they decrease or leave [0, n] it computes nothing and
+ * segment; variant 1 (B1_persistent) divides the elements, not the segments,
+ * over the device in chunks of one size and combines the partials of segments
+ * that span chunks in a fixed order (deterministic).  It checks the offsets on
+ * the device: if they decrease or leave [0, n] it computes nothing and
  * skel_sync reports SKEL_E_TIMEOUT with flag 4; the per-segment variant
  * reads the offsets on the host and returns SKEL_E_INVAL.  No offsets can
  * make either variant access memory outside the containers. */

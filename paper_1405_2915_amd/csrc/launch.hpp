@@ -32,8 +32,6 @@ struct Workspace {
     void* status = nullptr;
     size_t status_bytes = 0;
     uint64_t epoch_calls = 0;  // calls that advanced the device epoch since its last reset
-    void* counters = nullptr;  // zero when allocated; every user resets what it counts
-    size_t counters_bytes = 0;
 };
 
 // slots of the sync area, as indices of 64-bit words; each slot has its own
@@ -68,8 +66,6 @@ const DevInfo& device_info();
 skel_status workspace_for(void* stream, Workspace** out);
 skel_status ws_scratch(LaunchCtx& lc, size_t bytes, void** p);
 void retire(Workspace* w, void* p);  // free at skel_finalize, not before
-// zero-initialised counter array of at least `bytes` (kernels leave it zero)
-skel_status ws_counters(LaunchCtx& lc, size_t bytes, void** p);
 // descriptor array of at least `bytes` for one call that advances the device
 // epoch; fails with SKEL_E_STATE if the array would have to grow (or be
 // cleared) while the stream is being captured into a graph

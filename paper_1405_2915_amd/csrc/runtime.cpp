@@ -132,7 +132,6 @@ void free_workspace(Workspace* w) {
     dev_mfree(a, w->scratch, w->stream);
     dev_mfree(a, w->sync, w->stream);
     dev_mfree(a, w->status, w->stream);
-    dev_mfree(a, w->counters, w->stream);
     for (void* p : g_retired[w]) dev_mfree(a, p, w->stream);
     g_retired.erase(w);
     delete w;
@@ -204,34 +203,6 @@ skel_status ws_scratch(LaunchCtx& lc, size_t bytes, void** p) {
         w->scratch_bytes = want;
     }
     *p = w->scratch;
-    return SKEL_OK;
-}
-
-skel_status ws_counters(LaunchCtx& lc, size_t bytes, void** p) {
-    Workspace* w = lc.ws;
-    if (w->counters_bytes < bytes) {
-        hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-        if (hipStreamIsCapturing(lc.stream, &cs) != hipSuccess) {
-            (void)hipGetLastError();
-            cs = hipStreamCaptureStatusNone;
-        }
-        if (cs != hipStreamCaptureStatusNone)
-            return fail(SKEL_E_STATE,
-                        "the counter workspace must grow while the stream is captured; run "
-                        "the same call once before capture");
-        size_t want = bytes < 4096 ? 4096 : ((bytes + 4095) & ~size_t(4095));
-        void* q = dev_malloc(rt().allocator, want, w->stream);
-        if (!q) return fail(SKEL_E_NOMEM, "counter allocation of %zu bytes failed", want);
-        skel_status st = hip_check(hipMemsetAsync(q, 0, want, lc.stream), "hipMemsetAsync");
-        if (st != SKEL_OK) {
-            dev_mfree(rt().allocator, q, w->stream);
-            return st;
-        }
-        retire(w, w->counters);
-        w->counters = q;
-        w->counters_bytes = want;
-    }
-    *p = w->counters;
     return SKEL_OK;
 }
 

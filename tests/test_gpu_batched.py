@@ -45,6 +45,33 @@ def test_segments_small_and_edge_cases(skel, oracle_mod, op):
     skel.skel_sync()
 
 
+@pytest.mark.parametrize("op", list(RED_OPS))
+@pytest.mark.parametrize("lens", [
+    [4095, 1, 4096, 4097, 0, 0, 1023, 1, 1024, 2048, 3],      # chunk and slice edges
+    [0, 0, 1, 0, 4095, 0, 0],                                 # empty ones at the edges
+    [1] * 20000 + [0] * 700 + [2] * 5000,                     # many starts in a chunk
+    [5, 15 * 4096, 1, 16 * 4096, 3, 17 * 4096 - 1, 4],        # few pieces and many
+    [100, 4200 * 4096 + 17, 7, 0],                            # one long vector
+], ids=["edges", "empty", "short", "pieces", "long"])
+def test_segments_across_chunks(skel, oracle_mod, op, lens):
+    """B1 divides the elements into chunks of 4096 (slices of 1024): segments
+    that start, end or span at those edges, at the end of the data, and with
+    elements before the first and after the last offset; two calls give the
+    same bits."""
+    for lead, trail in ((0, 0), (3, 9000)):
+        off = (lead + np.concatenate([[0], np.cumsum(lens)])).astype(np.int64)
+        x = si.normal_f32(int(off[-1]) + trail, 2, 31)
+        check_segments(skel, oracle_mod, x, off, op, 1)
+    cx, co = skel.Container.from_numpy(x), skel.Container.from_numpy(off)
+    got = []
+    for _ in range(2):
+        out = skel.Container.empty(skel.F32, len(lens))
+        skel.skel_reduce_segments(RED_OPS[op], cx, co, out, variant=1)
+        got.append(out.to_numpy())
+    assert np.array_equal(got[0], got[1])
+    skel.skel_sync()
+
+
 def test_segments_log_uniform_batch(skel, oracle_mod):
     lens = si.log_uniform_lengths(512, 32, 1 << 20, config=2, index=10)
     off = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
