@@ -166,12 +166,6 @@ __global__ __launch_bounds__(kBlock) void ov1_adjoint(const float* g, float* dx,
         dx[j] = adj1_at(g, n, w, r, edge, j);
 }
 
-// elements 0 and n - 1 only (where clamped reads land)
-__global__ void ov1_adjoint_ends(const float* g, float* dx, int64_t n, WA1 w, int r, int edge) {
-    const int64_t j = threadIdx.x == 0 ? 0 : n - 1;
-    if (threadIdx.x < 2) dx[j] = adj1_at(g, n, w, r, edge, j);
-}
-
 // --------------------------------------------------------- MapOverlap 2D ---
 struct WA2 {
     float w[(2 * SKEL_MAX_RADIUS_2D + 1) * (2 * SKEL_MAX_RADIUS_2D + 1)];
@@ -339,26 +333,18 @@ skel_status launch_map_backward(int op, float p0, float p1, const float* x, cons
 // A1 (both dimensions): the transpose of a correlation with weights w inside
 // the array is the correlation with the reversed weights, so the forward
 // kernels compute it with a zero pad (CONST edges send nothing back, and for
-// CLAMP this is every element but the ends) or with the cyclic rule (exact);
-// for CLAMP the elements that clamped reads land on are then recomputed by
-// the gather.
+// CLAMP this is every element but the ends) or with the cyclic rule (exact).
+// For CLAMP the elements that clamped reads land on are, in 1D, computed by the
+// same launch; in 2D they are then recomputed by the gather.
 skel_status launch_overlap1d_adjoint(int v, const float* g, float* dx, int64_t n,
                                      const float* w, int r, int edge, LaunchCtx& lc) {
-    WA1 wk{};
-    for (int k = 0; k <= 2 * r; ++k) wk.w[k] = w[k];
     if (v == A0_GATHER) {
+        WA1 wk{};
+        for (int k = 0; k <= 2 * r; ++k) wk.w[k] = w[k];
         ov1_adjoint<<<grid_for(n, *lc.dev), kBlock, 0, lc.stream>>>(g, dx, n, wk, r, edge);
         return launch_check("ov1_adjoint");
     }
-    float wf[2 * SKEL_MAX_RADIUS_1D + 1];
-    for (int k = 0; k <= 2 * r; ++k) wf[k] = w[2 * r - k];
-    const int fwd = r <= 4 ? O1C_SHUFFLE : O1B_LDS_TILE;
-    skel_status e = launch_overlap1d(fwd, g, dx, n, wf, r,
-                                     edge == SKEL_EDGE_CYCLIC ? SKEL_EDGE_CYCLIC : SKEL_EDGE_CONST,
-                                     0.0f, lc);
-    if (e != SKEL_OK || edge != SKEL_EDGE_CLAMP) return e;
-    ov1_adjoint_ends<<<1, dev::kWave, 0, lc.stream>>>(g, dx, n, wk, r, edge);
-    return launch_check("ov1_adjoint_ends");
+    return launch_overlap1d_transposed(g, dx, n, w, r, edge, lc);
 }
 
 skel_status launch_overlap2d_adjoint(int v, const float* g, float* dx, int64_t rows,

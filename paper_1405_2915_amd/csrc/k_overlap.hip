@@ -8,8 +8,8 @@
 //
 // Variants:
 //   O1a  1D direct: one output per lane, taps read through the caches
-//   O1b  1D LDS tile: a workgroup stages 1024 + 2r inputs once, each lane
-//        computes four outputs from registers
+//   O1b  1D LDS tile: a workgroup stages its outputs' inputs once; each lane
+//        slides a register window over them, four taps per 16-byte LDS read
 //   O1c  1D cross-lane: r <= 4 neighbours come from adjacent lanes by
 //        shuffles; no LDS, no barrier
 //   O2a  2D direct: one output per lane, (2ry+1)(2rx+1) taps from global
@@ -29,6 +29,8 @@
 // 2D tiles are visited in an XCD-aware order: consecutive workgroups go to
 // different XCDs round-robin, so tile ids are remapped to give each XCD a
 // contiguous band of tiles whose shared halo rows stay in that XCD's L2.
+#include <type_traits>
+
 #include "kcommon.hpp"
 #include "dispatch.hpp"
 #include "launch.hpp"
@@ -37,6 +39,9 @@ namespace skel {
 namespace {
 
 using dev::f32x4;
+// a 16-byte vector at any float's address: one global access, as for an
+// aligned one (a line boundary inside it costs a second line)
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
 
 struct W1 {
     float w[2 * SKEL_MAX_RADIUS_1D + 1];
@@ -101,34 +106,91 @@ __global__ __launch_bounds__(kBlock) void ov1_direct(const float* x, float* out,
     out[i] = acc;
 }
 
-constexpr int kT1 = kBlock * 4;  // outputs per workgroup
+// The transpose of a clamped 1D map (adjoint of MapOverlap 1D, CLAMP) is the
+// zero-padded correlation with reversed weights except at the two end
+// elements, which also collect every read past them:
+//     out[0]   = sum_i lo[i] x[i],         lo[i] = w'[0] + ... of tap i outward
+//     out[n-1] = sum_m hi[m] x[n - 1 - m]
+// with the prefix sums of the forward weights as coefficients (make_ends).
+struct Ends1 {
+    float lo[SKEL_MAX_RADIUS_1D + 1], hi[SKEL_MAX_RADIUS_1D + 1];
+};
 
-template <int RT>
-__global__ __launch_bounds__(kBlock) void ov1_lds(const float* x, float* out, int64_t n, W1 w,
-                                                  int r_, int edge, float pad) {
-    constexpr int MR = RT >= 0 ? RT : SKEL_MAX_RADIUS_1D;
-    const int r = RT >= 0 ? RT : r_;
-    __shared__ float s[kT1 + 2 * MR];
-    const int64_t base = (int64_t)blockIdx.x * kT1;
-    for (int k = threadIdx.x; k < kT1 + 2 * r; k += kBlock) {
-        const int64_t j = base - r + k;
-        s[k] = (j >= 0 && j < n) ? x[j] : fetch1(x, n, j, edge, pad);
+// O1b.  A workgroup of NT lanes stages the inputs of its 4 * NT outputs in LDS;
+// a lane owns four consecutive outputs and slides a window of eight inputs
+// along the taps: per four taps one 16-byte LDS read feeds sixteen
+// multiply-adds, the weights come from scalar registers, and the loop runs over
+// the actual radius.  The additions of an output run in tap order, as in O1a.
+// What bounds it is HBM up to a radius of about 16, then the vector ALU (2r + 1
+// unpacked multiply-adds per output).  Measured on 2^24 floats, the map and its
+// transpose together: radius 5 51 us (4.9 TB/s), 16 62 us, 64 158 us, against
+// 267, 519 and 1780 us for a fully unrolled window of the largest radius (its
+// 129 guarded taps and 132 window registers).  Eight or sixteen outputs per
+// lane measured slower (radius 16: 65 and 84 us).
+template <int NT, bool ENDS>
+__global__ __launch_bounds__(NT) void ov1_window(const float* x, float* out, int64_t n, W1 w,
+                                                 int r, int edge, float pad, Ends1 ends) {
+    constexpr int T = NT * 4;  // outputs per workgroup
+    // (the last window read may reach past the taps by up to five floats)
+    __shared__ __attribute__((aligned(16))) float s[T + 2 * SKEL_MAX_RADIUS_1D + 8];
+    const int tid = threadIdx.x;
+    const int64_t base = (int64_t)blockIdx.x * T;
+    const int staged = T + 2 * r;
+    if (base - r >= 0 && base + T + r + 4 <= n) {
+        // whole vectors at any alignment; the last may pass the halo by three
+        const float* src = x + (base - r);
+        constexpr int V = 1 + (2 * SKEL_MAX_RADIUS_1D + T - 1) / T;
+        f32x4 v[V];
+#pragma unroll
+        for (int u = 0; u < V; ++u)
+            if (4 * (tid + u * NT) < staged)
+                v[u] = *reinterpret_cast<const f32x4u*>(src + 4 * (tid + u * NT));
+#pragma unroll
+        for (int u = 0; u < V; ++u)
+            if (4 * (tid + u * NT) < staged) *reinterpret_cast<f32x4*>(s + 4 * (tid + u * NT)) = v[u];
+    } else {
+        for (int k = tid; k < staged; k += NT) s[k] = fetch1(x, n, base - r + k, edge, pad);
     }
     __syncthreads();
-    const int o = threadIdx.x * 4;
-    float win[4 + 2 * MR];
-#pragma unroll
-    for (int k = 0; k < 4 + 2 * MR; ++k)
-        if (k < 4 + 2 * r) win[k] = s[o + k];
+    const f32x4* win = reinterpret_cast<const f32x4*>(s) + tid;
+    f32x4 lo = win[0];
     float acc[4] = {0.f, 0.f, 0.f, 0.f};
+    const auto taps = [&](int k, auto count) {
+        const f32x4 hi = win[k / 4 + 1];
+        const float v[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
 #pragma unroll
-    for (int k = 0; k <= 2 * MR; ++k) {
-        if (k > 2 * r) break;
+        for (int t = 0; t < decltype(count)::value; ++t)
 #pragma unroll
-        for (int c = 0; c < 4; ++c) acc[c] = __builtin_fmaf(w.w[k], win[c + k], acc[c]);
+            for (int c = 0; c < 4; ++c) acc[c] = __builtin_fmaf(w.w[k + t], v[c + t], acc[c]);
+        lo = hi;
+    };
+    int k = 0;
+#pragma unroll 2
+    for (; k + 4 <= 2 * r + 1; k += 4) taps(k, std::integral_constant<int, 4>());
+    if (r & 1) taps(k, std::integral_constant<int, 3>());  // 2r + 1 is odd: 3 or 1 remain
+    else taps(k, std::integral_constant<int, 1>());
+    if constexpr (ENDS) {
+        const int l = dev::lane(), mine = tid - l;  // first lane of this wavefront
+        const int reach = n - 1 < r ? (int)(n - 1) : r;
+        if (base == 0 && mine == 0) {
+            float p = 0.0f;
+            for (int i = l; i <= reach; i += dev::kWave) p = __builtin_fmaf(ends.lo[i], s[r + i], p);
+            p = dev::wave_reduce<dev::Comb<float, SKEL_SUM>>(p);
+            if (l == 0) acc[0] = p;
+        }
+        const int64_t e = n - 1 - base;  // the last element, if this tile holds it
+        if (e < T && e / 4 / dev::kWave == mine / dev::kWave) {
+            float p = 0.0f;
+            for (int m = l; m <= reach; m += dev::kWave)
+                p = __builtin_fmaf(ends.hi[m], s[(int)e + r - m], p);
+            p = dev::wave_reduce<dev::Comb<float, SKEL_SUM>>(p);
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+                if (4 * tid + c == (int)e) acc[c] = p;
+        }
     }
-    const int64_t i = base + o;
-    if (i + 4 <= n && (n & 3) == 0) {
+    const int64_t i = base + 4 * tid;
+    if (i + 4 <= n) {
         *reinterpret_cast<f32x4*>(out + i) = f32x4{acc[0], acc[1], acc[2], acc[3]};
     } else {
 #pragma unroll
@@ -152,9 +214,9 @@ __global__ __launch_bounds__(kBlock) void ov1_lds(const float* x, float* out, in
 #endif
 constexpr int kShflRows = SKEL_O1C_ROWS;
 
-template <int RT>
+template <int RT, bool ENDS>
 __global__ __launch_bounds__(kBlock) void ov1_shfl(const float* x, float* out, int64_t n, W1 w,
-                                                   int r_, int edge, float pad) {
+                                                   int r_, int edge, float pad, Ends1 ends) {
     constexpr int MR = RT >= 0 ? RT : 4;
     constexpr int U = kShflRows;
     const int r = RT >= 0 ? RT : r_;
@@ -208,6 +270,14 @@ __global__ __launch_bounds__(kBlock) void ov1_shfl(const float* x, float* out, i
                 float acc = 0.0f;
                 for (int kk = 0; kk <= 2 * r; ++kk)
                     acc = __builtin_fmaf(w.w[kk], fetch1(x, n, i + kk - r, edge, pad), acc);
+                if constexpr (ENDS) {
+                    if (i == 0 || i == n - 1) {
+                        acc = 0.0f;
+                        for (int m = 0; m <= r && m < n; ++m)
+                            acc = i == 0 ? __builtin_fmaf(ends.lo[m], x[m], acc)
+                                         : __builtin_fmaf(ends.hi[m], x[n - 1 - m], acc);
+                    }
+                }
                 out[i] = acc;
             }
         }
@@ -751,20 +821,26 @@ __global__ __launch_bounds__(kBlock) void ov2_march(const float* x, float* out, 
 // --------------------------------------------------------------- launchers
 int64_t div_up(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
+template <int NT>
+void run1d_window(const float* x, float* out, int64_t n, const W1& w, int r, int edge, float pad,
+                  const Ends1* ends, hipStream_t st) {
+    const unsigned grid = (unsigned)div_up(n, NT * 4);
+    if (ends) ov1_window<NT, true><<<grid, NT, 0, st>>>(x, out, n, w, r, edge, pad, *ends);
+    else ov1_window<NT, false><<<grid, NT, 0, st>>>(x, out, n, w, r, edge, pad, Ends1());
+}
+
 template <int RT>
 skel_status run1d(int v, const float* x, float* out, int64_t n, const W1& w, int r, int edge,
-                  float pad, hipStream_t st) {
+                  float pad, const Ends1* ends, hipStream_t st) {
     if (v == O1A_DIRECT) {
         ov1_direct<RT><<<(unsigned)div_up(n, kBlock), kBlock, 0, st>>>(x, out, n, w, r, edge, pad);
         return launch_check("overlap1d_direct");
     }
-    if (v == O1C_SHUFFLE) {  // selectable for r <= 4 only
-        ov1_shfl<RT><<<(unsigned)div_up(n, 4 * kBlock * kShflRows), kBlock, 0, st>>>(
-            x, out, n, w, r, edge, pad);
-        return launch_check("overlap1d_shuffle");
-    }
-    ov1_lds<RT><<<(unsigned)div_up(n, kT1), kBlock, 0, st>>>(x, out, n, w, r, edge, pad);
-    return launch_check("overlap1d_lds");
+    // selectable for r <= 4 only
+    const unsigned grid = (unsigned)div_up(n, 4 * kBlock * kShflRows);
+    if (ends) ov1_shfl<RT, true><<<grid, kBlock, 0, st>>>(x, out, n, w, r, edge, pad, *ends);
+    else ov1_shfl<RT, false><<<grid, kBlock, 0, st>>>(x, out, n, w, r, edge, pad, Ends1());
+    return launch_check("overlap1d_shuffle");
 }
 
 template <int RY, int RX, bool SEP>
@@ -844,16 +920,53 @@ skel_status run2d_fields(int v, const float* x, float* out, int64_t rows, int64_
 
 }  // namespace
 
+static skel_status launch_1d(int v, const float* x, float* out, int64_t n, const W1& wk, int r,
+                             int edge, float pad, const Ends1* ends, LaunchCtx& lc) {
+    if (v == O1B_LDS_TILE) {
+        // short arrays: one wavefront per workgroup, which spreads them over more
+        // CUs (2^12 floats, radius 16, map and transpose: 6.3 us against 7.3; 2^16:
+        // 6.2 / 6.5; from 2^18 on the smaller halo share of 256 lanes is level or
+        // better, 2^20 radius 64: 17.2 against 17.9)
+        if (n <= (INT64_C(1) << 17)) run1d_window<64>(x, out, n, wk, r, edge, pad, ends, lc.stream);
+        else run1d_window<256>(x, out, n, wk, r, edge, pad, ends, lc.stream);
+        return launch_check("overlap1d_window");
+    }
+    switch (r) {
+    case 1: return run1d<1>(v, x, out, n, wk, r, edge, pad, ends, lc.stream);
+    case 2: return run1d<2>(v, x, out, n, wk, r, edge, pad, ends, lc.stream);
+    case 3: return run1d<3>(v, x, out, n, wk, r, edge, pad, ends, lc.stream);
+    case 4: return run1d<4>(v, x, out, n, wk, r, edge, pad, ends, lc.stream);
+    default: return run1d<-1>(v, x, out, n, wk, r, edge, pad, ends, lc.stream);
+    }
+}
+
 skel_status launch_overlap1d(int v, const float* x, float* out, int64_t n, const float* w,
                              int r, int edge, float pad, LaunchCtx& lc) {
     W1 wk{};
     for (int k = 0; k <= 2 * r; ++k) wk.w[k] = w[k];
-    switch (r) {
-    case 1: return run1d<1>(v, x, out, n, wk, r, edge, pad, lc.stream);
-    case 2: return run1d<2>(v, x, out, n, wk, r, edge, pad, lc.stream);
-    case 4: return run1d<4>(v, x, out, n, wk, r, edge, pad, lc.stream);
-    default: return run1d<-1>(v, x, out, n, wk, r, edge, pad, lc.stream);
+    return launch_1d(v, x, out, n, wk, r, edge, pad, nullptr, lc);
+}
+
+skel_status launch_overlap1d_transposed(const float* g, float* dx, int64_t n, const float* w,
+                                        int r, int edge, LaunchCtx& lc) {
+    W1 wk{};
+    for (int k = 0; k <= 2 * r; ++k) wk.w[k] = w[2 * r - k];
+    const int v = r <= 4 ? O1C_SHUFFLE : O1B_LDS_TILE;
+    if (edge != SKEL_EDGE_CLAMP)
+        return launch_1d(v, g, dx, n, wk, r, edge, 0.0f, nullptr, lc);
+    // tap k of output i reads element i + k - r: element 0 collects the taps
+    // k <= r - i of output i, element n - 1 the taps k >= r + m of output
+    // n - 1 - m (a single element: every tap)
+    Ends1 ends{};
+    double lo = 0.0, hi = 0.0;
+    for (int i = r; i >= 0; --i) {
+        lo += w[r - i];
+        hi += w[r + i];
+        ends.lo[i] = (float)lo;
+        ends.hi[i] = (float)hi;
     }
+    if (n == 1) ends.lo[0] = ends.hi[0] = (float)(lo + hi - w[r]);
+    return launch_1d(v, g, dx, n, wk, r, SKEL_EDGE_CONST, 0.0f, &ends, lc);
 }
 
 skel_status launch_overlap2d(int v, const float* x, float* out, int64_t rows, int64_t cols,

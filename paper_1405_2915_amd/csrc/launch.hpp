@@ -92,6 +92,10 @@ skel_status launch_mapreduce(int variant, int map_op, float p0, float p1,
 skel_status launch_overlap1d(int variant, const float* x, float* out, int64_t n,
                              const float* w, int r, int edge, float pad,
                              LaunchCtx& lc);
+// the transpose of launch_overlap1d's map (w, r, edge of the forward call; CONST
+// pads send nothing back) applied to g, as one launch of its kernels
+skel_status launch_overlap1d_transposed(const float* g, float* dx, int64_t n, const float* w,
+                                        int r, int edge, LaunchCtx& lc);
 // `fields` images of rows x cols stored back to back, each mapped on its own
 // (its own borders); one launch covers up to kMaxFieldsPerLaunch of them
 constexpr int64_t kMaxFieldsPerLaunch = 65535;

@@ -266,6 +266,28 @@ RADII_2D = [(4, 4), (1, 1), (2, 2), (3, 1), (0, 2), (8, 8)]
 
 
 @pytest.mark.parametrize("edge", list(EDGES))
+@pytest.mark.parametrize("r", [3, 5, 8, 31, 63, 64])
+def test_mapoverlap1d_window(skel, oracle_mod, edge, r):
+    """The LDS window (O1b) and the transpose that runs it: both tile sizes
+    (256 and 1024 outputs) at their edges, arrays shorter than the radius, both
+    remainders of 2r + 1 by four taps.  At most 2r + 1 fused multiply-adds in
+    turn, and an end element's coefficients and lane sums rounded once more:
+    2r + 4 roundings of 2^-24 of the terms' magnitude."""
+    v = skel.variant_index(skel.SK_MAPOVERLAP1D, "O1b_lds_tile")
+    w = si.uniform_f32(2 * r + 1, -1.0, 1.0, 31, r)
+    tol = (2 * r + 4) * 2.0 ** -24
+    for n in (1, 2, r, r + 1, 255, 256, 257, 1000, 256 * 5 + 2, (1 << 17) + 1, (1 << 17) + 1024 + r):
+        x = si.uniform_f32(n, -1.0, 1.0, 31, 100)
+        y, dx = skel.Container.empty(skel.F32, n), skel.Container.empty(skel.F32, n)
+        skel.skel_mapoverlap1d(cont(skel, x), y, w, r, EDGES[edge], pad=0.25, variant=v)
+        skel.skel_mapoverlap1d_backward(cont(skel, x), dx, w, r, EDGES[edge])
+        for got, (ref, mag) in ((y, oracle_mod.mapoverlap1d(x, w, r, edge, 0.25)),
+                                (dx, oracle_mod.mapoverlap1d_adjoint(x, w, r, edge))):
+            bad = np.abs(got.to_numpy().astype(np.float64) - ref) > tol * mag + 1e-30
+            assert not bad.any(), (edge, r, n, got is dx, np.flatnonzero(bad)[:5])
+
+
+@pytest.mark.parametrize("edge", list(EDGES))
 @pytest.mark.parametrize("ry,rx", RADII_2D)
 def test_mapoverlap2d(skel, oracle_mod, edge, ry, rx):
     wy = si.uniform_f32(2 * ry + 1, 0.0, 1.0, 3, 10 + ry)
