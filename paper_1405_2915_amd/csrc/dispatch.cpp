@@ -9,12 +9,20 @@
 
 namespace skel {
 
-int overlap2d_dense_variant(int64_t n, int radius) {
-    return radius <= 2 && n >= (INT64_C(1) << 20) ? O2E_MARCH : O2B_LDS_TILE;
+// the marching window's strips of 256 columns are whole
+static bool whole_strips(int64_t cols) { return cols % 256 == 0; }
+
+static bool overlap2d_march(int64_t n, int64_t rows, int64_t cols, int radius) {
+    if (radius > 2) return false;
+    return rows < 16 ? n >= (INT64_C(1) << 20) : whole_strips(cols) && n >= (INT64_C(1) << 24);
 }
 
-int overlap2d_separable_variant(int64_t n, int radius) {
-    return radius <= 2 && n >= (INT64_C(1) << 20) ? O2E_MARCH : O2D_SEPARABLE_L1;
+int overlap2d_dense_variant(int64_t n, int64_t rows, int64_t cols, int radius) {
+    return overlap2d_march(n, rows, cols, radius) ? O2E_MARCH : O2B_LDS_TILE;
+}
+
+int overlap2d_separable_variant(int64_t n, int64_t rows, int64_t cols, int radius) {
+    return overlap2d_march(n, rows, cols, radius) ? O2E_MARCH : O2D_SEPARABLE_L1;
 }
 
 namespace {
@@ -117,8 +125,8 @@ int static_rule(const CallContext& c) {
         if (c.radius > 4) return O1B_LDS_TILE;
         return c.n <= (INT64_C(1) << 20) ? O1A_DIRECT : O1C_SHUFFLE;
     case SKEL_SK_MAPOVERLAP2D:
-        return c.separable ? overlap2d_separable_variant(c.n, c.radius)
-                           : overlap2d_dense_variant(c.n, c.radius);
+        return c.separable ? overlap2d_separable_variant(c.n, c.rows, c.cols, c.radius)
+                           : overlap2d_dense_variant(c.n, c.rows, c.cols, c.radius);
     case SKEL_SK_SCAN:
         // the flat look-back while the array fits its 1024 tiles (the tuned plan's
         // choice for int32 up to 2^22, and its binary32 combination order is
@@ -147,6 +155,11 @@ int table_rule(const CallContext& c) {
     int best = -1, best_k = -1, lowest = -1, lowest_k = 1 << 30;
     for (const auto& e : g_table) {
         if (e.skeleton != c.skeleton || e.dtype != (int)c.din || e.cls != cls) continue;
+        // the marching window was tuned on images of whole strips; a ragged last
+        // strip costs it more than it wins (9 x 9 Gaussian: 4096^2 34.8 us against
+        // 37.5 for the separable tile, 4000^2 52 / 35, 3000^2 53 / 21)
+        if (c.skeleton == SKEL_SK_MAPOVERLAP2D && e.variant == O2E_MARCH && !whole_strips(c.cols))
+            continue;
         if (e.log2n <= key && e.log2n > best_k) {
             best = e.variant;
             best_k = e.log2n;

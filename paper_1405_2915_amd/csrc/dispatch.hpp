@@ -49,20 +49,19 @@ struct CallContext {
     int rows_aligned = 0;  // row-wise Scan: every row starts 16-byte aligned
 };
 
-// 2D neighbourhood map with a dense (non-separable) weight matrix: the
-// marching window for radii up to 2 on 2^20 elements or more, else the LDS
-// tile.  Measured with the Infinity Cache evicted before each call, marching
-// window against LDS tile: 5-point stencil on 64 fields of 2048^2 357 / 426
-// us, on 16384^2 360 / 443, on 2048^2 8.6 / 13.0 (on 8192^2 96 / 84); 5 x 5
-// on 16384^2 379 / 452.  Dense 9 x 9 loses (4096^2: 96 / 68 us; its 64-row
-// strips or shorter ones).  Also the forward pass that the flipped transpose
-// runs.
-int overlap2d_dense_variant(int64_t n, int radius);
-// The same with the weights given as factors: the marching window for radii up
-// to 2 on 2^20 elements or more (3 x 3 over 64 fields of 2048^2: 357 against
-// 388 us, caches evicted), else the separable L1 variant (the 9 x 9 Gaussian:
-// level on 4096^2, slower for the marching window elsewhere).
-int overlap2d_separable_variant(int64_t n, int radius);
+// 2D neighbourhood map of n pixels in images of rows x cols: the marching
+// window where it beats the tiles, else the LDS tile (dense weights) or the
+// separable L1 tile (factors).  Also the forward pass that the flipped transpose
+// runs.  The marching window holds a strip of 256 columns x 16 rows per
+// wavefront, so it wants whole strips, enough of them to fill the device several
+// times (2^24 pixels) and a radius of at most 2; images of fewer than 16 rows,
+// which leave most of a tile idle, take it from 2^20 pixels on at any width.
+// Measured, map and clamped transpose, marching / tile: 5 x 5 on 64 fields of
+// 2048^2 781 / 871 us, separable 3 x 3 756 / 841, 5 x 5 740 / 900, 5-point 740 /
+// 740; on 8192^2 206 / 201 (5-point) and 209 / 213 (separable 5 x 5); but 5-point
+// on 1024^2 15.3 / 10.1, 2896^2 34 / 27, 3000^2 48 / 29, 1501 x 1999 43 / 18.
+int overlap2d_dense_variant(int64_t n, int64_t rows, int64_t cols, int radius);
+int overlap2d_separable_variant(int64_t n, int64_t rows, int64_t cols, int radius);
 
 int variant_count(int skeleton);
 const char* variant_name(int skeleton, int variant);

@@ -13,14 +13,14 @@
 //   O1c  1D cross-lane: r <= 4 neighbours come from adjacent lanes by
 //        shuffles; no LDS, no barrier
 //   O2a  2D direct: one output per lane, (2ry+1)(2rx+1) taps from global
-//   O2b  2D LDS tile: a 64x64 output tile plus halo staged in LDS with 16-byte
-//        loads; each lane computes a 4x4 output block, reusing every loaded
-//        row segment for up to four output rows
+//   O2b  2D LDS tile: a 64-column output tile of 16 or 32 rows plus halo staged
+//        in LDS with 16-byte loads; each lane computes four columns of one or
+//        two rows
 //   O2c  2D separable (W = wy (x) wx): the staged tile is filtered along rows
 //        into a second LDS buffer, then along columns; 2(2r+1) instead of
 //        (2r+1)^2 multiply-adds per output
 //   O2d  2D separable with the row pass read from global memory through L1
-//        and only its result staged in LDS (64x32 tiles, full occupancy)
+//        and only its result staged in LDS
 //   O2e  2D marching window (ry, rx <= 4): each wavefront walks down a strip
 //        of 256 columns, loading every input row once; horizontal neighbours
 //        come from the adjacent lanes by DPP moves and the 2ry+1 output rows
@@ -285,50 +285,196 @@ __global__ __launch_bounds__(kBlock) void ov1_shfl(const float* x, float* out, i
 }
 
 // ------------------------------------------------------------------- 2D
-constexpr int kTX = 64, kTY = 64;  // output tile of the LDS variants
+constexpr int kTX = 64;  // columns of an output tile (LDS variants)
 
-// compile-time radii, or (-1, -1) for any radius up to the maximum
+// compile-time radii of the direct form, or (-1, -1) for any radius
 template <int RY, int RX>
 struct Rad {
     static constexpr bool dyn = RY < 0;
     static constexpr int MY = dyn ? SKEL_MAX_RADIUS_2D : RY;
     static constexpr int MX = dyn ? SKEL_MAX_RADIUS_2D : RX;
-    static constexpr int HX = (MX + 3) / 4 * 4;  // column halo rounded to 16 bytes
-    static constexpr int LW = kTX + 2 * HX;      // LDS row width of the input tile
-    static constexpr int LH = kTY + 2 * MY;      // LDS rows of the input tile
 };
 
-// tile id -> (tile x, tile y) with an XCD-contiguous order
-__device__ __forceinline__ void tile_coords(int64_t nbx, int64_t nb, int64_t& bx, int64_t& by) {
-    int64_t b = blockIdx.x, L = b;
-    if ((nb & 7) == 0) L = (b & 7) * (nb >> 3) + (b >> 3);
+// The LDS variants know the column radius at compile time (their inner loops
+// run along a row) and take the row radius at run time (their outer loops run
+// down the rows), so every pair of radii has straight-line inner loops.
+template <int RX>
+struct Cols {
+    static constexpr int HX = (RX + 3) / 4 * 4;  // column halo rounded to 16 bytes
+    static constexpr int LW = kTX + 2 * HX;      // LDS row width of the input tile
+    static constexpr int NV = (4 + 2 * HX) / 4;  // 16-byte vectors a lane's 4 outputs read
+};
+constexpr int kHW = kTX + 4;  // LDS row width of a row-filtered tile (padded)
+
+// workgroup b of a grid rounded up to a multiple of 8 -> (tile x, tile y) of nb
+// tiles, in an XCD-contiguous order; false for the workgroups past the last tile
+__device__ __forceinline__ bool tile_coords(int64_t b, int64_t nbx, int64_t nb, int64_t& bx,
+                                            int64_t& by) {
+    const int64_t L = (b & 7) * ((nb + 7) >> 3) + (b >> 3);
     bx = L % nbx;
     by = L / nbx;
+    return L < nb;
 }
 
-// Stage rows [y0 - ry, y0 + kTY + ry) and columns [x0 - HX, x0 + kTX + HX) of
-// the input into LDS (row stride Rad::LW).
-template <class RD>
-__device__ __forceinline__ void stage_tile(const float* x, int64_t rows, int64_t cols,
-                                           int64_t y0, int64_t x0, int ry, int edge, float pad,
+// four consecutive columns starting at j of row rp, through the column rule
+__device__ __forceinline__ f32x4 fetch_row4(const float* rp, int64_t cols, int64_t j, int edge,
+                                            float pad) {
+    if (j >= 0 && j + 4 <= cols) return *reinterpret_cast<const f32x4u*>(rp + j);
+    float v[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        int64_t c;
+        v[q] = border(j + q, cols, edge, c) ? rp[c] : pad;
+    }
+    return f32x4{v[0], v[1], v[2], v[3]};
+}
+
+// the same of row i, through the row rule too
+__device__ __forceinline__ f32x4 fetch4(const float* x, int64_t rows, int64_t cols, int64_t i,
+                                        int64_t j, int edge, float pad) {
+    int64_t a;
+    if (!border(i, rows, edge, a)) return f32x4{pad, pad, pad, pad};
+    return fetch_row4(x + a * cols, cols, j, edge, pad);
+}
+
+// Stage nrows rows from y0 - ry and columns [x0 - HX, x0 + kTX + HX) of the
+// input into LDS (row stride Cols::LW), as 16-byte vectors at any alignment of
+// the rows; four loads in flight per lane.  Vectors that no output reads (past
+// a ragged last column or row and its halo) are left alone.
+template <int RX>
+__device__ __forceinline__ void stage_tile(const float* x, int64_t rows, int64_t cols, int64_t y0,
+                                           int64_t x0, int nrows, int ry, int edge, float pad,
                                            float* tin) {
-    constexpr int LW = RD::LW, HX = RD::HX, V = LW / 4;
-    const int nrows = kTY + 2 * ry;
-    const bool interior = y0 - ry >= 0 && y0 + kTY + ry <= rows && x0 - HX >= 0 &&
-                          x0 + kTX + HX <= cols && (cols & 3) == 0;
-    if (interior) {
-        const float* src = x + (y0 - ry) * cols + (x0 - HX);
-        for (int k = threadIdx.x; k < nrows * V; k += kBlock) {
-            const int rr = k / V, cc = k - rr * V;
-            f32x4 v = *reinterpret_cast<const f32x4*>(src + (int64_t)rr * cols + 4 * cc);
-            *reinterpret_cast<f32x4*>(tin + rr * LW + 4 * cc) = v;
+    using CL = Cols<RX>;
+    constexpr int V = CL::LW / 4;
+    const bool interior = y0 - ry >= 0 && y0 - ry + nrows <= rows && x0 - CL::HX >= 0 &&
+                          x0 + kTX + CL::HX <= cols;
+    const auto batch = [&](auto load) {
+        for (int k0 = threadIdx.x; k0 < nrows * V; k0 += 4 * kBlock) {
+            f32x4 v[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int k = k0 + u * kBlock, rr = k / V;
+                if (k < nrows * V) v[u] = load(rr, 4 * (k - rr * V));
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                if (k0 + u * kBlock < nrows * V)
+                    *reinterpret_cast<f32x4*>(tin + 4 * (k0 + u * kBlock)) = v[u];
         }
+    };
+    if (interior) {
+        const float* src = x + (y0 - ry) * cols + (x0 - CL::HX);
+        batch([&](int rr, int cc) {
+            return *reinterpret_cast<const f32x4u*>(src + (int64_t)rr * cols + cc);
+        });
     } else {
-        for (int k = threadIdx.x; k < nrows * LW; k += kBlock) {
-            const int rr = k / LW, cc = k - rr * LW;
-            tin[rr * LW + cc] = fetch2(x, rows, cols, y0 - ry + rr, x0 - HX + cc, edge, pad);
+        batch([&](int rr, int cc) {
+            const int64_t i = y0 - ry + rr, j = x0 - CL::HX + cc;
+            if (i >= rows + ry || j >= cols + RX) return f32x4{0.f, 0.f, 0.f, 0.f};
+            return fetch4(x, rows, cols, i, j, edge, pad);
+        });
+    }
+}
+
+// The transpose of a clamped 2D map is the zero-padded correlation with
+// reversed weights except on the first and last rows and columns, which also
+// collect the reads past them.  Workgroups 0 .. nbb - 1 of a transposed launch
+// of the tile forms compute those pixels (and the tiles leave them out), so
+// that they run beside the tiles; the marching form, whose registers have no
+// room for either, is followed by a launch of its own (ov2_border).  A border pixel of row 0 weighs row i by the
+// sum of the weight rows a <= ry - i, one of the last row by the sum of a >= ry
+// + m (i = rows - 1 - m), and likewise along the columns; the row sums are
+// tabulated in LDS, the column sums of the corner columns run along.  kBorderG
+// lanes share a pixel's row terms, combined by a fixed butterfly.
+// Measured on CLAMP transposes against a gather of every border pixel's taps in
+// a second launch: that launch took 11.6 us of the 9 x 9 transpose on 4096^2, 4.7
+// on 24 fields of 121 x 163 and 30 on 64 of 2048^2 (5-point); beside the tiles
+// the first two cost nothing measurable, the last (own launch) 12 us.
+constexpr int kBorderG = 4;
+constexpr int kBorderTab = (2 * SKEL_MAX_RADIUS_2D + 1) * (2 * SKEL_MAX_RADIUS_2D + 1) +
+                           2 * (SKEL_MAX_RADIUS_2D + 1) * (2 * SKEL_MAX_RADIUS_2D + 1);
+
+__device__ __forceinline__ int64_t border_pixels(int64_t rows, int64_t cols) {
+    return (rows > 1 ? 2 : 1) * cols + (cols > 1 ? 2 : 1) * (rows > 2 ? rows - 2 : 0);
+}
+
+__device__ __forceinline__ void border_transposed(const float* g, float* dx, int64_t rows,
+                                                  int64_t cols, const W2& w, int ry, int rx,
+                                                  float* tab) {
+    const int nx = 2 * rx + 1, ny = 2 * ry + 1;
+    float* lo = tab + ny * nx;
+    float* hi = lo + (ry + 1) * nx;
+    // w holds the reversed weights: W[a][b] = w.w[last - (a * nx + b)]
+    const int lastw = ny * nx - 1;
+    for (int q = threadIdx.x; q <= lastw; q += kBlock) tab[q] = w.w[lastw - q];
+    for (int q = threadIdx.x; q < (ry + 1) * nx; q += kBlock) {
+        const int i = q / nx, b = q - i * nx;
+        float sl = 0.0f, sh = 0.0f;
+        for (int a = 0; a < ny; ++a) {
+            const float wab = w.w[lastw - (a * nx + b)];
+            if (rows == 1 || a <= ry - i) sl += wab;
+            if (a >= ry + i) sh += wab;
+        }
+        lo[q] = sl;
+        hi[q] = sh;
+    }
+    __syncthreads();
+    const int64_t p = ((int64_t)blockIdx.x * kBlock + threadIdx.x) / kBorderG;
+    const int lg = threadIdx.x % kBorderG;
+    const bool live = p < border_pixels(rows, cols);  // (the butterfly needs every lane)
+    int64_t s = 0, t = 0;
+    const int64_t nrow = rows > 1 ? 2 : 1;
+    if (live && p < nrow * cols) {
+        s = p < cols ? 0 : rows - 1;
+        t = p < cols ? p : p - cols;
+    } else if (live) {
+        const int64_t q = p - nrow * cols;
+        s = 1 + (cols > 1 ? q >> 1 : q);
+        t = cols > 1 && (q & 1) ? cols - 1 : 0;
+    }
+    // row terms: table row k weighs input row i0 + di * k
+    const float* tr = s == 0 ? lo : s == rows - 1 ? hi : tab;
+    const int64_t i0 = s == 0 ? 0 : s == rows - 1 ? rows - 1 : s + ry;
+    const int di = s == 0 ? 1 : -1, terms = s == 0 || s == rows - 1 ? ry + 1 : ny;
+    float acc = 0.0f;
+    for (int k = live ? lg : terms; k < terms; k += kBorderG) {
+        const int64_t i = i0 + di * k;
+        if (i < 0 || i >= rows) continue;
+        const float* rk = tr + k * nx;
+        const float* gi = g + i * cols;
+        if (cols == 1) {
+            float c = 0.0f;
+            for (int b = 0; b < nx; ++b) c += rk[b];
+            acc = __builtin_fmaf(c, gi[0], acc);
+        } else if (t == 0 || t == cols - 1) {
+            // input column m from the edge, farthest first: the weights that
+            // reach the edge from it add up
+            const int dir = t == 0 ? 1 : -1;
+            const float* wm = t == 0 ? rk : rk + 2 * rx;  // weight of column m: wm[dir * (rx - m)]
+            const float* gm = gi + t;                     // column m: gm[dir * m]
+            float c = 0.0f;
+            int m = rx;
+            for (; m >= cols; --m) c += wm[dir * (rx - m)];
+#pragma unroll 4
+            for (; m >= 0; --m) {
+                c += wm[dir * (rx - m)];
+                acc = __builtin_fmaf(c, gm[dir * m], acc);
+            }
+        } else if (t >= rx && t + rx < cols) {
+            const float* gj = gi + t + rx;
+#pragma unroll 4
+            for (int b = 0; b < nx; ++b) acc = __builtin_fmaf(rk[b], gj[-b], acc);
+        } else {
+            for (int b = 0; b < nx; ++b) {
+                const int64_t j = t + rx - b;
+                if (j >= 0 && j < cols) acc = __builtin_fmaf(rk[b], gi[j], acc);
+            }
         }
     }
+#pragma unroll
+    for (int o = kBorderG >> 1; o > 0; o >>= 1) acc += __shfl_xor(acc, o);
+    if (live && lg == 0) dx[s * cols + t] = acc;
 }
 
 template <int RY, int RX>
@@ -360,230 +506,260 @@ __global__ __launch_bounds__(kBlock) void ov2_direct(const float* x, float* out,
     out[i * cols + j] = acc;
 }
 
-// store one 4-wide output segment of row i starting at column j
+__global__ __launch_bounds__(kBlock) void ov2_border(const float* g, float* dx, int64_t rows,
+                                                     int64_t cols, W2 w, int ry, int rx) {
+    __shared__ float tab[kBorderTab];
+    border_transposed(g + (int64_t)blockIdx.y * rows * cols, dx + (int64_t)blockIdx.y * rows * cols,
+                      rows, cols, w, ry, rx, tab);
+}
+
+// store one 4-wide output segment of row i starting at column j (inner: leave
+// out the first and last rows and columns, see border_transposed)
 __device__ __forceinline__ void store4(float* out, int64_t rows, int64_t cols, int64_t i,
-                                       int64_t j, const float (&v)[4]) {
-    if (i >= rows) return;
-    if (j + 4 <= cols && (cols & 3) == 0) {
+                                       int64_t j, const float (&v)[4], bool inner) {
+    if (i >= rows || (inner && (i == 0 || i == rows - 1))) return;
+    const bool whole = j + 4 <= cols && !(inner && (j == 0 || j + 4 == cols));
+    if (whole && (cols & 3) == 0) {
         // non-temporal: measured faster than plain stores for the 2D tiles
         // (9x9 separable on 4096^2: 42 us against 46 us)
         dev::store_vec_nt(f32x4{v[0], v[1], v[2], v[3]},
                           reinterpret_cast<f32x4*>(out + i * cols + j));
+    } else if (whole) {
+        // (plain: neighbouring lanes share the lines of an unaligned row)
+        *reinterpret_cast<f32x4u*>(out + i * cols + j) = f32x4{v[0], v[1], v[2], v[3]};
     } else {
 #pragma unroll
         for (int c = 0; c < 4; ++c)
-            if (j + c < cols) out[i * cols + j + c] = v[c];
+            if (j + c < cols && !(inner && (j + c == 0 || j + c == cols - 1)))
+                out[i * cols + j + c] = v[c];
     }
 }
 
-template <int RY, int RX>
+// O2b.  What bounds it from radius 2 on is the vector ALU: one multiply-add per
+// tap and output (unpacked), the weights in scalar registers, 4 x RO outputs
+// per lane so that a row read from LDS feeds RO output rows.  RO: rows per lane
+// (a tile has 16 * RO rows).  Measured, map and clamped transpose together,
+// against 64-row tiles with run-time column radii, element-wise staging of
+// unaligned rows and border tiles, and a second launch for the border pixels:
+// dense 7 x 7 on 1501 x 1999 83 -> 24 us, on 4096^2 242 -> 84; 17 x 17 on 4096^2
+// 720 -> 295 (its multiply-adds alone: 247); 5-point on 24 fields of 121 x 163
+// 21.5 -> 9.1.
+template <int RX, int RO>
 __global__ __launch_bounds__(kBlock) void ov2_lds(const float* x, float* out, int64_t rows,
-                                                  int64_t cols, W2 w, int ry_, int rx_, int edge,
-                                                  float pad, int64_t nbx, int64_t nb) {
+                                                  int64_t cols, W2 w, int ry, int edge, float pad,
+                                                  int64_t nbx, int64_t nb, int nbb) {
     // blockIdx.y: one of several equally shaped images stored back to back
     x += (int64_t)blockIdx.y * rows * cols;
     out += (int64_t)blockIdx.y * rows * cols;
-    using RD = Rad<RY, RX>;
-    constexpr int LW = RD::LW, HX = RD::HX, MY = RD::MY, MX = RD::MX;
-    const int ry = RD::dyn ? ry_ : RY, rx = RD::dyn ? rx_ : RX;
-    const int wx = 2 * rx + 1;
-    __shared__ __attribute__((aligned(16))) float tin[RD::LH * LW];
+    static_assert(RO == 1 || RO == 2, "the row loop below");
+    using CL = Cols<RX>;
+    constexpr int NX = 2 * RX + 1, LW = CL::LW;
+    extern __shared__ __attribute__((aligned(16))) float tin[];
+    if ((int)blockIdx.x < nbb) {
+        border_transposed(x, out, rows, cols, w, ry, RX, tin);
+        return;
+    }
     int64_t bx, by;
-    tile_coords(nbx, nb, bx, by);
-    const int64_t y0 = by * kTY, x0 = bx * kTX;
-    stage_tile<RD>(x, rows, cols, y0, x0, ry, edge, pad, tin);
+    if (!tile_coords((int64_t)blockIdx.x - nbb, nbx, nb, bx, by)) return;
+    const int64_t y0 = by * (16 * RO), x0 = bx * kTX;
+    stage_tile<RX>(x, rows, cols, y0, x0, 16 * RO + 2 * ry, ry, edge, pad, tin);
     __syncthreads();
     const int cg = threadIdx.x % 16, rg = threadIdx.x / 16;
-    float acc[4][4];
-#pragma unroll
-    for (int o = 0; o < 4; ++o)
-#pragma unroll
-        for (int c = 0; c < 4; ++c) acc[o][c] = 0.0f;
-    const int c0 = 4 * cg + HX - rx;  // LDS column of tap b = 0 for output column 0
-    // input row k of the block's window contributes to output row o with a = k - o
-#pragma unroll
-    for (int k = 0; k < 4 + 2 * MY; ++k) {
-        if (k >= 4 + 2 * ry) break;
-        float seg[4 + 2 * MX];
-        const float* row = tin + (4 * rg + k) * LW + c0;
-#pragma unroll
-        for (int t = 0; t < 4 + 2 * MX; ++t)
-            if (t < 4 + 2 * rx) seg[t] = row[t];
-#pragma unroll
-        for (int o = 0; o < 4; ++o) {
-            const int a = k - o;
-            if (a < 0 || a > 2 * ry) continue;
-#pragma unroll
-            for (int b = 0; b <= 2 * MX; ++b) {
-                if (b > 2 * rx) break;
-                const float wab = w.w[a * wx + b];
-#pragma unroll
-                for (int c = 0; c < 4; ++c) acc[o][c] = __builtin_fmaf(wab, seg[c + b], acc[o][c]);
-            }
-        }
-    }
-#pragma unroll
-    for (int o = 0; o < 4; ++o) store4(out, rows, cols, y0 + 4 * rg + o, x0 + 4 * cg, acc[o]);
-}
-
-template <int RY, int RX>
-__global__ __launch_bounds__(kBlock) void ov2_sep(const float* x, float* out, int64_t rows,
-                                                  int64_t cols, W2 w, int ry_, int rx_, int edge,
-                                                  float pad, int64_t nbx, int64_t nb) {
-    // blockIdx.y: one of several equally shaped images stored back to back
-    x += (int64_t)blockIdx.y * rows * cols;
-    out += (int64_t)blockIdx.y * rows * cols;
-    using RD = Rad<RY, RX>;
-    constexpr int LW = RD::LW, HX = RD::HX, MY = RD::MY, MX = RD::MX;
-    constexpr int HW = kTX + 4;  // row-pass buffer stride (padded)
-    const int ry = RD::dyn ? ry_ : RY, rx = RD::dyn ? rx_ : RX;
-    __shared__ __attribute__((aligned(16))) float tin[RD::LH * LW];
-    __shared__ __attribute__((aligned(16))) float th[RD::LH * HW];
-    int64_t bx, by;
-    tile_coords(nbx, nb, bx, by);
-    const int64_t y0 = by * kTY, x0 = bx * kTX;
-    stage_tile<RD>(x, rows, cols, y0, x0, ry, edge, pad, tin);
-    __syncthreads();
-    const int cg = threadIdx.x % 16, rg = threadIdx.x / 16;
-    // row pass: th[y][x] = sum_b wx[b] * in[y][x + b - rx] for all staged rows
-    const int nrows = kTY + 2 * ry;
-    for (int y = rg; y < nrows; y += 16) {
-        const float* row = tin + y * LW + 4 * cg + HX - rx;
-        float seg[4 + 2 * MX];
-#pragma unroll
-        for (int t = 0; t < 4 + 2 * MX; ++t)
-            if (t < 4 + 2 * rx) seg[t] = row[t];
-        float h[4] = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int b = 0; b <= 2 * MX; ++b) {
-            if (b > 2 * rx) break;
-#pragma unroll
-            for (int c = 0; c < 4; ++c) h[c] = __builtin_fmaf(w.wx[b], seg[c + b], h[c]);
-        }
-        *reinterpret_cast<f32x4*>(th + y * HW + 4 * cg) = f32x4{h[0], h[1], h[2], h[3]};
-    }
-    __syncthreads();
-    // column pass: out[y][x] = sum_a wy[a] * th[y + a][x]
-    float acc[4][4];
-#pragma unroll
-    for (int o = 0; o < 4; ++o)
-#pragma unroll
-        for (int c = 0; c < 4; ++c) acc[o][c] = 0.0f;
-#pragma unroll
-    for (int k = 0; k < 4 + 2 * MY; ++k) {
-        if (k >= 4 + 2 * ry) break;
-        const f32x4 v = *reinterpret_cast<const f32x4*>(th + (4 * rg + k) * HW + 4 * cg);
-#pragma unroll
-        for (int o = 0; o < 4; ++o) {
-            const int a = k - o;
-            if (a < 0 || a > 2 * ry) continue;
-            const float wa = w.wy[a];
-            acc[o][0] = __builtin_fmaf(wa, v.x, acc[o][0]);
-            acc[o][1] = __builtin_fmaf(wa, v.y, acc[o][1]);
-            acc[o][2] = __builtin_fmaf(wa, v.z, acc[o][2]);
-            acc[o][3] = __builtin_fmaf(wa, v.w, acc[o][3]);
-        }
-    }
-#pragma unroll
-    for (int o = 0; o < 4; ++o) store4(out, rows, cols, y0 + 4 * rg + o, x0 + 4 * cg, acc[o]);
-}
-
-// O2d: separable, with the row pass read straight from global memory through
-// the L1 cache (each lane loads its 4 + 2*HX aligned inputs as 16-byte
-// vectors; neighbouring lanes' overlaps hit L1), so LDS holds only the
-// row-pass result of a 64 x 32 tile.  The small LDS footprint allows full
-// occupancy, and the 32-row tile keeps 4x more workgroups in flight than the
-// 64 x 64 tile.
-#ifndef SKEL_O2D_TY
-#define SKEL_O2D_TY 32
-#endif
-constexpr int kTY2 = SKEL_O2D_TY;
-
-template <int RY, int RX>
-__global__ __launch_bounds__(kBlock) void ov2_sep_l1(const float* x, float* out, int64_t rows,
-                                                     int64_t cols, W2 w, int ry_, int rx_,
-                                                     int edge, float pad, int64_t nbx,
-                                                     int64_t nb) {
-    // blockIdx.y: one of several equally shaped images stored back to back
-    x += (int64_t)blockIdx.y * rows * cols;
-    out += (int64_t)blockIdx.y * rows * cols;
-    using RD = Rad<RY, RX>;
-    constexpr int MY = RD::MY, MX = RD::MX, HX = RD::HX;
-    constexpr int HW = kTX + 4;              // row-pass buffer stride (padded)
-    constexpr int LH = kTY2 + 2 * MY;        // row-pass rows
-    constexpr int NV = (4 + 2 * HX) / 4;     // 16-byte vectors per lane and row
-    constexpr int RO = kTY2 / 16;            // output rows per lane
-    const int ry = RD::dyn ? ry_ : RY, rx = RD::dyn ? rx_ : RX;
-    __shared__ __attribute__((aligned(16))) float th[LH * HW];
-    int64_t bx, by;
-    tile_coords(nbx, nb, bx, by);
-    const int64_t y0 = by * kTY2, x0 = bx * kTX;
-    const bool interior = y0 - ry >= 0 && y0 + kTY2 + ry <= rows && x0 - HX >= 0 &&
-                          x0 + kTX + HX <= cols && (cols & 3) == 0;
-    const int cg = threadIdx.x % 16, rg = threadIdx.x / 16;
-    const int nrows = kTY2 + 2 * ry;
-    // row pass: every row this lane handles is loaded before any arithmetic
-    // (kIt rows of NV 16-byte vectors in flight per lane)
-    constexpr int kIt = (LH + 15) / 16;
-    float seg[kIt][4 + 2 * HX];
-#pragma unroll
-    for (int it = 0; it < kIt; ++it) {
-        const int y = rg + 16 * it;
-        if (y >= nrows) continue;
-        const int64_t gy = y0 - ry + y;
-        if (interior) {
-            const float* src = x + gy * cols + (x0 - HX + 4 * cg);
-#pragma unroll
-            for (int v = 0; v < NV; ++v) {
-                const f32x4 t = *reinterpret_cast<const f32x4*>(src + 4 * v);
-                seg[it][4 * v] = t.x;
-                seg[it][4 * v + 1] = t.y;
-                seg[it][4 * v + 2] = t.z;
-                seg[it][4 * v + 3] = t.w;
-            }
-        } else {
-#pragma unroll
-            for (int t = 0; t < 4 + 2 * HX; ++t)
-                seg[it][t] = fetch2(x, rows, cols, gy, x0 - HX + 4 * cg + t, edge, pad);
-        }
-    }
-#pragma unroll
-    for (int it = 0; it < kIt; ++it) {
-        const int y = rg + 16 * it;
-        if (y >= nrows) continue;
-        float h[4] = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int b = 0; b <= 2 * MX; ++b) {
-            if (b > 2 * rx) break;
-#pragma unroll
-            for (int c = 0; c < 4; ++c)
-                h[c] = __builtin_fmaf(w.wx[b], seg[it][c + b + HX - rx], h[c]);
-        }
-        *reinterpret_cast<f32x4*>(th + y * HW + 4 * cg) = f32x4{h[0], h[1], h[2], h[3]};
-    }
-    __syncthreads();
     float acc[RO][4];
 #pragma unroll
     for (int o = 0; o < RO; ++o)
 #pragma unroll
         for (int c = 0; c < 4; ++c) acc[o][c] = 0.0f;
+    // input row k of the lane's window contributes to output row o with weight
+    // row k - o: to both rows of a pair but for the first and last k
+    const float* win = tin + RO * rg * LW + 4 * cg;
+    const auto row_of = [&](int k, float (&seg)[4 * CL::NV]) {
 #pragma unroll
-    for (int k = 0; k < RO + 2 * MY; ++k) {
-        if (k >= RO + 2 * ry) break;
-        const f32x4 v = *reinterpret_cast<const f32x4*>(th + (RO * rg + k) * HW + 4 * cg);
+        for (int v = 0; v < CL::NV; ++v) {
+            const f32x4 q = *reinterpret_cast<const f32x4*>(win + k * LW + 4 * v);
+            seg[4 * v] = q.x;
+            seg[4 * v + 1] = q.y;
+            seg[4 * v + 2] = q.z;
+            seg[4 * v + 3] = q.w;
+        }
+    };
+    const auto add = [&](float (&o)[4], const float* wr, const float (&seg)[4 * CL::NV]) {
 #pragma unroll
-        for (int o = 0; o < RO; ++o) {
-            const int a = k - o;
-            if (a < 0 || a > 2 * ry) continue;
-            const float wa = w.wy[a];
-            acc[o][0] = __builtin_fmaf(wa, v.x, acc[o][0]);
-            acc[o][1] = __builtin_fmaf(wa, v.y, acc[o][1]);
-            acc[o][2] = __builtin_fmaf(wa, v.z, acc[o][2]);
-            acc[o][3] = __builtin_fmaf(wa, v.w, acc[o][3]);
+        for (int b = 0; b < NX; ++b)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) o[c] = __builtin_fmaf(wr[b], seg[CL::HX - RX + b + c], o[c]);
+    };
+    float seg[4 * CL::NV];
+    row_of(0, seg);
+    add(acc[0], w.w, seg);
+    for (int k = 1; k <= 2 * ry; ++k) {
+        row_of(k, seg);
+        add(acc[0], w.w + k * NX, seg);
+        if constexpr (RO == 2) add(acc[1], w.w + (k - 1) * NX, seg);
+    }
+    if constexpr (RO == 2) {
+        row_of(2 * ry + 1, seg);
+        add(acc[1], w.w + 2 * ry * NX, seg);
+    }
+#pragma unroll
+    for (int o = 0; o < RO; ++o)
+        store4(out, rows, cols, y0 + RO * rg + o, x0 + 4 * cg, acc[o], nbb > 0);
+}
+
+// the column pass of the separable tiles: RO output rows per lane from the
+// row-filtered tile th (row stride kHW)
+template <int RO>
+__device__ __forceinline__ void column_pass(const float* th, const W2& w, int ry, int rg, int cg,
+                                            float (&acc)[RO][4]) {
+#pragma unroll
+    for (int o = 0; o < RO; ++o)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) acc[o][c] = 0.0f;
+    // filtered row k contributes to output row o with weight k - o
+    const float* win = th + RO * rg * kHW + 4 * cg;
+    const auto add = [&](float (&o)[4], float wa, f32x4 v) {
+#pragma unroll
+        for (int c = 0; c < 4; ++c) o[c] = __builtin_fmaf(wa, v[c], o[c]);
+    };
+    add(acc[0], w.wy[0], *reinterpret_cast<const f32x4*>(win));
+#pragma unroll 4
+    for (int k = 1; k <= 2 * ry; ++k) {
+        const f32x4 v = *reinterpret_cast<const f32x4*>(win + k * kHW);
+        add(acc[0], w.wy[k], v);
+        if constexpr (RO == 2) add(acc[1], w.wy[k - 1], v);
+    }
+    if constexpr (RO == 2)
+        add(acc[1], w.wy[2 * ry], *reinterpret_cast<const f32x4*>(win + (2 * ry + 1) * kHW));
+}
+
+// O2c: the staged tile filtered along its rows into a second LDS buffer
+template <int RX, int RO>
+__global__ __launch_bounds__(kBlock) void ov2_sep(const float* x, float* out, int64_t rows,
+                                                  int64_t cols, W2 w, int ry, int edge, float pad,
+                                                  int64_t nbx, int64_t nb, int nbb) {
+    // blockIdx.y: one of several equally shaped images stored back to back
+    x += (int64_t)blockIdx.y * rows * cols;
+    out += (int64_t)blockIdx.y * rows * cols;
+    using CL = Cols<RX>;
+    constexpr int LW = CL::LW;
+    extern __shared__ __attribute__((aligned(16))) float tin[];
+    if ((int)blockIdx.x < nbb) {
+        border_transposed(x, out, rows, cols, w, ry, RX, tin);
+        return;
+    }
+    const int nrows = 16 * RO + 2 * ry;
+    float* th = tin + nrows * LW;
+    int64_t bx, by;
+    if (!tile_coords((int64_t)blockIdx.x - nbb, nbx, nb, bx, by)) return;
+    const int64_t y0 = by * (16 * RO), x0 = bx * kTX;
+    stage_tile<RX>(x, rows, cols, y0, x0, nrows, ry, edge, pad, tin);
+    __syncthreads();
+    const int cg = threadIdx.x % 16, rg = threadIdx.x / 16;
+    // row pass: th[y][x] = sum_b wx[b] * in[y][x + b - rx] for all staged rows
+    for (int y = rg; y < nrows; y += 16) {
+        const float* row = tin + y * LW + 4 * cg;
+        float seg[4 * CL::NV];
+#pragma unroll
+        for (int v = 0; v < CL::NV; ++v) {
+            const f32x4 q = *reinterpret_cast<const f32x4*>(row + 4 * v);
+            seg[4 * v] = q.x;
+            seg[4 * v + 1] = q.y;
+            seg[4 * v + 2] = q.z;
+            seg[4 * v + 3] = q.w;
+        }
+        f32x4 h = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int b = 0; b <= 2 * RX; ++b)
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+                h[c] = __builtin_fmaf(w.wx[b], seg[CL::HX - RX + b + c], h[c]);
+        *reinterpret_cast<f32x4*>(th + y * kHW + 4 * cg) = h;
+    }
+    __syncthreads();
+    float acc[RO][4];
+    column_pass<RO>(th, w, ry, rg, cg, acc);
+#pragma unroll
+    for (int o = 0; o < RO; ++o)
+        store4(out, rows, cols, y0 + RO * rg + o, x0 + 4 * cg, acc[o], nbb > 0);
+}
+
+// O2d: separable, with the row pass read straight from global memory through
+// the L1 cache (each lane loads its 4 + 2*HX inputs as 16-byte vectors;
+// neighbouring lanes' overlaps hit L1), so LDS holds only the row-pass result
+// of a 64 x 16*RO tile.  The small LDS footprint allows full occupancy, and the
+// low tiles keep many workgroups in flight.  Measured as O2b: 7 x 7 on 1501 x 1999
+// 97 -> 25 us, on 4096^2 440 -> 68; 9 x 9 on 4096^2 80 -> 73 (the map 36, the
+// transpose 36 + 12 for its border before).
+template <int RX, int RO>
+// (eight wavefronts per SIMD for radii up to 4: 64 registers where 66 would
+// leave seven; 8192^2 9 x 9, map and transpose, 230 -> 225 us)
+__global__ __launch_bounds__(kBlock, RX <= 4 ? 8 : 1) void ov2_sep_l1(const float* x, float* out, int64_t rows,
+                                                     int64_t cols, W2 w, int ry, int edge,
+                                                     float pad, int64_t nbx, int64_t nb, int nbb) {
+    // blockIdx.y: one of several equally shaped images stored back to back
+    x += (int64_t)blockIdx.y * rows * cols;
+    out += (int64_t)blockIdx.y * rows * cols;
+    using CL = Cols<RX>;
+    constexpr int HX = CL::HX, NV = CL::NV;
+    extern __shared__ __attribute__((aligned(16))) float th[];
+    if ((int)blockIdx.x < nbb) {
+        border_transposed(x, out, rows, cols, w, ry, RX, th);
+        return;
+    }
+    int64_t bx, by;
+    if (!tile_coords((int64_t)blockIdx.x - nbb, nbx, nb, bx, by)) return;
+    const int64_t y0 = by * (16 * RO), x0 = bx * kTX;
+    const int nrows = 16 * RO + 2 * ry;
+    const bool interior = y0 - ry >= 0 && y0 - ry + nrows <= rows && x0 - HX >= 0 &&
+                          x0 + kTX + HX <= cols;
+    const int cg = threadIdx.x % 16, rg = threadIdx.x / 16;
+    // row pass: every row this lane handles is loaded before any arithmetic
+    // (kIt rows of NV 16-byte vectors in flight per lane)
+    constexpr int kIt = RO + 1;  // covers 16 * RO + 2 * ry rows, 2 * ry <= 16
+    static_assert(2 * SKEL_MAX_RADIUS_2D <= 16, "rows of the row pass");
+    f32x4 seg[kIt][NV];
+    if (interior) {
+        const float* src = x + (y0 - ry + rg) * cols + (x0 - HX + 4 * cg);
+#pragma unroll
+        for (int it = 0; it < kIt; ++it)
+            if (rg + 16 * it < nrows)
+#pragma unroll
+                for (int v = 0; v < NV; ++v)
+                    seg[it][v] = *reinterpret_cast<const f32x4u*>(src + 16 * it * cols + 4 * v);
+    } else {
+#pragma unroll
+        for (int it = 0; it < kIt; ++it) {
+            const int64_t i = y0 - ry + rg + 16 * it;
+            if (rg + 16 * it >= nrows) continue;
+#pragma unroll
+            for (int v = 0; v < NV; ++v) {
+                const int64_t j = x0 - HX + 4 * (cg + v);
+                seg[it][v] = i >= rows + ry || j >= cols + RX
+                                 ? f32x4{0.f, 0.f, 0.f, 0.f}
+                                 : fetch4(x, rows, cols, i, j, edge, pad);
+            }
         }
     }
 #pragma unroll
-    for (int o = 0; o < RO; ++o) store4(out, rows, cols, y0 + RO * rg + o, x0 + 4 * cg, acc[o]);
+    for (int it = 0; it < kIt; ++it) {
+        const int y = rg + 16 * it;
+        if (y >= nrows) continue;
+        f32x4 h = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int b = 0; b <= 2 * RX; ++b)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                const int e = HX - RX + b + c;
+                h[c] = __builtin_fmaf(w.wx[b], seg[it][e / 4][e % 4], h[c]);
+            }
+        *reinterpret_cast<f32x4*>(th + y * kHW + 4 * cg) = h;
+    }
+    __syncthreads();
+    float acc[RO][4];
+    column_pass<RO>(th, w, ry, rg, cg, acc);
+#pragma unroll
+    for (int o = 0; o < RO; ++o)
+        store4(out, rows, cols, y0 + RO * rg + o, x0 + 4 * cg, acc[o], nbb > 0);
 }
 
 // O2e.  A workgroup's four wavefronts take four vertically stacked strips,
@@ -614,29 +790,20 @@ struct March {
     static_assert(chunk % NW == 0 && (rows + 2 * RY) % chunk == 0, "whole chunks per strip");
 };
 
-// four consecutive columns starting at j of row rp, through the column rule
-__device__ __forceinline__ f32x4 fetch_row4(const float* rp, int64_t cols, int64_t j,
-                                            bool aligned, int edge, float pad) {
-    if (aligned && j >= 0 && j + 4 <= cols) return *reinterpret_cast<const f32x4*>(rp + j);
-    float v[4];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        int64_t c;
-        v[q] = border(j + q, cols, edge, c) ? rp[c] : pad;
-    }
-    return f32x4{v[0], v[1], v[2], v[3]};
-}
-
 // Add loaded row m of a strip (held in ring position t = m mod (2ry+1)) into
 // the output rows it feeds, then store output row m - 2ry, now complete, and
 // clear its slot for row m + 1.  c: this lane's four columns; e: the chunk
 // beyond the strip's end read by lanes 0 (left) and 63 (right).  SEP: the
 // weights are factors, so the row is filtered once with wx and the result
-// added with wy[a] (the LDS separable variants' order of operations).
-template <int RY, int MX, bool SEP>
+// added with wy[a] (the LDS separable variants' order of operations).  STORE:
+// how the lane's four columns are stored (MS_EACH: one by one, those inside the
+// row only).
+enum MarchStore { MS_NT, MS_VEC, MS_EACH };
+
+template <int RY, int MX, bool SEP, int STORE>
 __device__ __forceinline__ void march_row(float (&acc)[2 * RY + 1][4], int t, int m, f32x4 c,
                                           f32x4 e, const W2& w, int rx, float* out,
-                                          int64_t i0, int64_t j, int64_t cols, bool vec_store) {
+                                          int64_t i0, int64_t j, int64_t cols) {
     constexpr int NW = 2 * RY + 1;
     const int nx = 2 * rx + 1;
     const f32x4 lt = dev::wave_shift_up(c, e), rt = dev::wave_shift_down(c, e);
@@ -672,13 +839,15 @@ __device__ __forceinline__ void march_row(float (&acc)[2 * RY + 1][4], int t, in
     const int sd = (t + 1) % NW;
     if (m >= 2 * RY) {
         float* op = out + (i0 + m - 2 * RY) * cols;
-        if (vec_store) {
-            dev::store_vec_nt(f32x4{acc[sd][0], acc[sd][1], acc[sd][2], acc[sd][3]},
-                              reinterpret_cast<f32x4*>(op + j));
+        const f32x4 o = {acc[sd][0], acc[sd][1], acc[sd][2], acc[sd][3]};
+        if constexpr (STORE == MS_NT) {
+            dev::store_vec_nt(o, reinterpret_cast<f32x4*>(op + j));
+        } else if constexpr (STORE == MS_VEC) {
+            *reinterpret_cast<f32x4u*>(op + j) = o;
         } else {
 #pragma unroll
             for (int q = 0; q < 4; ++q)
-                if (j + q < cols) op[j + q] = acc[sd][q];
+                if (j + q < cols) op[j + q] = o[q];
         }
     }
 #pragma unroll
@@ -688,7 +857,7 @@ __device__ __forceinline__ void march_row(float (&acc)[2 * RY + 1][4], int t, in
 template <int RY, int RX, bool SEP>
 __global__ __launch_bounds__(kBlock) void ov2_march(const float* x, float* out, int64_t rows,
                                                     int64_t cols, W2 w, int rx_, int edge,
-                                                    float pad, int64_t nbx, int64_t nb) {
+                                                    float pad, int64_t nbx) {
     // blockIdx.y: one of several equally shaped images stored back to back
     x += (int64_t)blockIdx.y * rows * cols;
     out += (int64_t)blockIdx.y * rows * cols;
@@ -714,48 +883,54 @@ __global__ __launch_bounds__(kBlock) void ov2_march(const float* x, float* out, 
 #pragma unroll
         for (int q = 0; q < 4; ++q) acc[s][q] = 0.0f;
     int m0 = 0;
-    // fast path: the strip lies inside the row, so every row is two
-    // unconditional 16-byte loads per lane.  Rows beyond the image ends (at
+    // fast path: the strip and its edge chunk lie inside the row (or the strip
+    // ends with it), so every row is two unconditional 16-byte loads per lane, at
+    // any alignment of the rows.  Rows beyond the image ends (at
     // most ry <= rows away) and the edge chunks beyond the row ends map by the
     // edge rule without branches: cyclic reads the chunk at the other end,
     // clamp repeats the row's end value, const takes the pad.
-    if (aligned && j0 + kMarchCols <= cols && rows >= kMarchMaxR) {
+    const int64_t after = cols - (j0 + kMarchCols);  // columns beyond the strip
+    if ((after == 0 || after >= 4) && rows >= kMarchMaxR) {
         const bool lo = l == 0 && j0 == 0, hi = l == dev::kWave - 1 && j0 + kMarchCols == cols;
         const bool efix = (lo || hi) && edge != SKEL_EDGE_CYCLIC;
         const int64_t jf = lo ? cols - 4 : hi ? 0 : je;
         const int64_t jr = efix ? j : jf;
-        for (; m0 + CH <= nin; m0 += CH) {
-            f32x4 c[CH], e[CH];
-            bool in[CH];
+        const auto strip = [&](auto store) {
+            for (; m0 + CH <= nin; m0 += CH) {
+                f32x4 c[CH], e[CH];
+                bool in[CH];
 #pragma unroll
-            for (int t = 0; t < CH; ++t) {
-                const int64_t k = i0 - RY + m0 + t;
-                in[t] = k >= 0 && k < rows;
-                const int64_t kk = in[t] ? k
-                                 : edge == SKEL_EDGE_CYCLIC ? (k < 0 ? k + rows : k - rows)
-                                 : (k < 0 ? 0 : rows - 1);
-                c[t] = *reinterpret_cast<const f32x4*>(x + kk * cols + j);
-                e[t] = *reinterpret_cast<const f32x4*>(x + kk * cols + jr);
-            }
+                for (int t = 0; t < CH; ++t) {
+                    const int64_t k = i0 - RY + m0 + t;
+                    in[t] = k >= 0 && k < rows;
+                    const int64_t kk = in[t] ? k
+                                     : edge == SKEL_EDGE_CYCLIC ? (k < 0 ? k + rows : k - rows)
+                                     : (k < 0 ? 0 : rows - 1);
+                    c[t] = *reinterpret_cast<const f32x4u*>(x + kk * cols + j);
+                    e[t] = *reinterpret_cast<const f32x4u*>(x + kk * cols + jr);
+                }
 #pragma unroll
-            for (int t = 0; t < CH; ++t) {
-                if (edge == SKEL_EDGE_CONST && !in[t]) {
-                    c[t] = f32x4{pad, pad, pad, pad};
-                    e[t] = c[t];
+                for (int t = 0; t < CH; ++t) {
+                    if (edge == SKEL_EDGE_CONST && !in[t]) {
+                        c[t] = f32x4{pad, pad, pad, pad};
+                        e[t] = c[t];
+                    }
+                    if (efix) {
+                        const float b = edge == SKEL_EDGE_CONST ? pad : lo ? c[t].x : c[t].w;
+                        e[t] = f32x4{b, b, b, b};
+                    }
+                    march_row<RY, MX, SEP, decltype(store)::value>(
+                        acc, t % NW, m0 + t, c[t], e[t], w, rx, out, i0, j, cols);
                 }
-                if (efix) {
-                    const float b = edge == SKEL_EDGE_CONST ? pad : lo ? c[t].x : c[t].w;
-                    e[t] = f32x4{b, b, b, b};
-                }
-                march_row<RY, MX, SEP>(acc, t % NW, m0 + t, c[t], e[t], w, rx, out, i0, j, cols,
-                                  true);
             }
-        }
+        };
+        if (aligned) strip(std::integral_constant<int, MS_NT>());
+        else strip(std::integral_constant<int, MS_VEC>());
     } else if (rows >= kMarchMaxR) {
-        // a strip past a ragged row end, or rows not 16-byte aligned: the
-        // column rule is the same for every row, so each lane maps its four
-        // columns and the edge chunk once; rows are then straight-line element
-        // loads from valid addresses, with the pad selected afterwards
+        // a strip past a ragged row end: the column rule is the same for every
+        // row, so each lane maps its four columns and the edge chunk once; rows
+        // are then straight-line element loads from valid addresses, with the pad
+        // selected afterwards
         int64_t ci[4], ei[4];
         bool cp[4], ep[4];
 #pragma unroll
@@ -766,7 +941,6 @@ __global__ __launch_bounds__(kBlock) void ov2_march(const float* x, float* out, 
             ep[q] = !border(je + q, cols, edge, cc);
             ei[q] = ep[q] ? 0 : cc;
         }
-        const bool vec_store = aligned && j + 4 <= cols;
         for (; m0 + CH <= nin; m0 += CH) {
             float cv[CH][4], ev[CH][4];
             bool in[CH];
@@ -793,9 +967,9 @@ __global__ __launch_bounds__(kBlock) void ov2_march(const float* x, float* out, 
                     c[q] = padrow || cp[q] ? pad : cv[t][q];
                     e[q] = padrow || ep[q] ? pad : ev[t][q];
                 }
-                march_row<RY, MX, SEP>(acc, t % NW, m0 + t, f32x4{c[0], c[1], c[2], c[3]},
-                                       f32x4{e[0], e[1], e[2], e[3]}, w, rx, out, i0, j, cols,
-                                       vec_store);
+                march_row<RY, MX, SEP, MS_EACH>(
+                    acc, t % NW, m0 + t, f32x4{c[0], c[1], c[2], c[3]},
+                    f32x4{e[0], e[1], e[2], e[3]}, w, rx, out, i0, j, cols);
             }
         }
     }
@@ -810,10 +984,10 @@ __global__ __launch_bounds__(kBlock) void ov2_march(const float* x, float* out, 
             f32x4 c = {pad, pad, pad, pad}, e = {pad, pad, pad, pad};
             if (border(i0 - RY + m, rows, edge, kk)) {
                 const float* rp = x + kk * cols;
-                c = fetch_row4(rp, cols, j, aligned, edge, pad);
-                if (l == 0 || l == dev::kWave - 1) e = fetch_row4(rp, cols, je, aligned, edge, pad);
+                c = fetch_row4(rp, cols, j, edge, pad);
+                if (l == 0 || l == dev::kWave - 1) e = fetch_row4(rp, cols, je, edge, pad);
             }
-            march_row<RY, MX, SEP>(acc, t, m, c, e, w, rx, out, i0, j, cols, aligned && j + 4 <= cols);
+            march_row<RY, MX, SEP, MS_EACH>(acc, t, m, c, e, w, rx, out, i0, j, cols);
         }
     }
 }
@@ -843,77 +1017,140 @@ skel_status run1d(int v, const float* x, float* out, int64_t n, const W1& w, int
     return launch_check("overlap1d_shuffle");
 }
 
+// One launch over `fields` images.  nbb: workgroups per image for the border
+// pixels of a clamped transpose (0: the plain map).
+struct Call2 {
+    const float* x;
+    float* out;
+    int64_t rows, cols;
+    unsigned fields;
+    const W2& w;
+    bool sep;
+    int ry, rx, edge;
+    float pad;
+    int nbb;
+    int cus;
+    hipStream_t st;
+};
+
 template <int RY, int RX, bool SEP>
-skel_status run2d_march(const float* x, float* out, int64_t rows, int64_t cols, unsigned fields,
-                        const W2& w, int ry, int rx, int edge, float pad, hipStream_t st) {
-    const int64_t nbx = div_up(cols, kMarchCols);
-    constexpr int64_t kWaves = kBlock / dev::kWave;
-    if constexpr (RY >= 0) {
-        const int64_t nb = nbx * div_up(rows, March<RY, (RX < 0)>::rows * kWaves);
-        ov2_march<RY, RX, SEP><<<dim3((unsigned)nb, fields), kBlock, 0, st>>>(
-            x, out, rows, cols, w, rx, edge, pad, nbx, nb);
-    } else {
-        switch (ry) {
-#define SKEL_O2E_CASE(R)                                                                       \
-    case R: {                                                                                  \
-        const int64_t nb = nbx * div_up(rows, March<R, true>::rows * kWaves);                  \
-        ov2_march<R, -1, SEP><<<dim3((unsigned)nb, fields), kBlock, 0, st>>>(                  \
-            x, out, rows, cols, w, rx, edge, pad, nbx, nb);                                    \
-        break;                                                                                 \
+void march_launch(const Call2& c) {
+    const int64_t nbx = div_up(c.cols, kMarchCols);
+    const int64_t nb = nbx * div_up(c.rows, March<RY, (RX < 0)>::rows * (kBlock / dev::kWave));
+    ov2_march<RY, RX, SEP><<<dim3((unsigned)nb, c.fields), kBlock, 0, c.st>>>(
+        c.x, c.out, c.rows, c.cols, c.w, c.rx, c.edge, c.pad, nbx);
+}
+
+template <int RY, int RX>
+void march_form(const Call2& c) {
+    if (c.sep) march_launch<RY, RX, true>(c);
+    else march_launch<RY, RX, false>(c);
+}
+
+// selectable for ry, rx <= 4 only
+skel_status run2d_march(const Call2& c) {
+    if (c.ry == c.rx && (c.ry == 1 || c.ry == 2 || c.ry == 4)) {
+        if (c.ry == 1) march_form<1, 1>(c);
+        else if (c.ry == 2) march_form<2, 2>(c);
+        else march_form<4, 4>(c);
+        return launch_check("overlap2d_march");
     }
-            SKEL_O2E_CASE(0)
-            SKEL_O2E_CASE(1)
-            SKEL_O2E_CASE(2)
-            SKEL_O2E_CASE(3)
-            SKEL_O2E_CASE(4)
-#undef SKEL_O2E_CASE
-        default: return SKEL_E_UNSUPPORTED;
-        }
+    switch (c.ry) {
+    case 0: march_form<0, -1>(c); break;
+    case 1: march_form<1, -1>(c); break;
+    case 2: march_form<2, -1>(c); break;
+    case 3: march_form<3, -1>(c); break;
+    case 4: march_form<4, -1>(c); break;
+    default: return SKEL_E_UNSUPPORTED;
     }
     return launch_check("overlap2d_march");
 }
 
 template <int RY, int RX>
-skel_status run2d(int v, const float* x, float* out, int64_t rows, int64_t cols,
-                  unsigned fields, const W2& w, bool sep, int ry, int rx, int edge, float pad,
-                  hipStream_t st) {
-    if (v == O2A_DIRECT) {
-        const int64_t nbx = div_up(cols, 64), nby = div_up(rows, 4);
-        ov2_direct<RY, RX><<<dim3((unsigned)(nbx * nby), fields), kBlock, 0, st>>>(
-            x, out, rows, cols, w, ry, rx, edge, pad, nbx);
-        return launch_check("overlap2d_direct");
-    }
-    if (v == O2E_MARCH)  // selectable for ry, rx <= 4 only
-        return sep ? run2d_march<RY, RX, true>(x, out, rows, cols, fields, w, ry, rx, edge, pad, st)
-                   : run2d_march<RY, RX, false>(x, out, rows, cols, fields, w, ry, rx, edge, pad,
-                                                st);
-    if (v == O2D_SEPARABLE_L1) {
-        const int64_t nbx = div_up(cols, kTX), nb = nbx * div_up(rows, kTY2);
-        ov2_sep_l1<RY, RX><<<dim3((unsigned)nb, fields), kBlock, 0, st>>>(
-            x, out, rows, cols, w, ry, rx, edge, pad, nbx, nb);
-        return launch_check("overlap2d_separable_l1");
-    }
-    const int64_t nbx = div_up(cols, kTX), nby = div_up(rows, kTY), nb = nbx * nby;
-    if (v == O2B_LDS_TILE) {
-        ov2_lds<RY, RX><<<dim3((unsigned)nb, fields), kBlock, 0, st>>>(
-            x, out, rows, cols, w, ry, rx, edge, pad, nbx, nb);
-        return launch_check("overlap2d_lds");
-    }
-    ov2_sep<RY, RX><<<dim3((unsigned)nb, fields), kBlock, 0, st>>>(x, out, rows, cols, w, ry,
-                                                                   rx, edge, pad, nbx, nb);
-    return launch_check("overlap2d_separable");
+skel_status run2d_direct(const Call2& c) {
+    const int64_t nbx = div_up(c.cols, 64), nby = div_up(c.rows, 4);
+    ov2_direct<RY, RX><<<dim3((unsigned)(nbx * nby), c.fields), kBlock, 0, c.st>>>(
+        c.x, c.out, c.rows, c.cols, c.w, c.ry, c.rx, c.edge, c.pad, nbx);
+    return launch_check("overlap2d_direct");
 }
 
-template <int RY, int RX>
-skel_status run2d_fields(int v, const float* x, float* out, int64_t rows, int64_t cols,
-                         int64_t fields, const W2& w, bool sep, int ry, int rx, int edge,
-                         float pad, hipStream_t st) {
-    const int64_t img = rows * cols;
+// grid and LDS of one tile launch; bytes_per_row: LDS per row of the tile
+template <class K>
+void tile_launch(K kern, int ro, size_t bytes_per_row, const Call2& c) {
+    const int64_t nbx = div_up(c.cols, kTX), nb = nbx * div_up(c.rows, 16 * ro);
+    size_t lds = (16 * ro + 2 * c.ry) * bytes_per_row;
+    if (c.nbb) lds = std::max(lds, kBorderTab * sizeof(float));
+    kern<<<dim3((unsigned)((nb + 7) / 8 * 8 + c.nbb), c.fields), kBlock, lds, c.st>>>(
+        c.x, c.out, c.rows, c.cols, c.w, c.ry, c.edge, c.pad, nbx, nb, c.nbb);
+}
+
+// Rows per lane (a tile has 16 times as many).  One row per lane keeps more
+// workgroups in flight, whose loads overlap other workgroups' arithmetic; two
+// share a row's LDS reads and halo.  With 16 workgroups per CU left at two rows
+// (2^23 pixels) the second is level or better, below it the first (map and
+// transpose, one / two rows per lane: 200 x 300 5-point 8.4 / 10.6 us, dense
+// 17 x 17 21.6 / 27.2; 1501 x 1999 dense 9 x 9 30.4 / 34.1, separable 25.9 /
+// 32.7; 4096^2 5-point 63.5 / 58.6, dense 9 x 9 116 / 112).  Four and eight
+// rows per lane and tiles of 128 and 256 columns measured slower (4096^2 dense
+// 9 x 9: 115-153 us).
+template <int RX>
+skel_status tile_form(int v, const Call2& c) {
+    const int64_t tiles = div_up(c.cols, kTX) * div_up(c.rows, 16) * c.fields;
+    const bool two = tiles >= 32 * (int64_t)c.cus;
+    constexpr size_t in_row = Cols<RX>::LW * sizeof(float), th_row = kHW * sizeof(float);
+    if (v == O2B_LDS_TILE) {
+        if (two) tile_launch(ov2_lds<RX, 2>, 2, in_row, c);
+        else tile_launch(ov2_lds<RX, 1>, 1, in_row, c);
+        return launch_check("overlap2d_lds");
+    }
+    if (v == O2C_LDS_SEPARABLE) {
+        if (two) tile_launch(ov2_sep<RX, 2>, 2, in_row + th_row, c);
+        else tile_launch(ov2_sep<RX, 1>, 1, in_row + th_row, c);
+        return launch_check("overlap2d_separable");
+    }
+    if (two) tile_launch(ov2_sep_l1<RX, 2>, 2, th_row, c);
+    else tile_launch(ov2_sep_l1<RX, 1>, 1, th_row, c);
+    return launch_check("overlap2d_separable_l1");
+}
+
+skel_status run2d_tile(int v, const Call2& c) {
+    switch (c.rx) {
+    case 0: return tile_form<0>(v, c);
+    case 1: return tile_form<1>(v, c);
+    case 2: return tile_form<2>(v, c);
+    case 3: return tile_form<3>(v, c);
+    case 4: return tile_form<4>(v, c);
+    case 5: return tile_form<5>(v, c);
+    case 6: return tile_form<6>(v, c);
+    case 7: return tile_form<7>(v, c);
+    case 8: return tile_form<8>(v, c);
+    default: return SKEL_E_UNSUPPORTED;
+    }
+}
+
+skel_status run2d(int v, const Call2& c) {
+    if (v == O2E_MARCH) {
+        const skel_status e = run2d_march(c);
+        if (e != SKEL_OK || !c.nbb) return e;
+        ov2_border<<<dim3(c.nbb, c.fields), kBlock, 0, c.st>>>(c.x, c.out, c.rows, c.cols, c.w,
+                                                               c.ry, c.rx);
+        return launch_check("overlap2d_border");
+    }
+    if (v != O2A_DIRECT) return run2d_tile(v, c);
+    if (c.ry == 4 && c.rx == 4) return run2d_direct<4, 4>(c);
+    if (c.ry == 1 && c.rx == 1) return run2d_direct<1, 1>(c);
+    if (c.ry == 2 && c.rx == 2) return run2d_direct<2, 2>(c);
+    return run2d_direct<-1, -1>(c);
+}
+
+skel_status run2d_fields(int v, Call2 c, int64_t fields) {
+    const int64_t img = c.rows * c.cols;
     for (int64_t f0 = 0; f0 < fields; f0 += kMaxFieldsPerLaunch) {
-        const unsigned nf = (unsigned)std::min<int64_t>(fields - f0, kMaxFieldsPerLaunch);
-        const skel_status e = run2d<RY, RX>(v, x + f0 * img, out + f0 * img, rows, cols, nf, w,
-                                            sep, ry, rx, edge, pad, st);
+        c.fields = (unsigned)std::min<int64_t>(fields - f0, kMaxFieldsPerLaunch);
+        const skel_status e = run2d(v, c);
         if (e != SKEL_OK) return e;
+        c.x += kMaxFieldsPerLaunch * img;
+        c.out += kMaxFieldsPerLaunch * img;
     }
     return SKEL_OK;
 }
@@ -981,13 +1218,34 @@ skel_status launch_overlap2d(int v, const float* x, float* out, int64_t rows, in
         for (int a = 0; a < ny; ++a) wk.wy[a] = wy[a];
         for (int b = 0; b < nx; ++b) wk.wx[b] = wx[b];
     }
-    if (ry == 4 && rx == 4)
-        return run2d_fields<4, 4>(v, x, out, rows, cols, fields, wk, !w2d, ry, rx, edge, pad, lc.stream);
-    if (ry == 1 && rx == 1)
-        return run2d_fields<1, 1>(v, x, out, rows, cols, fields, wk, !w2d, ry, rx, edge, pad, lc.stream);
-    if (ry == 2 && rx == 2)
-        return run2d_fields<2, 2>(v, x, out, rows, cols, fields, wk, !w2d, ry, rx, edge, pad, lc.stream);
-    return run2d_fields<-1, -1>(v, x, out, rows, cols, fields, wk, !w2d, ry, rx, edge, pad, lc.stream);
+    const Call2 c{x, out, rows, cols, 0, wk, !w2d, ry, rx, edge, pad, 0, lc.dev->cus, lc.stream};
+    return run2d_fields(v, c, fields);
+}
+
+skel_status launch_overlap2d_transposed(const float* g, float* dx, int64_t rows, int64_t cols,
+                                        int64_t fields, const float* w2d, const float* wy,
+                                        const float* wx, int ry, int rx, int edge, LaunchCtx& lc) {
+    W2 wk{};
+    const int ny = 2 * ry + 1, nx = 2 * rx + 1;
+    for (int a = 0; a < ny; ++a)
+        for (int b = 0; b < nx; ++b)
+            wk.w[(ny - 1 - a) * nx + (nx - 1 - b)] = w2d ? w2d[a * nx + b] : wy[a] * wx[b];
+    if (!w2d) {
+        for (int a = 0; a < ny; ++a) wk.wy[a] = wy[ny - 1 - a];
+        for (int b = 0; b < nx; ++b) wk.wx[b] = wx[nx - 1 - b];
+    }
+    const int64_t n = fields * rows * cols;
+    const int r = ry > rx ? ry : rx;
+    const int v = w2d ? overlap2d_dense_variant(n, rows, cols, r)
+                      : overlap2d_separable_variant(n, rows, cols, r);
+    int nbb = 0;
+    if (edge == SKEL_EDGE_CLAMP)
+        nbb = (int)div_up(((rows > 1 ? 2 : 1) * cols +
+                           (cols > 1 ? 2 : 1) * (rows > 2 ? rows - 2 : 0)) * kBorderG, kBlock);
+    const Call2 c{g, dx, rows, cols, 0, wk, !w2d, ry, rx,
+                  edge == SKEL_EDGE_CYCLIC ? SKEL_EDGE_CYCLIC : SKEL_EDGE_CONST, 0.0f, nbb,
+                  lc.dev->cus, lc.stream};
+    return run2d_fields(v, c, fields);
 }
 
 }  // namespace skel

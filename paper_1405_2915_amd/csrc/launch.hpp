@@ -103,6 +103,11 @@ skel_status launch_overlap2d(int variant, const float* x, float* out,
                              int64_t rows, int64_t cols, int64_t fields, const float* w2d,
                              const float* wy, const float* wx, int ry, int rx,
                              int edge, float pad, LaunchCtx& lc);
+// the transpose of that map applied to g (every field on its own), by the
+// variant the plan's rule gives the flipped correlation, in one launch
+skel_status launch_overlap2d_transposed(const float* g, float* dx, int64_t rows, int64_t cols,
+                                        int64_t fields, const float* w2d, const float* wy,
+                                        const float* wx, int ry, int rx, int edge, LaunchCtx& lc);
 skel_status launch_reduce_segments(int variant, int op, const float* x, int64_t n,
                                    const int64_t* off_dev, const int64_t* off_host,
                                    int64_t nseg, float* out, LaunchCtx& lc);

@@ -318,6 +318,66 @@ def test_mapoverlap2d(skel, oracle_mod, edge, ry, rx):
 # These shapes put strips at both row ends (widths that are multiples of 256),
 # a ragged last strip (260, 772), images of 4 and 5 rows (rows wrapped or
 # clamped up to 4 away) and strips that end mid-strip in height.
+# images at the edges of the 64-column tiles of 16 rows, unaligned rows
+TILE_SHAPES = [(1, 70), (70, 1), (2, 2), (15, 63), (16, 64), (17, 65), (33, 130), (100, 333)]
+TILE_RADII = [(0, 0), (0, 3), (3, 0), (1, 2), (5, 5), (2, 6), (7, 7), (8, 1), (8, 8)]
+
+
+@pytest.mark.parametrize("edge", list(EDGES))
+@pytest.mark.parametrize("ry,rx", TILE_RADII)
+def test_mapoverlap2d_tiles_and_transpose(skel, oracle_mod, edge, ry, rx):
+    """The LDS tiles for every column radius, and the transpose whose border
+    pixels run beside the tiles: each output is at most (2ry+1)(2rx+1) fused
+    multiply-adds in turn (a row and a column pass for factors), and a border
+    pixel's coefficients are sums of weights rounded in turn: that many
+    roundings of 2^-24 of the terms' magnitude, and eight more."""
+    wy = si.uniform_f32(2 * ry + 1, -1.0, 1.0, 51, ry)
+    wx = si.uniform_f32(2 * rx + 1, -1.0, 1.0, 51, 20 + rx)
+    w2d = si.uniform_f32((2 * ry + 1) * (2 * rx + 1), -1.0, 1.0, 51, 40).reshape(2 * ry + 1, -1)
+    tol = ((2 * ry + 1) * (2 * rx + 1) + 8) * 2.0 ** -24
+    for shape in TILE_SHAPES:
+        x = si.uniform_f32(shape[0] * shape[1], -1.0, 1.0, 51, 60).reshape(shape)
+        for names, kw in ((["O2b_lds_tile"], {"w2d": w2d}),
+                          (["O2c_lds_separable", "O2d_separable_l1"], {"wy": wy, "wx": wx})):
+            ref, mag = oracle_mod.mapoverlap2d(x, ry, rx, edge=edge, pad=0.5, **kw)
+            for name in names:
+                out = skel.Container.empty(skel.F32, *shape)
+                skel.skel_mapoverlap2d(cont(skel, x), out, ry=ry, rx=rx, edge=EDGES[edge], pad=0.5,
+                                       variant=skel.variant_index(skel.SK_MAPOVERLAP2D, name), **kw)
+                got = out.to_numpy().reshape(shape).astype(np.float64)
+                bad = np.abs(got - ref) > tol * mag + 1e-30
+                assert not bad.any(), (edge, ry, rx, shape, name, np.argwhere(bad)[:3])
+            ref, mag = oracle_mod.mapoverlap2d_adjoint(x, ry, rx, edge=edge, **kw)
+            out = skel.Container.empty(skel.F32, *shape)
+            skel.skel_mapoverlap2d_backward(cont(skel, x), out, ry=ry, rx=rx, edge=EDGES[edge], **kw)
+            got = out.to_numpy().reshape(shape).astype(np.float64)
+            bad = np.abs(got - ref) > tol * mag + 1e-30
+            assert not bad.any(), (edge, ry, rx, shape, "transpose", np.argwhere(bad)[:3])
+
+
+@pytest.mark.parametrize("sep", [False, True])
+def test_mapoverlap2d_two_row_tiles(skel, oracle_mod, sep):
+    """2^23 pixels and more: two rows per lane; unaligned rows, a ragged last
+    tile.  Compared with the oracle on sampled rows."""
+    rows, cols, r = 2900, 2903, 3
+    wy, wx = si.uniform_f32(7, 0.0, 1.0, 52, 1), si.uniform_f32(7, -1.0, 1.0, 52, 2)
+    kw = {"wy": wy, "wx": wx} if sep else {"w2d": si.uniform_f32(49, -1.0, 1.0, 52, 3).reshape(7, 7)}
+    x = si.uniform_f32(rows * cols, -1.0, 1.0, 52, 4).reshape(rows, cols)
+    out, dx = skel.Container.empty(skel.F32, rows, cols), skel.Container.empty(skel.F32, rows, cols)
+    skel.skel_mapoverlap2d(cont(skel, x), out, ry=r, rx=r, edge=EDGES["clamp"], **kw)
+    skel.skel_mapoverlap2d_backward(cont(skel, x), dx, ry=r, rx=r, edge=EDGES["clamp"], **kw)
+    tol = (49 + 8) * 2.0 ** -24
+    for fn, got in ((oracle_mod.mapoverlap2d, out), (oracle_mod.mapoverlap2d_adjoint, dx)):
+        got = got.to_numpy().reshape(rows, cols).astype(np.float64)
+        for a, b in ((0, 40), (1440, 1480), (rows - 40, rows)):
+            # a band of the image with its own halo is exact away from the cut
+            lo, hi = max(0, a - 2 * r), min(rows, b + 2 * r)
+            ref, mag = fn(x[lo:hi], r, r, edge="clamp", **kw)
+            s = slice(r if lo else 0, (hi - lo) - (r if hi < rows else 0))
+            bad = np.abs(got[lo:hi][s] - ref[s]) > tol * mag[s] + 1e-30
+            assert not bad.any(), (sep, a, np.argwhere(bad)[:3])
+
+
 MARCH_SHAPES = [(4, 256), (5, 512), (37, 768), (70, 1024), (20, 260), (9, 772)]
 MARCH_RADII = [(1, 1), (2, 2), (4, 4), (3, 1), (0, 2), (4, 0)]
 
