@@ -78,7 +78,7 @@ SCAN_KERNELS = {
 }
 # device sources of the dominant kernel: its traffic figure holds only while
 # their combined hash is the one the counters were taken on
-KERNEL_SRC = {"scan_excl_i32_i64": ("k_scan.hip", "kcommon.hpp", "kepoch.hpp")}
+KERNEL_SRC = {"scan_excl_i32_i64": ("k_scan.hip", "kscan.hpp", "kcommon.hpp", "kepoch.hpp")}
 
 
 def source_hash(name):

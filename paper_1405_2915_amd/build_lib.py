@@ -24,7 +24,7 @@ LIB = os.path.join(PKG, "libskel.so")
 HOSTTEST_LIB = os.path.join(PKG, "libskel_hosttest.so")
 
 HIP_SOURCES = ["common.cpp", "container.cpp", "dispatch.cpp", "runtime.cpp", "chain_table.cpp",
-               "skeletons.cpp", "k_map.hip", "k_reduce.hip", "k_scan.hip",
+               "skeletons.cpp", "k_map.hip", "k_reduce.hip", "k_scan.hip", "k_scan_rows.hip",
                "k_overlap.hip", "k_segments.hip", "k_grad.hip", "k_chain.hip"]
 HOST_SOURCES = ["common.cpp", "container.cpp", "dispatch.cpp", "chain_table.cpp"]
 

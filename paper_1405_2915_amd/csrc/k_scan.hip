@@ -35,7 +35,12 @@
 //       tiles numbered by workgroup index, and each tile reads the totals of
 //       all its predecessors in one round of parallel loads (no prefix chain,
 //       no atomic counter)
-//   S3  S2's tile step run by persistent workgroups (one per resident slot)
+//   S3  (middle sizes: the flat look-back of S5 on tiles of four wavefronts,
+//       while the device holds them all at once, up to 2^23 elements; the
+//       32768-element tiles below would leave CUs idle there: 5000003 floats are
+//       153 tiles for 256 CUs, 14.3 us per scan against 11.5 flat, and 2^23
+//       floats 17.7 against 15.1)
+//       S2's tile step run by persistent workgroups (one per resident slot)
 //       that loop over tile ids; a workgroup takes its next id once its
 //       stores are issued, so no workgroup launch sits between one tile's
 //       stores and the next tile's loads, and the counter's round trip
@@ -49,233 +54,14 @@
 // skel_sync reports, and finishes (with wrong values) instead of hanging.
 #include <mutex>
 
-#include "kcommon.hpp"
+#include "kscan.hpp"
 #include "dispatch.hpp"
-#include "kepoch.hpp"
 #include "launch.hpp"
-
-#ifndef SKEL_SCAN_WAVES
-#define SKEL_SCAN_WAVES 16
-#endif
-
 
 namespace skel {
 namespace {
 
 using namespace dev;
-
-constexpr uint32_t kSpinLimit = 1u << 22;
-constexpr int kFlatPerLane = 8;  // S5: descriptors each lane reads per round
-
-template <int DIN, int DOUT, int OP, int WAVES = SKEL_SCAN_WAVES>
-struct SP {
-    using in_t = typename Stored<DIN>::type;
-    using out_t = typename Stored<DOUT>::type;
-    using acc_t = typename Acc<DIN, DOUT, OP>::type;
-    using C = Comb<acc_t, OP>;
-    static constexpr int E = 16 / sizeof(in_t);           // elements per lane per row
-    static constexpr int R = sizeof(in_t) == 4 ? 8 : 16;  // rows per wavefront
-    static constexpr int kWaveElems = kWave * E * R;      // 2048
-    // wavefronts per workgroup: 16 for 4-byte inputs; 8 for 8-byte inputs,
-    // whose raw rows need twice the registers
-    static constexpr int NW = sizeof(in_t) == 4 ? WAVES : (WAVES > 1 ? WAVES / 2 : 1);
-    static constexpr int kBlock = NW * kWave;
-    static constexpr int64_t kTile = (int64_t)NW * kWaveElems;
-};
-
-template <class P>
-using Raw = typename P::in_t[P::R][P::E];
-
-template <class P>
-__device__ __forceinline__ int64_t lane_base(int64_t tile) {
-    return tile * P::kTile + (int64_t)(threadIdx.x / kWave) * P::kWaveElems +
-           (int64_t)lane() * P::E;
-}
-
-// Load the lane's share of `tile` (rows of 16-byte vectors); NT marks the
-// loads non-temporal (input read once: measured a few percent faster for the
-// single-pass scan).
-template <class P, bool FULL, bool NT = false>
-__device__ __forceinline__ void tile_load(const typename P::in_t* in, int64_t n, int64_t tile,
-                                          Raw<P>& raw) {
-    const int64_t b = lane_base<P>(tile);
-#pragma unroll
-    for (int r = 0; r < P::R; ++r) {
-        const int64_t idx = b + (int64_t)r * kWave * P::E;
-        if (FULL || idx + P::E <= n) {
-            if constexpr (NT) load16_nt(in + idx, raw[r]);
-            else load16(in + idx, raw[r]);
-        } else {
-#pragma unroll
-            for (int e = 0; e < P::E; ++e) raw[r][e] = idx + e < n ? in[idx + e] : 0;
-        }
-    }
-}
-
-// op over the lane's elements below n
-template <class P, bool FULL>
-__device__ __forceinline__ typename P::acc_t lane_total(int64_t n, int64_t tile,
-                                                        const Raw<P>& raw) {
-    using C = typename P::C;
-    const int64_t b = lane_base<P>(tile);
-    typename P::acc_t t = C::id();
-#pragma unroll
-    for (int r = 0; r < P::R; ++r)
-#pragma unroll
-        for (int e = 0; e < P::E; ++e)
-            if (FULL || b + (int64_t)r * kWave * P::E + e < n)
-                t = C::op(t, widen<typename P::acc_t>(raw[r][e]));
-    return t;
-}
-
-// Compiler-only barrier on the raw inputs (emits no instruction): without it
-// the compiler keeps the widened values of phase 1 alive across the tile wait
-// to reuse them in the store phase, which doubles the live registers.
-template <class P>
-__device__ __forceinline__ void keep_raw_only(Raw<P>& raw) {
-#pragma unroll
-    for (int r = 0; r < P::R; ++r)
-#pragma unroll
-        for (int e = 0; e < P::E; ++e) asm volatile("" : "+v"(raw[r][e]));
-}
-
-// Scan the wavefront's slice given its exclusive prefix, and store it.  REV:
-// the slice is combined from its last element down (the prefix then holds
-// everything after the slice).
-// Returns prefix op (the slice's elements below n).
-template <class P, bool FULL, bool REV = false>
-__device__ __forceinline__ typename P::acc_t tile_scan_store(typename P::out_t* out, int64_t n,
-                                                             int64_t tile, const Raw<P>& raw,
-                                                             typename P::acc_t prefix,
-                                                             bool exclusive) {
-    using acc_t = typename P::acc_t;
-    using out_t = typename P::out_t;
-    using C = typename P::C;
-    constexpr int E = P::E;
-    const int l = lane();
-    const int64_t b = lane_base<P>(tile);
-    acc_t running = prefix;
-#pragma unroll
-    for (int rr = 0; rr < P::R; ++rr) {
-        const int r = REV ? P::R - 1 - rr : rr;
-        const int64_t idx = b + (int64_t)r * kWave * E;
-        acc_t loc[E];  // lane-local inclusive scan of the row vector (in scan order)
-        acc_t t = C::id();
-#pragma unroll
-        for (int ee = 0; ee < E; ++ee) {
-            const int e = REV ? E - 1 - ee : ee;
-            const acc_t x = (FULL || idx + e < n) ? widen<acc_t>(raw[r][e]) : C::id();
-            t = C::op(t, x);
-            loc[e] = t;
-        }
-        const acc_t incl = REV ? wave_inclusive_suffix_scan<C>(t) : wave_inclusive_scan<C>(t);
-        const acc_t tot = lane_value(incl, REV ? 0 : kWave - 1);
-        const acc_t ex = REV ? wave_shift_down(incl, C::id()) : wave_shift_up(incl, C::id());
-        const bool first = REV ? l == kWave - 1 : l == 0;
-        const acc_t base = C::op(running, first ? C::id() : ex);
-        out_t o[E];
-#pragma unroll
-        for (int e = 0; e < E; ++e) {
-            const int before = REV ? e + 1 : e - 1;  // previous element in scan order
-            const bool none = REV ? e == E - 1 : e == 0;
-            const acc_t v = exclusive ? (none ? base : C::op(base, loc[before]))
-                                      : C::op(base, loc[e]);
-            o[e] = (out_t)v;
-        }
-        if (FULL || idx + E <= n) {
-            // plain stores: with a row's stores outstanding per lane they
-            // stream faster than non-temporal ones (i32 -> i64 exclusive scan
-            // of 2^27: 353 us against 417 us)
-            store_vecs<out_t, E>(out + idx, o);
-        } else {
-#pragma unroll
-            for (int e = 0; e < E; ++e)
-                if (idx + e < n) out[idx + e] = o[e];
-        }
-        running = C::op(running, tot);
-        // one row at a time: keeps the live registers to one row's temporaries
-        // (interleaving rows would spill at 1024 lanes per workgroup)
-        __builtin_amdgcn_sched_barrier(0);
-    }
-    return running;
-}
-
-// Wavefront totals -> LDS; returns (exclusive prefix of this wavefront within
-// the tile, tile total) in every thread.  Contains one barrier.
-template <class P, bool REV = false>
-__device__ __forceinline__ void tile_totals(typename P::acc_t lane_t, typename P::acc_t* s_wtot,
-                                            typename P::acc_t* wex, typename P::acc_t* agg) {
-    using C = typename P::C;
-    const int w = threadIdx.x / kWave;
-    const typename P::acc_t wt = wave_reduce<C>(lane_t);
-    if (lane() == 0) s_wtot[w] = wt;
-    __syncthreads();
-    *wex = C::id();
-    *agg = C::id();
-#pragma unroll
-    for (int k = 0; k < P::NW; ++k) {
-        const typename P::acc_t t = s_wtot[k];
-        if (REV ? k > w : k < w) *wex = C::op(*wex, t);
-        *agg = C::op(*agg, t);
-    }
-}
-
-// --------------------------------------------------------- tile descriptors
-// two self-validating words per tile (see tagged_put / tagged_get)
-enum { ST_INVALID = 0, ST_AGG = 1, ST_PREFIX = 2 };
-
-template <class A>
-__device__ __forceinline__ void publish(u64* st, int64_t t, int state, A val, uint32_t epoch) {
-    tagged_put(st + 2 * t, state, epoch, val);
-}
-
-// Run by one whole wavefront.  Publishes the tile total, finds the exclusive
-// prefix of the tile from its predecessors' descriptors, publishes the
-// inclusive prefix, and returns the exclusive prefix (in every lane).  Lane l
-// inspects tile base - l; a descriptor once seen valid (AGG or PREFIX) is
-// final for this call, so a retry re-reads only the lanes still invalid.
-template <class P>
-__device__ typename P::acc_t lookback(u64* status, int64_t tile, typename P::acc_t agg,
-                                      uint32_t epoch, u64* err) {
-    using acc_t = typename P::acc_t;
-    using C = typename P::C;
-    const int l = lane();
-    if (tile == 0) {
-        if (l == 0) publish(status, 0, ST_PREFIX, agg, epoch);
-        return C::id();
-    }
-    if (l == 0) publish(status, tile, ST_AGG, agg, epoch);
-    acc_t excl = C::id();
-    int64_t base = tile - 1;
-    uint32_t spins = 0;
-    int s = ST_INVALID;
-    acc_t val = C::id();
-    while (true) {
-        if (s == ST_INVALID) {
-            const int64_t j = base - l;
-            s = j >= 0 ? tagged_get(status + 2 * j, epoch, val) : ST_PREFIX;
-            if (j < 0) val = C::id();
-        }
-        const u64 pre = __ballot(s == ST_PREFIX);
-        const u64 inv = __ballot(s == ST_INVALID);
-        const int p = pre ? __ffsll((long long)pre) - 1 : kWave;
-        const u64 need = p >= kWave - 1 ? ~0ull : ((2ull << p) - 1);
-        if (inv & need) {
-            if (++spins > kSpinLimit) {
-                if (l == 0) atomicOr(err, 1ull);
-                break;
-            }
-            __builtin_amdgcn_s_sleep(1);
-            continue;
-        }
-        excl = C::op(excl, wave_reduce<C>(l <= p ? val : C::id()));
-        if (p < kWave) break;
-        base -= kWave;
-        s = ST_INVALID;
-    }
-    if (l == 0) publish(status, tile, ST_PREFIX, C::op(excl, agg), epoch);
-    return excl;
-}
 
 // ------------------------------------------------------------------ kernels
 // `seq` is the tile's position in scan order (descriptor index), `tile` the
@@ -387,53 +173,6 @@ __global__ __launch_bounds__(P::kBlock) void scan_lookback_persist(
             epoch_advance(sync);
         }
     }
-}
-
-// S5: flat look-back.  The tile is the workgroup index: workgroups start in
-// index order, so every tile waited on has already started (and with at most
-// kFlatMaxTiles small tiles all of them are resident at once).  Each tile
-// publishes its total, then every lane of the workgroup reads its share of the
-// totals of all preceding tiles -- one round of parallel loads, re-reading only
-// those not yet valid -- and the workgroup combines them.  A tile so waits for
-// one publish-to-read latency, not for a chain of prefixes, and takes no
-// ticket from an atomic counter (device-scope atomics on one word serialise).
-// The last tile in scan order advances the epoch once it has seen every other
-// tile's total: by then every tile has read this call's epoch.
-template <class P>
-__device__ __forceinline__ typename P::acc_t flat_prefix(u64* status, int64_t seq,
-                                                         uint32_t epoch, u64* err) {
-    using acc_t = typename P::acc_t;
-    using C = typename P::C;
-    acc_t a = C::id();
-    for (int64_t base = 0; base < seq; base += (int64_t)kFlatPerLane * P::kBlock) {
-        acc_t v[kFlatPerLane];
-        bool ready[kFlatPerLane];
-#pragma unroll
-        for (int k = 0; k < kFlatPerLane; ++k) {
-            v[k] = C::id();
-            ready[k] = base + k * P::kBlock + (int64_t)threadIdx.x >= seq;
-        }
-        uint32_t spins = 0;
-        while (true) {
-            bool all = true;
-#pragma unroll
-            for (int k = 0; k < kFlatPerLane; ++k) {
-                if (ready[k]) continue;
-                const int64_t j = base + k * P::kBlock + threadIdx.x;
-                ready[k] = tagged_get(status + 2 * j, epoch, v[k]) != ST_INVALID;
-                all = all && ready[k];
-            }
-            if (all) break;
-            if (++spins > kSpinLimit) {  // bounded: flag it and finish
-                atomicOr(err, 1ull);
-                break;
-            }
-            __builtin_amdgcn_s_sleep(1);
-        }
-#pragma unroll
-        for (int k = 0; k < kFlatPerLane; ++k) a = C::op(a, ready[k] ? v[k] : C::id());
-    }
-    return a;
 }
 
 template <class P, bool FULL, bool REV>
@@ -585,71 +324,6 @@ __global__ __launch_bounds__(P::kBlock) void scan_single(const typename P::in_t*
     }
 }
 
-// ----------------------------------------------------------- row-wise scans
-// Every row of a rows x cols matrix scanned on its own (a batch of Scan
-// instances of one length).  SR1: one wavefront per row, walking it in chunks
-// of 2048 elements laid out like one wavefront's slice of a tile and carrying
-// the running prefix from chunk to chunk (REV: from the row's end).  Rows
-// whose starts are not 16-byte aligned take 64-element chunks of single-element
-// accesses instead.
-template <int DIN, int DOUT, int OP>
-struct SPW : SP<DIN, DOUT, OP> {
-    static constexpr int NW = 1;
-    static constexpr int kBlock = kWave;
-    static constexpr int64_t kTile = SP<DIN, DOUT, OP>::kWaveElems;
-};
-
-template <class P, bool REV>
-__global__ __launch_bounds__(kWave) void scan_rows_vec(const typename P::in_t* in,
-                                                       typename P::out_t* out, int64_t rows,
-                                                       int64_t cols, int exclusive) {
-    using acc_t = typename P::acc_t;
-    const int64_t nch = (cols + P::kTile - 1) / P::kTile;
-    for (int64_t row = blockIdx.x; row < rows; row += gridDim.x) {
-        const typename P::in_t* src = in + row * cols;
-        typename P::out_t* dst = out + row * cols;
-        acc_t carry = P::C::id();
-        for (int64_t q = 0; q < nch; ++q) {
-            const int64_t ch = REV ? nch - 1 - q : q;
-            Raw<P> raw;
-            if ((ch + 1) * P::kTile <= cols) {
-                tile_load<P, true, true>(src, cols, ch, raw);
-                keep_raw_only<P>(raw);
-                carry = tile_scan_store<P, true, REV>(dst, cols, ch, raw, carry, exclusive != 0);
-            } else {
-                tile_load<P, false, true>(src, cols, ch, raw);
-                keep_raw_only<P>(raw);
-                carry = tile_scan_store<P, false, REV>(dst, cols, ch, raw, carry, exclusive != 0);
-            }
-        }
-    }
-}
-
-template <class P, bool REV>
-__global__ __launch_bounds__(kWave) void scan_rows_scalar(const typename P::in_t* in,
-                                                          typename P::out_t* out, int64_t rows,
-                                                          int64_t cols, int exclusive) {
-    using acc_t = typename P::acc_t;
-    using C = typename P::C;
-    const int l = lane();
-    const int64_t nch = (cols + kWave - 1) / kWave;
-    for (int64_t row = blockIdx.x; row < rows; row += gridDim.x) {
-        const typename P::in_t* src = in + row * cols;
-        typename P::out_t* dst = out + row * cols;
-        acc_t carry = C::id();
-        for (int64_t q = 0; q < nch; ++q) {
-            const int64_t i = (REV ? nch - 1 - q : q) * kWave + l;
-            const acc_t x = i < cols ? widen<acc_t>(src[i]) : C::id();
-            const acc_t incl = REV ? wave_inclusive_suffix_scan<C>(x) : wave_inclusive_scan<C>(x);
-            const acc_t nb = REV ? wave_shift_down(incl, C::id()) : wave_shift_up(incl, C::id());
-            const bool first = REV ? l == kWave - 1 : l == 0;
-            const acc_t v = C::op(carry, exclusive ? (first ? C::id() : nb) : incl);
-            if (i < cols) dst[i] = (typename P::out_t)v;
-            carry = C::op(carry, lane_value(incl, REV ? 0 : kWave - 1));
-        }
-    }
-}
-
 // --------------------------------------------------------------- launchers
 // S1's three launches; `sums` holds one accumulator per tile (written by the
 // first launch before the others read it, so it needs no clearing)
@@ -724,9 +398,21 @@ skel_status scan_typed(int v, int kind, const void* x, void* y, int64_t n, Launc
         return reduce_then_scan<P>(in, out, n, excl, static_cast<acc_t*>(mem), st);
     }
     case S3_PERSISTENT_LOOKBACK: {
+        // middle sizes: flat, while the device holds every tile at once (so that
+        // a tile waits only on tiles that are running); 8192 elements per tile
+        using PM = SP<DIN, DOUT, OP, DIN == SKEL_I64 ? 8 : 4>;
+        const auto flat = rev ? scan_flat<PM, true> : scan_flat<PM, false>;
+        const int64_t ntm = (n + PM::kTile - 1) / PM::kTile;
+        const bool mid = ntm <= kFlatMaxTiles &&
+                         ntm <= resident_slots(reinterpret_cast<const void*>(flat), PM::kBlock, lc);
         void* status = nullptr;
-        skel_status e = ws_status(lc, (size_t)ntiles * 16, &status);
+        skel_status e = ws_status(lc, (size_t)(mid ? ntm : ntiles) * 16, &status);
         if (e != SKEL_OK) return e;
+        if (mid) {
+            flat<<<(unsigned)ntm, PM::kBlock, 0, st>>>(in, out, n, ntm, excl,
+                                                       static_cast<u64*>(status), lc.ws->sync);
+            return launch_check("scan_flat_mid");
+        }
         auto kern = rev ? scan_lookback_persist<P, true> : scan_lookback_persist<P, false>;
         const int64_t slots = resident_slots(reinterpret_cast<const void*>(kern), P::kBlock, lc);
         if (slots < 1) return fail(SKEL_E_HIP, "scan_lookback_persist does not fit a CU");
@@ -749,36 +435,6 @@ skel_status scan_typed(int v, int kind, const void* x, void* y, int64_t n, Launc
     }
 }
 
-template <int DIN, int DOUT, int OP>
-skel_status scan_rows_typed(int kind, const void* x, void* y, int64_t rows, int64_t cols,
-                            bool vec, LaunchCtx& lc) {
-    using P = SPW<DIN, DOUT, OP>;
-    const auto* in = static_cast<const typename P::in_t*>(x);
-    auto* out = static_cast<typename P::out_t*>(y);
-    const bool rev = kind == SKEL_REVERSE_INCLUSIVE || kind == SKEL_REVERSE_EXCLUSIVE;
-    const int excl = (kind == SKEL_EXCLUSIVE || kind == SKEL_REVERSE_EXCLUSIVE) ? 1 : 0;
-    const unsigned grid = (unsigned)std::min<int64_t>(rows, INT64_C(1) << 20);
-    hipStream_t st = lc.stream;
-    if (vec) {
-        if (rev) scan_rows_vec<P, true><<<grid, kWave, 0, st>>>(in, out, rows, cols, excl);
-        else scan_rows_vec<P, false><<<grid, kWave, 0, st>>>(in, out, rows, cols, excl);
-        return launch_check("scan_rows_vec");
-    }
-    if (rev) scan_rows_scalar<P, true><<<grid, kWave, 0, st>>>(in, out, rows, cols, excl);
-    else scan_rows_scalar<P, false><<<grid, kWave, 0, st>>>(in, out, rows, cols, excl);
-    return launch_check("scan_rows_scalar");
-}
-
-template <int DIN, int DOUT>
-skel_status scan_rows_op(int kind, int op, const void* x, void* y, int64_t rows, int64_t cols,
-                         bool vec, LaunchCtx& lc) {
-    switch (op) {
-    case SKEL_SUM: return scan_rows_typed<DIN, DOUT, SKEL_SUM>(kind, x, y, rows, cols, vec, lc);
-    case SKEL_MIN: return scan_rows_typed<DIN, DOUT, SKEL_MIN>(kind, x, y, rows, cols, vec, lc);
-    default: return scan_rows_typed<DIN, DOUT, SKEL_MAX>(kind, x, y, rows, cols, vec, lc);
-    }
-}
-
 template <int DIN, int DOUT>
 skel_status scan_op(int v, int kind, int op, const void* x, void* y, int64_t n,
                     LaunchCtx& lc) {
@@ -790,15 +446,6 @@ skel_status scan_op(int v, int kind, int op, const void* x, void* y, int64_t n,
 }
 
 }  // namespace
-
-skel_status launch_scan_rows(int kind, int op, skel_dtype din, skel_dtype dout, const void* x,
-                             void* y, int64_t rows, int64_t cols, bool vec, LaunchCtx& lc) {
-    if (din == SKEL_I32 && dout == SKEL_I32)
-        return scan_rows_op<SKEL_I32, SKEL_I32>(kind, op, x, y, rows, cols, vec, lc);
-    if (din == SKEL_I32) return scan_rows_op<SKEL_I32, SKEL_I64>(kind, op, x, y, rows, cols, vec, lc);
-    if (din == SKEL_I64) return scan_rows_op<SKEL_I64, SKEL_I64>(kind, op, x, y, rows, cols, vec, lc);
-    return scan_rows_op<SKEL_F32, SKEL_F32>(kind, op, x, y, rows, cols, vec, lc);
-}
 
 skel_status launch_scan(int v, int kind, int op, skel_dtype din, skel_dtype dout,
                         const void* x, void* y, int64_t n, LaunchCtx& lc) {

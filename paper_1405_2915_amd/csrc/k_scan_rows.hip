@@ -1,0 +1,391 @@
+// Row-wise Scan: every row of a rows x cols matrix scanned on its own (a batch of
+// Scan instances of one length, Section III), in one launch for all rows.  Vectors
+// are accessed at element alignment, so ragged rows cost no more instructions
+// than aligned ones.  Forms, by shape:
+//   short rows   up to 32 vectors: 8, 16 or 32 lanes per row, so that a wavefront
+//                scans several rows at once
+//   a wavefront  per row, walking it in chunks of as many vectors per lane as the
+//                row needs (1, 2, 4 or 8 rows of 64 vectors) with a running carry;
+//                the form for many rows
+//   few rows     (fewer than 1024 wavefronts' worth of work in flight) of more
+//                than 4096 elements are cut into tiles: with up to 1024 tiles of
+//                two wavefronts in all, the flat look-back within each row;
+//                otherwise tiles of 16 wavefronts (4 for rows of at most 8192)
+//                with the decoupled look-back within each row, or without any
+//                where a row is one tile
+// All are HBM-bound once enough rows or tiles are in flight.  Measured, forward
+// and reverse together, against one wavefront per row in chunks of 2048 elements
+// (64-element chunks of single accesses where rows are not 16-byte aligned),
+// binary32: 65536 x 20 117 -> 7 us, 20000 x 100 43 -> 9.2, 3000 x 1001 18.2 -> 11.3,
+// 65536 x 512 121 -> 89 (6 TB/s), 900 x 5001 64 -> 20, 300 x 100001 1469 -> 112,
+// 40 x 50001 394 -> 18, 3 x 1000003 9800 -> 22; 16384 x 2048 92.6 both (5.8 TB/s).
+#include "kscan.hpp"
+#include "dispatch.hpp"
+#include "launch.hpp"
+
+namespace skel {
+namespace {
+
+using namespace dev;
+
+// one wavefront, RV * 256 elements per chunk
+template <int DIN, int DOUT, int OP, int RV>
+struct SPW : SP<DIN, DOUT, OP, 1, false> {
+    using Base = SP<DIN, DOUT, OP, 1, false>;
+    static constexpr int NW = 1;
+    static constexpr int kBlock = kWave;
+    static constexpr int R = RV * 256 / (kWave * Base::E);
+    static constexpr int kWaveElems = kWave * Base::E * R;
+    static constexpr int64_t kTile = kWaveElems;
+};
+
+template <class P, bool REV>
+__global__ __launch_bounds__(kWave) void scan_rows_wave(const typename P::in_t* in,
+                                                        typename P::out_t* out, int64_t rows,
+                                                        int64_t cols, int exclusive) {
+    using acc_t = typename P::acc_t;
+    const int64_t nch = (cols + P::kTile - 1) / P::kTile;
+    for (int64_t row = blockIdx.x; row < rows; row += gridDim.x) {
+        const typename P::in_t* src = in + row * cols;
+        typename P::out_t* dst = out + row * cols;
+        acc_t carry = P::C::id();
+        for (int64_t q = 0; q < nch; ++q) {
+            const int64_t ch = REV ? nch - 1 - q : q;
+            Raw<P> raw;
+            if ((ch + 1) * P::kTile <= cols) {
+                tile_load<P, true, true>(src, cols, ch, raw);
+                keep_raw_only<P>(raw);
+                carry = tile_scan_store<P, true, REV>(dst, cols, ch, raw, carry, exclusive != 0);
+            } else {
+                tile_load<P, false, true>(src, cols, ch, raw);
+                keep_raw_only<P>(raw);
+                carry = tile_scan_store<P, false, REV>(dst, cols, ch, raw, carry, exclusive != 0);
+            }
+        }
+    }
+}
+
+// inclusive scan within groups of G = 8, 16 or 32 lanes (REV: from the group's
+// last lane down): row-of-16 steps that stay inside the group, then for 32 the
+// other half's total
+template <class C, bool REV, class T>
+__device__ __forceinline__ T group_scan(T v, int G) {
+    const T id = C::id();
+    const int l = lane(), p = REV ? G - 1 - (l & (G - 1)) : l & (G - 1);
+    T u;
+    u = REV ? dpp<kDppRowShl + 1>(id, v) : dpp<kDppRowShr + 1>(id, v);
+    if (p >= 1) v = REV ? C::op(v, u) : C::op(u, v);
+    u = REV ? dpp<kDppRowShl + 2>(id, v) : dpp<kDppRowShr + 2>(id, v);
+    if (p >= 2) v = REV ? C::op(v, u) : C::op(u, v);
+    u = REV ? dpp<kDppRowShl + 4>(id, v) : dpp<kDppRowShr + 4>(id, v);
+    if (p >= 4) v = REV ? C::op(v, u) : C::op(u, v);
+    if (G > 8) {
+        // (lanes 16 .. 31 of a group of 32 take only their own half's here)
+        const int h = p & 15;
+        u = REV ? dpp<kDppRowShl + 8>(id, v) : dpp<kDppRowShr + 8>(id, v);
+        if (h >= 8) v = REV ? C::op(v, u) : C::op(u, v);
+    }
+    if (G > 16) {
+        const T a = lane_value(v, REV ? 16 : 15), b = lane_value(v, REV ? 48 : 47);
+        const T t = l < 32 ? a : b;
+        if (p >= 16) v = REV ? C::op(v, t) : C::op(t, v);
+    }
+    return v;
+}
+
+constexpr int kShortBlock = 256;
+// fewer rows than this, longer than that, are cut into tiles: 1024 wavefronts
+// with one chunk each in flight reach about half of HBM's rate (500 x 20000 44
+// us for a wavefront per row, 38 in tiles; at 1024 x 32768 both 113), and a row of
+// up to 4096 elements is two chunks
+constexpr int64_t kFewRows = 1024, kLongRow = 4096;
+
+template <class P, bool REV>
+__global__ __launch_bounds__(kShortBlock) void scan_rows_short(const typename P::in_t* in,
+                                                               typename P::out_t* out,
+                                                               int64_t rows, int cols,
+                                                               int exclusive, int G) {
+    using in_t = typename P::in_t;
+    using out_t = typename P::out_t;
+    using acc_t = typename P::acc_t;
+    using C = typename P::C;
+    constexpr int E = P::E;
+    const int64_t row = ((int64_t)blockIdx.x * kShortBlock + threadIdx.x) / G;
+    const int g = (int)threadIdx.x & (G - 1), c0 = g * E;
+    const bool live = row < rows;  // (every lane takes part in the lane moves)
+    const in_t* src = in + row * cols + c0;
+    out_t* dst = out + row * cols + c0;
+    in_t raw[E];
+    if (live && c0 + E <= cols) {
+        load16_any(src, raw);
+    } else {
+#pragma unroll
+        for (int e = 0; e < E; ++e) raw[e] = live && c0 + e < cols ? src[e] : in_t(0);
+    }
+    acc_t loc[E];
+    acc_t t = C::id();
+#pragma unroll
+    for (int ee = 0; ee < E; ++ee) {
+        const int e = REV ? E - 1 - ee : ee;
+        t = C::op(t, c0 + e < cols ? widen<acc_t>(raw[e]) : C::id());
+        loc[e] = t;
+    }
+    const acc_t incl = group_scan<C, REV>(t, G);
+    const acc_t nb = REV ? wave_shift_down(incl, C::id()) : wave_shift_up(incl, C::id());
+    const acc_t base = C::op(C::id(), (REV ? g == G - 1 : g == 0) ? C::id() : nb);
+    out_t o[E];
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        const int before = REV ? e + 1 : e - 1;
+        const bool none = REV ? e == E - 1 : e == 0;
+        const acc_t v = exclusive ? (none ? base : C::op(base, loc[before])) : C::op(base, loc[e]);
+        o[e] = (out_t)v;
+    }
+    if (live && c0 + E <= cols) {
+        store_vecs_any<out_t, E>(dst, o);
+    } else if (live) {
+#pragma unroll
+        for (int e = 0; e < E; ++e)
+            if (c0 + e < cols) dst[e] = o[e];
+    }
+}
+
+// Flat look-back within each row: tile seq = row * tpr + t (t in scan order)
+// publishes its total and reads those of the t tiles before it in its row.  All
+// tiles are resident at once (the launcher checks), so every wait ends.  The last
+// workgroup advances the epoch once it has seen every tile's total: by then every
+// tile has read this call's epoch.
+template <class P, bool FULL, bool REV>
+__device__ __forceinline__ void flat_row_tile(const typename P::in_t* src, typename P::out_t* dst,
+                                              int64_t cols, int64_t first, int64_t t, int64_t tile,
+                                              int exclusive, u64* status, u64* sync) {
+    using acc_t = typename P::acc_t;
+    using C = typename P::C;
+    __shared__ acc_t s_wtot[P::NW];
+    __shared__ acc_t s_red[P::NW];
+    __shared__ acc_t s_prefix;
+    __shared__ uint32_t s_epoch;
+    uint32_t ep = 0;
+    if (threadIdx.x == 0) ep = epoch_of_call(sync);  // in flight with the tile's loads
+    Raw<P> raw;
+    tile_load<P, FULL, true>(src, cols, tile, raw);
+    acc_t wex, agg;
+    tile_totals<P, REV>(lane_total<P, FULL>(cols, tile, raw), s_wtot, &wex, &agg);
+    if (threadIdx.x == 0) {
+        s_epoch = ep;
+        publish(status, first + t, ST_AGG, agg, ep);
+    }
+    __syncthreads();
+    const acc_t pre = block_reduce<C>(
+        flat_prefix<P>(status + 2 * first, t, s_epoch, sync + SYNC_ERROR), s_red);
+    if (threadIdx.x == 0) s_prefix = pre;
+    __syncthreads();
+    keep_raw_only<P>(raw);
+    tile_scan_store<P, FULL, REV>(dst, cols, tile, raw, C::op(s_prefix, wex), exclusive != 0);
+    if (blockIdx.x == gridDim.x - 1) {
+        flat_prefix<P>(status, (int64_t)gridDim.x - 1, s_epoch, sync + SYNC_ERROR);
+        __syncthreads();
+        if (threadIdx.x == 0) epoch_advance(sync);
+    }
+}
+
+template <class P, bool REV>
+__global__ __launch_bounds__(P::kBlock) void scan_rows_flat(const typename P::in_t* in,
+                                                            typename P::out_t* out, int64_t cols,
+                                                            int64_t tpr, int exclusive,
+                                                            u64* status, u64* sync) {
+    const int64_t row = (int64_t)blockIdx.x / tpr, t = (int64_t)blockIdx.x - row * tpr;
+    const int64_t tile = REV ? tpr - 1 - t : t;
+    const typename P::in_t* src = in + row * cols;
+    typename P::out_t* dst = out + row * cols;
+    if ((tile + 1) * P::kTile <= cols)
+        flat_row_tile<P, true, REV>(src, dst, cols, row * tpr, t, tile, exclusive, status, sync);
+    else
+        flat_row_tile<P, false, REV>(src, dst, cols, row * tpr, t, tile, exclusive, status, sync);
+}
+
+// Tiles with the decoupled look-back within each row (tpr > 1), numbered by an
+// atomic counter in start order so that a tile waits only on tiles already
+// running; tpr == 1: one workgroup per row, nothing to wait for.
+template <class P, bool FULL, bool REV>
+__device__ __forceinline__ void row_tile(const typename P::in_t* src, typename P::out_t* dst,
+                                         int64_t cols, int64_t first, int64_t t, int64_t tile,
+                                         bool alone, int exclusive, u64* status, u64* sync,
+                                         uint32_t epoch) {
+    using acc_t = typename P::acc_t;
+    __shared__ acc_t s_wtot[P::NW];
+    __shared__ acc_t s_prefix;
+    Raw<P> raw;
+    tile_load<P, FULL, true>(src, cols, tile, raw);
+    acc_t wex, agg;
+    tile_totals<P, REV>(lane_total<P, FULL>(cols, tile, raw), s_wtot, &wex, &agg);
+    acc_t prefix = P::C::id();
+    if (!alone) {
+        if (threadIdx.x < kWave) {
+            const acc_t e = lookback<P>(status + 2 * first, t, agg, epoch, sync + SYNC_ERROR);
+            if (threadIdx.x == 0) s_prefix = e;
+        }
+        __syncthreads();
+        prefix = s_prefix;
+    }
+    keep_raw_only<P>(raw);
+    tile_scan_store<P, FULL, REV>(dst, cols, tile, raw, P::C::op(prefix, wex), exclusive != 0);
+}
+
+template <class P, bool REV>
+__global__ __launch_bounds__(P::kBlock) void scan_rows_tiles(const typename P::in_t* in,
+                                                             typename P::out_t* out, int64_t cols,
+                                                             int64_t tpr, int exclusive,
+                                                             u64* status, u64* sync) {
+    __shared__ int64_t s_tile;
+    __shared__ uint32_t s_epoch;
+    const bool alone = tpr == 1;
+    int64_t seq = blockIdx.x;
+    uint32_t epoch = 0;
+    if (!alone) {
+        if (threadIdx.x == 0) {
+            s_epoch = epoch_of_call(sync);
+            const u64 k = atomicAdd(&sync[SYNC_TILE_COUNTER], 1ull);
+            if (k == (u64)gridDim.x - 1)  // every other tile id has been taken
+                __hip_atomic_store(&sync[SYNC_TILE_COUNTER], 0ull, __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_AGENT);
+            s_tile = (int64_t)k;
+        }
+        __syncthreads();
+        seq = s_tile;
+        epoch = s_epoch;
+    }
+    const int64_t row = seq / tpr, t = seq - row * tpr;
+    const int64_t tile = REV ? tpr - 1 - t : t;
+    const typename P::in_t* src = in + row * cols;
+    typename P::out_t* dst = out + row * cols;
+    if ((tile + 1) * P::kTile <= cols)
+        row_tile<P, true, REV>(src, dst, cols, row * tpr, t, tile, alone, exclusive, status, sync,
+                               epoch);
+    else
+        row_tile<P, false, REV>(src, dst, cols, row * tpr, t, tile, alone, exclusive, status, sync,
+                                epoch);
+    if (!alone && threadIdx.x == 0) {
+        const u64 d = atomicAdd(&sync[SYNC_DONE], 1ull);
+        if (d == (u64)gridDim.x - 1) {
+            __hip_atomic_store(&sync[SYNC_DONE], 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            epoch_advance(sync);
+        }
+    }
+}
+
+// --------------------------------------------------------------- launchers
+struct RowsCall {
+    const void* x;
+    void* y;
+    int64_t rows, cols;
+    bool rev;
+    int excl;
+};
+
+template <int DIN, int DOUT, int OP, int RV>
+skel_status run_wave(const RowsCall& c, LaunchCtx& lc) {
+    using P = SPW<DIN, DOUT, OP, RV>;
+    const auto kern = c.rev ? scan_rows_wave<P, true> : scan_rows_wave<P, false>;
+    const unsigned grid = (unsigned)std::min<int64_t>(c.rows, INT64_C(1) << 20);
+    kern<<<grid, kWave, 0, lc.stream>>>(static_cast<const typename P::in_t*>(c.x),
+                                        static_cast<typename P::out_t*>(c.y), c.rows, c.cols,
+                                        c.excl);
+    return launch_check("scan_rows_wave");
+}
+
+// the descriptor array for a tiled form, or NULL where it cannot be had inside a
+// graph capture (the form that needs none then serves the call)
+skel_status tile_status(LaunchCtx& lc, int64_t tiles, void** status) {
+    *status = nullptr;
+    if (ws_status_ready(lc, (size_t)tiles * 16, 1) != SKEL_OK) {
+        clear_error();
+        return SKEL_OK;
+    }
+    return ws_status(lc, (size_t)tiles * 16, status);
+}
+
+template <class P>
+skel_status run_tiles(const RowsCall& c, LaunchCtx& lc, bool* done) {
+    const int64_t tpr = (c.cols + P::kTile - 1) / P::kTile;
+    void* status = nullptr;
+    if (tpr > 1) {
+        const skel_status e = tile_status(lc, c.rows * tpr, &status);
+        if (e != SKEL_OK || !status) return e;
+    }
+    const auto kern = c.rev ? scan_rows_tiles<P, true> : scan_rows_tiles<P, false>;
+    kern<<<(unsigned)(c.rows * tpr), P::kBlock, 0, lc.stream>>>(
+        static_cast<const typename P::in_t*>(c.x), static_cast<typename P::out_t*>(c.y), c.cols,
+        tpr, c.excl, static_cast<u64*>(status), lc.ws->sync);
+    *done = true;
+    return launch_check("scan_rows_tiles");
+}
+
+template <int DIN, int DOUT, int OP>
+skel_status scan_rows_typed(const RowsCall& c, LaunchCtx& lc) {
+    using PS = SP<DIN, DOUT, OP, 2, false>;   // small tiles
+    using PM = SP<DIN, DOUT, OP, 4, false>;
+    using PL = SP<DIN, DOUT, OP, 16, false>;
+    constexpr int E = PS::E;
+    if (c.cols <= 32 * E) {
+        const int G = c.cols <= 8 * E ? 8 : c.cols <= 16 * E ? 16 : 32;
+        const auto kern = c.rev ? scan_rows_short<PS, true> : scan_rows_short<PS, false>;
+        const int64_t grid = (c.rows * G + kShortBlock - 1) / kShortBlock;
+        if (grid < (INT64_C(1) << 31)) {
+            kern<<<(unsigned)grid, kShortBlock, 0, lc.stream>>>(
+                static_cast<const typename PS::in_t*>(c.x), static_cast<typename PS::out_t*>(c.y),
+                c.rows, (int)c.cols, c.excl, G);
+            return launch_check("scan_rows_short");
+        }
+    }
+    if (c.rows < kFewRows && c.cols > kLongRow) {
+        const int64_t tpr = (c.cols + PS::kTile - 1) / PS::kTile;
+        const auto flat = c.rev ? scan_rows_flat<PS, true> : scan_rows_flat<PS, false>;
+        if (c.rows * tpr <= kFlatMaxTiles &&
+            c.rows * tpr <= resident_slots(reinterpret_cast<const void*>(flat), PS::kBlock, lc)) {
+            void* status = nullptr;
+            const skel_status e = tile_status(lc, c.rows * tpr, &status);
+            if (e != SKEL_OK) return e;
+            if (status) {
+                flat<<<(unsigned)(c.rows * tpr), PS::kBlock, 0, lc.stream>>>(
+                    static_cast<const typename PS::in_t*>(c.x),
+                    static_cast<typename PS::out_t*>(c.y), c.cols, tpr, c.excl,
+                    static_cast<u64*>(status), lc.ws->sync);
+                return launch_check("scan_rows_flat");
+            }
+        } else {
+            bool done = false;
+            const skel_status e = c.cols <= PM::kTile ? run_tiles<PM>(c, lc, &done)
+                                                      : run_tiles<PL>(c, lc, &done);
+            if (e != SKEL_OK || done) return e;
+        }
+    }
+    if (c.cols <= 256) return run_wave<DIN, DOUT, OP, 1>(c, lc);
+    if (c.cols <= 512) return run_wave<DIN, DOUT, OP, 2>(c, lc);
+    if (c.cols <= 1024) return run_wave<DIN, DOUT, OP, 4>(c, lc);
+    return run_wave<DIN, DOUT, OP, 8>(c, lc);
+}
+
+template <int DIN, int DOUT>
+skel_status scan_rows_op(int op, const RowsCall& c, LaunchCtx& lc) {
+    switch (op) {
+    case SKEL_SUM: return scan_rows_typed<DIN, DOUT, SKEL_SUM>(c, lc);
+    case SKEL_MIN: return scan_rows_typed<DIN, DOUT, SKEL_MIN>(c, lc);
+    default: return scan_rows_typed<DIN, DOUT, SKEL_MAX>(c, lc);
+    }
+}
+
+}  // namespace
+
+skel_status launch_scan_rows(int kind, int op, skel_dtype din, skel_dtype dout, const void* x,
+                             void* y, int64_t rows, int64_t cols, LaunchCtx& lc) {
+    const RowsCall c{x, y, rows, cols,
+                     kind == SKEL_REVERSE_INCLUSIVE || kind == SKEL_REVERSE_EXCLUSIVE,
+                     kind == SKEL_EXCLUSIVE || kind == SKEL_REVERSE_EXCLUSIVE ? 1 : 0};
+    if (din == SKEL_I32 && dout == SKEL_I32) return scan_rows_op<SKEL_I32, SKEL_I32>(op, c, lc);
+    if (din == SKEL_I32) return scan_rows_op<SKEL_I32, SKEL_I64>(op, c, lc);
+    if (din == SKEL_I64) return scan_rows_op<SKEL_I64, SKEL_I64>(op, c, lc);
+    return scan_rows_op<SKEL_F32, SKEL_F32>(op, c, lc);
+}
+
+}  // namespace skel

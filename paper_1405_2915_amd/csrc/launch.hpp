@@ -114,10 +114,9 @@ skel_status launch_reduce_segments(int variant, int op, const float* x, int64_t 
 skel_status launch_scan(int variant, int kind, int op, skel_dtype din,
                         skel_dtype dout, const void* x, void* out, int64_t n,
                         LaunchCtx& lc);
-// every row of a rows x cols matrix scanned on its own, one wavefront per row;
-// vec: row starts are 16-byte aligned for both types (16-byte accesses)
+// every row of a rows x cols matrix scanned on its own, in one launch
 skel_status launch_scan_rows(int kind, int op, skel_dtype din, skel_dtype dout, const void* x,
-                             void* y, int64_t rows, int64_t cols, bool vec, LaunchCtx& lc);
+                             void* y, int64_t rows, int64_t cols, LaunchCtx& lc);
 // the call chain Map -> MapOverlap 2D -> Reduce SUM over `fields` images of
 // rows x cols (k_chain.hip): out[0] = the sum; the backward pass writes
 // dx = d(sum)/dx * g1[0] and, if dparams is not NULL, the parameter gradients

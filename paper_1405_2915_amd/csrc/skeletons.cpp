@@ -499,7 +499,7 @@ skel_status skel_scan_rows(skel_container* in, skel_container* out, skel_scan_ki
         if (in->n == 0) return SKEL_OK;
         if (v == SR1_WAVE_PER_ROW)
             return launch_scan_rows(kind, op, a, b, ops.ptr(in), ops.ptr(out), in->rows,
-                                    in->cols, cc.rows_aligned != 0, lc);
+                                    in->cols, lc);
         // every row's single-pass scan takes the same descriptor array and
         // advances the epoch once: the first row's call sizes the array
         // before it enqueues anything; that no later row has to reset it

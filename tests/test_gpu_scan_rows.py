@@ -139,3 +139,94 @@ def test_scan_rows_drawn_shapes(skel, oracle_mod, rows, cols, pair, kind, op, va
                         variant=variant)
     assert np.array_equal(out.to_numpy().reshape(rows, cols),
                           oracle_mod.scan_rows(x, kind, op, dout))
+
+
+# the forms of the single launch: 8, 16 and 32 lanes per row, a wavefront per row
+# with 1, 2, 4 and 8 vectors per lane, one workgroup of 4 and of 16 wavefronts per
+# row, the flat look-back within rows, the decoupled look-back within rows -- each
+# at its edges, rows at any alignment
+FORM_SHAPES = [(9, 15), (33, 31), (70, 33), (130, 65), (31, 127), (9, 129), (70, 257), (41, 1023),
+               (1030, 2047), (3, 4097), (700, 4099), (230, 8193), (40, 32769), (2, 500001),
+               (90, 65537), (300, 32767)]
+
+
+@pytest.mark.parametrize("pair", ["f32", "i32_i32", "i32_i64", "i64_i64"])
+def test_scan_rows_forms(skel, oracle_mod, pair):
+    din, dout, npd, npo = {"f32": (skel.F32, skel.F32, np.float32, np.float32),
+                           "i32_i32": (skel.I32, skel.I32, np.int32, np.int32),
+                           "i32_i64": (skel.I32, skel.I64, np.int32, np.int64),
+                           "i64_i64": (skel.I64, skel.I64, np.int64, np.int64)}[pair]
+    for rows, cols in FORM_SHAPES:
+        if pair == "f32":
+            x = si.normal_f32(rows * cols, 23, cols).reshape(rows, cols)
+        else:
+            x = si.int_uniform_i32(rows * cols, 1000, 23, cols).astype(npd).reshape(rows, cols)
+        cx = skel.Container.from_numpy(x)
+        for k, kind in enumerate(("inclusive", "exclusive", "reverse_inclusive",
+                                  "reverse_exclusive")):
+            out = skel.Container.empty(dout, rows, cols)
+            skel.skel_scan_rows(cx, out, k, skel.SUM, variant=SR1)
+            got = out.to_numpy().reshape(rows, cols)
+            v = x[:, ::-1] if k >= 2 else x
+            wide = np.cumsum(v, axis=1, dtype=np.float64 if pair == "f32" else np.int64)
+            if k % 2:
+                wide = wide - v
+            ref = wide[:, ::-1] if k >= 2 else wide
+            if pair == "f32":
+                mag = np.cumsum(np.abs(v), axis=1, dtype=np.float64)
+                mag = mag[:, ::-1] if k >= 2 else mag
+                bad = np.abs(got - ref) > 1e-5 * mag + 1e-30
+            else:
+                bad = got != ref.astype(npo)
+            assert not bad.any(), (pair, rows, cols, kind, np.argwhere(bad)[:3])
+    skel.skel_sync()
+
+
+@pytest.mark.parametrize("op", ["min", "max"])
+def test_scan_rows_forms_min_max_in_place(skel, op):
+    """In place; a NaN leaves the running minimum or maximum as it is."""
+    fn = np.fmin if op == "min" else np.fmax
+    for rows, cols in FORM_SHAPES:
+        x = si.normal_f32(rows * cols, 24, cols).reshape(rows, cols)
+        x[:, cols // 2] = np.nan
+        x[:, 0] = np.inf if op == "max" else -np.inf
+        c = skel.Container.from_numpy(x)
+        skel.skel_scan_rows(c, c, skel.REVERSE_INCLUSIVE, skel.MIN if op == "min" else skel.MAX,
+                            variant=SR1)
+        ref = fn.accumulate(x[:, ::-1], axis=1)[:, ::-1]
+        ident = np.float32(np.inf if op == "min" else -np.inf)
+        ref = np.where(np.isnan(ref), ident, ref)
+        assert np.array_equal(c.to_numpy().reshape(rows, cols), ref), (op, rows, cols)
+
+
+def test_scan_rows_tiled_form_under_capture(skel):
+    """A tiled shape whose descriptors were never allocated on the stream is
+    served inside a capture by the form that needs none; repeated replays give
+    the eager result."""
+    import torch
+    rows, cols = 90, 65537
+    xt = torch.randint(0, 1000, (rows, cols), device="cuda", dtype=torch.int32)
+    yt = torch.empty_like(xt)
+    cx, cy = skel.wrap_tensor(xt), skel.wrap_tensor(yt)
+    s = torch.cuda.Stream()
+    small = skel.wrap_tensor(xt[:1, :100].contiguous())
+    with torch.cuda.stream(s):  # the stream's workspace exists, its descriptors do not
+        skel.skel_map(skel.MAP_IDENTITY, None, [skel.Container.from_numpy(np.ones(4, np.float32))],
+                      skel.Container.empty(skel.F32, 4))
+    torch.cuda.synchronize()
+    want = torch.cumsum(xt.to(torch.int64), 1).to(torch.int32)
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=s):
+        skel.skel_scan_rows(cx, cy, skel.INCLUSIVE, skel.SUM, variant=SR1)
+    for _ in range(3):
+        yt.zero_()
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(yt, want)
+    with torch.cuda.stream(s):
+        yt.zero_()
+        skel.skel_scan_rows(cx, cy, skel.INCLUSIVE, skel.SUM, variant=SR1)
+    torch.cuda.synchronize()
+    assert torch.equal(yt, want)
+    for c in (cx, cy, small):
+        c.destroy()
