@@ -80,6 +80,7 @@ class _Allocator(C.Structure):
 
 
 _lib = None
+_call = None  # _skelcall, bound to the loaded library
 _live = weakref.WeakSet()
 _keepalive = []
 # handles of containers collected while a graph capture was running on the
@@ -154,8 +155,27 @@ def load_library(path: str = LIB_PATH):
                               "with `python -m paper_1405_2915_amd.build_lib`") from e
         fn.restype = res
         fn.argtypes = args
+    _bind_calls(lib, path)
     _lib = lib
     return lib
+
+
+def _bind_calls(lib, path) -> None:
+    """Give _skelcall (the skeleton calls without ctypes) the entry points of
+    the loaded library."""
+    global _call
+    try:
+        from . import _skelcall
+    except ImportError as e:
+        raise ImportError(f"_skelcall.so is not built or older than the sources ({e}); rebuild "
+                          "it with `python -m paper_1405_2915_amd.build_lib`") from e
+    _skelcall.bind(Container, _current_stream,
+                   {n: C.cast(getattr(lib, n), C.c_void_p).value
+                    for n in ("skel_map", "skel_reduce", "skel_mapreduce", "skel_mapoverlap1d",
+                              "skel_mapoverlap1d_backward", "skel_mapoverlap2d_fields",
+                              "skel_mapoverlap2d_fields_backward", "skel_scan", "skel_scan_rows",
+                              "skel_reduce_segments")})
+    _call = _skelcall
 
 
 def _L():
@@ -170,14 +190,28 @@ def _check(status: int, where: str) -> None:
 
 # torch's raw current-stream query (no Stream object per call), when present
 _RAW_STREAM = getattr(getattr(torch, "_C", None), "_cuda_getCurrentRawStream", None)
+_torch_initialized = getattr(getattr(torch, "cuda", None), "is_initialized", None)
 
 
 def _current_stream() -> int:
-    if torch is not None and torch.cuda.is_initialized():
+    if torch is not None and _torch_initialized():
         if _RAW_STREAM is not None:
             return _RAW_STREAM(_device)
         return torch.cuda.current_stream().cuda_stream
     return 0
+
+
+def _c():
+    if _call is None:
+        load_library()
+    return _call
+
+
+# The wrappers below hand plain arguments to _skelcall, which returns the call's
+# status; for any other argument it returns None, and the general path converts
+# or rejects it.
+def _s(stream):
+    return None if stream is None else _stream(stream)
 
 
 def _stream(stream) -> int:
@@ -531,6 +565,9 @@ def _floats(w):
 def skel_map(op: int, params, ins, out: Container, variant: int = VARIANT_AUTO,
              stream=None) -> None:
     """Map: out[i] = f(ins[0][i], ins[1][i])."""
+    st = _c().map(op, params, ins, out, variant, _s(stream))
+    if st is not None:
+        return _check(st, "skel_map")
     arr, nin = _handles(ins)
     ho = _h(out)
     p, pp, np_ = _params(params)
@@ -539,12 +576,18 @@ def skel_map(op: int, params, ins, out: Container, variant: int = VARIANT_AUTO,
 
 def skel_reduce(op: int, inp: Container, out1: Container, variant: int = VARIANT_AUTO,
                 stream=None) -> None:
+    st = _c().reduce(op, inp, out1, variant, _s(stream))
+    if st is not None:
+        return _check(st, "skel_reduce")
     _check(_L().skel_reduce(op, _h(inp), _h(out1), variant, _stream(stream)),
            "skel_reduce")
 
 
 def skel_mapreduce(map_op: int, params, ins, op: int, out1: Container,
                    variant: int = VARIANT_AUTO, stream=None) -> None:
+    st = _c().mapreduce(map_op, params, ins, op, out1, variant, _s(stream))
+    if st is not None:
+        return _check(st, "skel_mapreduce")
     arr, nin = _handles(ins)
     p, pp, np_ = _params(params)
     _check(_L().skel_mapreduce(map_op, pp, np_, arr, nin, op, _h(out1), variant,
@@ -554,6 +597,9 @@ def skel_mapreduce(map_op: int, params, ins, op: int, out1: Container,
 def skel_mapoverlap1d(inp: Container, out: Container, w, radius: int,
                       edge: int = EDGE_CLAMP, pad: float = 0.0,
                       variant: int = VARIANT_AUTO, stream=None) -> None:
+    st = _c().mapoverlap1d(inp, out, w, radius, edge, pad, variant, _s(stream))
+    if st is not None:
+        return _check(st, "skel_mapoverlap1d")
     wa, wp = _floats(w)
     if wa is None or wa.size != 2 * radius + 1:
         raise ValueError("w must hold 2*radius+1 weights")
@@ -587,6 +633,9 @@ def skel_mapoverlap2d(inp: Container, out: Container, w2d=None, wy=None, wx=None
                       ry: int | None = None, rx: int | None = None,
                       edge: int = EDGE_CLAMP, pad: float = 0.0,
                       variant: int = VARIANT_AUTO, stream=None) -> None:
+    st = _c().mapoverlap2d_fields(inp, out, 1, w2d, wy, wx, ry, rx, edge, pad, variant, _s(stream))
+    if st is not None:
+        return _check(st, "skel_mapoverlap2d")
     (p2, py, px), keep, ry, rx = _weights_2d(w2d, wy, wx, ry, rx)
     _check(_L().skel_mapoverlap2d(_h(inp), _h(out), p2, py, px, ry, rx, edge, pad, variant,
                                   _stream(stream)), "skel_mapoverlap2d")
@@ -598,6 +647,10 @@ def skel_mapoverlap2d_fields(inp: Container, out: Container, fields: int, w2d=No
                              variant: int = VARIANT_AUTO, stream=None) -> None:
     """The 2D map on each of `fields` equally shaped images stored back to back
     in (fields * H, W) containers."""
+    st = _c().mapoverlap2d_fields(inp, out, fields, w2d, wy, wx, ry, rx, edge, pad, variant,
+                                  _s(stream))
+    if st is not None:
+        return _check(st, "skel_mapoverlap2d_fields")
     (p2, py, px), keep, ry, rx = _weights_2d(w2d, wy, wx, ry, rx)
     _check(_L().skel_mapoverlap2d_fields(_h(inp), _h(out), fields, p2, py, px, ry, rx, edge,
                                          pad, variant, _stream(stream)),
@@ -606,6 +659,9 @@ def skel_mapoverlap2d_fields(inp: Container, out: Container, fields: int, w2d=No
 
 def skel_scan(inp: Container, out: Container, kind: int = INCLUSIVE, op: int = SUM,
               variant: int = VARIANT_AUTO, stream=None) -> None:
+    st = _c().scan(inp, out, kind, op, variant, _s(stream))
+    if st is not None:
+        return _check(st, "skel_scan")
     _check(_L().skel_scan(_h(inp), _h(out), kind, op, variant, _stream(stream)),
            "skel_scan")
 
@@ -623,6 +679,9 @@ def skel_scan_noalloc(in_ptr: int, din: int, out_ptr: int, dout: int, n: int,
 def skel_scan_rows(inp: Container, out: Container, kind: int = INCLUSIVE, op: int = SUM,
                    variant: int = VARIANT_AUTO, stream=None) -> None:
     """Scan every row of a (rows, cols) container on its own."""
+    st = _c().scan_rows(inp, out, kind, op, variant, _s(stream))
+    if st is not None:
+        return _check(st, "skel_scan_rows")
     _check(_L().skel_scan_rows(_h(inp), _h(out), kind, op, variant,
                                _stream(stream)), "skel_scan_rows")
 
@@ -630,6 +689,9 @@ def skel_scan_rows(inp: Container, out: Container, kind: int = INCLUSIVE, op: in
 def skel_reduce_segments(op: int, inp: Container, offsets: Container, out: Container,
                          variant: int = VARIANT_AUTO, stream=None) -> None:
     """out[s] = op over inp[offsets[s]:offsets[s+1]] for every segment s."""
+    st = _c().reduce_segments(op, inp, offsets, out, variant, _s(stream))
+    if st is not None:
+        return _check(st, "skel_reduce_segments")
     _check(_L().skel_reduce_segments(op, _h(inp), _h(offsets), _h(out), variant,
                                      _stream(stream)), "skel_reduce_segments")
 
@@ -650,6 +712,9 @@ def skel_map_backward(map_op: int, params, ins, g: Container, grad_ins,
 def skel_mapoverlap1d_backward(g: Container, grad_in: Container, w, radius: int,
                                edge: int = EDGE_CLAMP, variant: int = VARIANT_AUTO,
                                stream=None) -> None:
+    st = _c().mapoverlap1d_backward(g, grad_in, w, radius, edge, variant, _s(stream))
+    if st is not None:
+        return _check(st, "skel_mapoverlap1d_backward")
     wa, wp = _floats(w)
     if wa is None or wa.size != 2 * radius + 1:
         raise ValueError("w must hold 2*radius+1 weights")
@@ -662,6 +727,10 @@ def skel_mapoverlap2d_backward(g: Container, grad_in: Container, w2d=None, wy=No
                                ry: int | None = None, rx: int | None = None,
                                edge: int = EDGE_CLAMP, variant: int = VARIANT_AUTO,
                                stream=None) -> None:
+    st = _c().mapoverlap2d_fields_backward(g, grad_in, 1, w2d, wy, wx, ry, rx, edge, variant,
+                                           _s(stream))
+    if st is not None:
+        return _check(st, "skel_mapoverlap2d_backward")
     (p2, py, px), keep, ry, rx = _weights_2d(w2d, wy, wx, ry, rx)
     _check(_L().skel_mapoverlap2d_backward(_h(g), _h(grad_in), p2, py, px, ry, rx, edge,
                                            variant, _stream(stream)),
@@ -673,6 +742,10 @@ def skel_mapoverlap2d_fields_backward(g: Container, grad_in: Container, fields: 
                                       rx: int | None = None, edge: int = EDGE_CLAMP,
                                       variant: int = VARIANT_AUTO, stream=None) -> None:
     """The 2D transpose on each of `fields` equally shaped images."""
+    st = _c().mapoverlap2d_fields_backward(g, grad_in, fields, w2d, wy, wx, ry, rx, edge, variant,
+                                           _s(stream))
+    if st is not None:
+        return _check(st, "skel_mapoverlap2d_fields_backward")
     (p2, py, px), keep, ry, rx = _weights_2d(w2d, wy, wx, ry, rx)
     _check(_L().skel_mapoverlap2d_fields_backward(_h(g), _h(grad_in), fields, p2, py, px, ry,
                                                   rx, edge, variant,

@@ -14,6 +14,7 @@ import concurrent.futures as cf
 import os
 import subprocess
 import sys
+import sysconfig
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
@@ -65,6 +66,19 @@ def build_hip(verbose: bool = False, jobs: int = 8) -> str:
     return LIB
 
 
+CALL_LIB = os.path.join(PKG, "_skelcall.so")
+
+
+def build_call(verbose: bool = False) -> str:
+    """_skelcall.so: the Python binding's skeleton calls without ctypes."""
+    tmp = CALL_LIB + ".tmp"
+    _run(["g++", "-std=c++17", "-O2", "-fPIC", "-shared", "-Wall", f"-I{INC}",
+          "-I" + sysconfig.get_paths()["include"], "-o", tmp,
+          os.path.join(CSRC, "pycall.cpp")], verbose)
+    os.replace(tmp, CALL_LIB)
+    return CALL_LIB
+
+
 HOSTTEST_SAN_LIB = os.path.join(PKG, "libskel_hosttest_san.so")
 # AddressSanitizer and UndefinedBehaviorSanitizer for the host-only builds
 SANITIZE = ["-fsanitize=address,undefined", "-fno-omit-frame-pointer",
@@ -102,6 +116,7 @@ def build_scan_stress(verbose: bool = False) -> str:
 
 def build(verbose: bool = False) -> None:
     build_hip(verbose)
+    build_call(verbose)
     build_scan_stress(verbose)
     build_hosttest(verbose)
 

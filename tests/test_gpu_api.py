@@ -198,3 +198,82 @@ def test_failed_call_keeps_coherence_state(skel):
     assert out.valid_ranges(skel.DEVICE) == before[1]
     assert out.stats()["eager_equiv"] == before[2]["eager_equiv"]
     assert out.to_numpy()[0] == 42.0
+
+
+def test_plain_and_converted_arguments_agree(skel):
+    """Calls whose arguments are plain (containers, numbers, float32 arrays) go
+    straight to the library; the same values in other forms (lists, float64 and
+    strided arrays, numpy scalars, a Container subclass) are converted first.
+    Both give the same bits and raise the same errors."""
+    import torch
+
+    class Sub(skel.Container):
+        """a second name of another container's handle, which that one frees"""
+
+        def __del__(self):
+            pass
+
+    def sub(c):
+        d = object.__new__(Sub)
+        d.__dict__.update(c.__dict__)
+        return d
+
+    n = 3000
+    x = skel.Container.from_numpy(si.uniform_f32(n, -1.0, 1.0, 61, 0).reshape(50, 60))
+    k = skel.Container.from_numpy(si.int_uniform_i32(n, 100, 61, 1).reshape(50, 60))
+    off = skel.Container.from_numpy(np.array([0, 7, 7, 2999, 3000], np.int64))
+    w1 = si.uniform_f32(5, -1.0, 1.0, 61, 2)
+    w2 = si.uniform_f32(15, -1.0, 1.0, 61, 3).reshape(3, 5)
+    wy, wx = si.uniform_f32(3, 0.0, 1.0, 61, 4), si.uniform_f32(7, 0.0, 1.0, 61, 5)
+    f64 = lambda a: a.astype(np.float64)
+    strided = lambda a: np.repeat(a, 2, axis=-1)[..., ::2]
+    f32 = lambda *s: skel.Container.empty(skel.F32, *s)
+    i64 = lambda *s: skel.Container.empty(skel.I64, *s)
+    st = torch.cuda.current_stream()
+    calls = [
+        (f32, (50, 60), lambda o, c, a, p: skel.skel_map(skel.MAP_AFFINE, p([2.0, 0.5]), [c(x)], o)),
+        (f32, (1,), lambda o, c, a, p: skel.skel_reduce(skel.SUM, c(x), o)),
+        (f32, (1,), lambda o, c, a, p: skel.skel_mapreduce(skel.MAP_AXPY, p([3]), (c(x), c(x)),
+                                                           skel.MAX, o)),
+        (f32, (50, 60), lambda o, c, a, p: skel.skel_mapoverlap1d(c(x), o, a(w1), 2,
+                                                                  skel.EDGE_CONST, 0.25)),
+        (f32, (50, 60), lambda o, c, a, p: skel.skel_mapoverlap1d_backward(c(x), o, a(w1), 2)),
+        (f32, (50, 60), lambda o, c, a, p: skel.skel_mapoverlap2d(c(x), o, w2d=a(w2))),
+        (f32, (50, 60), lambda o, c, a, p: skel.skel_mapoverlap2d_fields(c(x), o, 2, wy=a(wy),
+                                                                         wx=a(wx))),
+        (f32, (50, 60), lambda o, c, a, p: skel.skel_mapoverlap2d_backward(c(x), o, wy=a(wy),
+                                                                           wx=a(wx), stream=st)),
+        (f32, (50, 60), lambda o, c, a, p: skel.skel_mapoverlap2d_fields_backward(
+            c(x), o, 5, w2d=a(w2), ry=1, rx=2)),
+        (i64, (50, 60), lambda o, c, a, p: skel.skel_scan(c(k), o, skel.EXCLUSIVE, skel.SUM)),
+        (i64, (50, 60), lambda o, c, a, p: skel.skel_scan_rows(c(k), o, skel.REVERSE_INCLUSIVE)),
+        (f32, (4,), lambda o, c, a, p: skel.skel_reduce_segments(skel.MIN, c(x), off, o)),
+    ]
+    same = lambda v: v
+    forms = [(same, same, same), (sub, f64, lambda p: [np.float64(v) for v in p]),
+             (same, strided, tuple), (same, lambda a: a.tolist(), same)]
+    for i, (make, shape, call) in enumerate(calls):
+        got = []
+        for c, a, p in forms:
+            o = make(*shape)
+            call(o, c, a, p)
+            got.append(o.to_numpy())
+        for g in got[1:]:
+            assert np.array_equal(got[0], g), i
+    # errors: the status of a call that the library refuses, the exceptions of
+    # arguments that the binding refuses
+    o = f32(50, 60)
+    for bad in (lambda: skel.skel_map(skel.MAP_AXPY, [2.5], [x], o),
+                lambda: skel.skel_map(skel.MAP_AXPY, np.array([2.5]), [x], o),
+                lambda: skel.skel_mapoverlap2d(x, x, w2d=w2)):
+        with pytest.raises(skel.SkelError) as e:
+            bad()
+        assert e.value.status == skel.E_INVAL
+    with pytest.raises(ValueError):
+        skel.skel_mapoverlap1d(x, o, w1, 3)
+    with pytest.raises(ValueError):
+        skel.skel_mapoverlap2d(x, o, wy=wy, wx=wx, ry=2)
+    dead = f32(4)
+    dead.destroy()
+    with pytest.raises(TypeError):
+        skel.skel_reduce(skel.SUM, dead, f32(1))
