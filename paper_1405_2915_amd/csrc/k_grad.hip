@@ -16,6 +16,8 @@
 //
 // All are HBM streams (map_grad: 12 to 20 bytes per element; adjoints: 8
 // bytes per element plus the cached neighbourhood reads).
+#include <type_traits>
+
 #include "kcommon.hpp"
 #include "kelem.hpp"
 #include "dispatch.hpp"
@@ -34,6 +36,13 @@ template <int OP>
 constexpr int grad_nparams() { return dev::map_nparams<OP>(); }
 using dev::elem_grad;
 
+constexpr int kGradVecs = 4;  // vectors in flight per lane and input
+
+// What bounds it: HBM.  Without parameter sums every workgroup takes one chunk
+// (2^26 elements: MUL 227 -> 213 us, TANH 133 -> 125 against a grid of 8 workgroups
+// per CU that walks the chunks); with them such a grid keeps the partials few,
+// and loads its next chunk before it computes (AFFINE_TANH 143 -> 135, AXPY 193
+// -> 184: 5.8 TB/s).
 template <int OP, bool BCAST>
 __global__ __launch_bounds__(kBlock) void map_grad(const float* x, const float* y,
                                                    const float* g, float* dx, float* dy,
@@ -41,7 +50,7 @@ __global__ __launch_bounds__(kBlock) void map_grad(const float* x, const float* 
                                                    float* partials) {
     constexpr bool TWO = grad_two_inputs<OP>();
     constexpr int NP = grad_nparams<OP>();
-    constexpr int U = 4;  // vectors in flight per lane and input
+    constexpr int U = kGradVecs;
     const float gb = BCAST ? g[0] : 0.0f;
     float a0 = 0.0f, a1 = 0.0f;
     const int64_t nv = n / 4;
@@ -50,28 +59,32 @@ __global__ __launch_bounds__(kBlock) void map_grad(const float* x, const float* 
     const f32x4* gv = reinterpret_cast<const f32x4*>(g);
     // chunks of U * kBlock vectors, every load of a chunk issued before the
     // arithmetic; single-use inputs and outputs are streamed non-temporally
-    for (int64_t c = (int64_t)blockIdx.x * U * kBlock; c < nv; c += (int64_t)gridDim.x * U * kBlock) {
-        f32x4 xa[U], ya[U], ga[U];
+    struct Chunk {
+        f32x4 x[U], y[U], g[U];
+    };
+    const auto load = [&](int64_t c, Chunk& k, auto full) {
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int64_t i = c + u * kBlock + threadIdx.x;
-            const bool in = i < nv;
-            xa[u] = in ? __builtin_nontemporal_load(&xv[i]) : f32x4{0.f, 0.f, 0.f, 0.f};
+            const bool in = decltype(full)::value || i < nv;
+            const f32x4 z = {0.f, 0.f, 0.f, 0.f};
+            k.x[u] = in ? __builtin_nontemporal_load(&xv[i]) : z;
             // y enters the derivatives of MUL only (AXPY's are 1 and p0)
-            ya[u] = (OP == SKEL_MAP_MUL && in) ? __builtin_nontemporal_load(&yv[i])
-                                               : f32x4{0.f, 0.f, 0.f, 0.f};
-            ga[u] = BCAST ? f32x4{gb, gb, gb, gb}
-                          : (in ? __builtin_nontemporal_load(&gv[i]) : f32x4{0.f, 0.f, 0.f, 0.f});
+            k.y[u] = (OP == SKEL_MAP_MUL && in) ? __builtin_nontemporal_load(&yv[i]) : z;
+            k.g[u] = BCAST ? f32x4{gb, gb, gb, gb}
+                           : (in ? __builtin_nontemporal_load(&gv[i]) : z);
         }
+    };
+    const auto use = [&](int64_t c, const Chunk& k, auto full) {
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int64_t i = c + u * kBlock + threadIdx.x;
-            if (i >= nv) break;
+            if (!decltype(full)::value && i >= nv) break;
             f32x4 ox, oy;
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 float ddx, ddy, s0, s1;
-                elem_grad<OP>(xa[u][e], ya[u][e], ga[u][e], p0, p1, ddx, ddy, s0, s1);
+                elem_grad<OP>(k.x[u][e], k.y[u][e], k.g[u][e], p0, p1, ddx, ddy, s0, s1);
                 ox[e] = ddx;
                 oy[e] = ddy;
                 a0 += s0;
@@ -80,6 +93,24 @@ __global__ __launch_bounds__(kBlock) void map_grad(const float* x, const float* 
             dev::store_vec_nt(ox, reinterpret_cast<f32x4*>(dx) + i);
             if constexpr (TWO) dev::store_vec_nt(oy, reinterpret_cast<f32x4*>(dy) + i);
         }
+    };
+    constexpr int64_t CH = U * kBlock;
+    const int64_t stride = (int64_t)gridDim.x * CH;
+    int64_t c = (int64_t)blockIdx.x * CH;
+    if (c + CH <= nv) {
+        // the next chunk's loads are issued before this chunk's arithmetic
+        Chunk next;
+        load(c, next, std::true_type());
+        for (; c + CH <= nv; c += stride) {
+            const Chunk k = next;
+            if (c + stride + CH <= nv) load(c + stride, next, std::true_type());
+            use(c, k, std::true_type());
+        }
+    }
+    if (c < nv) {
+        Chunk k;
+        load(c, k, std::false_type());
+        use(c, k, std::false_type());
     }
     // the n % 4 tail, one element per low lane of the first workgroup
     const int64_t t = nv * 4 + (int64_t)blockIdx.x * kBlock + threadIdx.x;
@@ -104,15 +135,25 @@ __global__ __launch_bounds__(kBlock) void map_grad(const float* x, const float* 
     }
 }
 
-// parameter gradients: the workgroups' partials summed in workgroup order
-__global__ __launch_bounds__(kBlock) void map_grad_finish(const float* partials, int groups,
-                                                          int nparams, float* out) {
-    __shared__ float l0[kBlock / dev::kWave], l1[kBlock / dev::kWave];
+// parameter gradients: the workgroups' partials (pairs) summed, two pairs per
+// load and lane, every lane's loads of a round in flight together (2048 pairs:
+// one round; 2^16 elements with two parameter sums: 7.4 -> 6.8 us for both
+// launches)
+constexpr int kFinish = 1024;
+__global__ __launch_bounds__(kFinish) void map_grad_finish(const float* partials, int groups,
+                                                           int nparams, float* out) {
+    __shared__ float l0[kFinish / dev::kWave], l1[kFinish / dev::kWave];
     using C = dev::Comb<float, SKEL_SUM>;
+    const f32x4* pv = reinterpret_cast<const f32x4*>(partials);
     float a0 = 0.0f, a1 = 0.0f;
-    for (int b = threadIdx.x; b < groups; b += kBlock) {
-        a0 += partials[2 * b];
-        a1 += partials[2 * b + 1];
+    for (int b = threadIdx.x; b < groups / 2; b += kFinish) {
+        const f32x4 v = pv[b];
+        a0 += v.x + v.z;
+        a1 += v.y + v.w;
+    }
+    if ((groups & 1) && threadIdx.x == 0) {
+        a0 += partials[2 * groups - 2];
+        a1 += partials[2 * groups - 1];
     }
     a0 = dev::block_reduce<C>(a0, l0);
     a1 = dev::block_reduce<C>(a1, l1);
@@ -237,7 +278,9 @@ skel_status map_grad_op(float p0, float p1, const float* x, const float* y, cons
                         bool bcast, float* dx, float* dy, int64_t n, float* dparams,
                         LaunchCtx& lc) {
     constexpr int NP = grad_nparams<OP>();
-    const int groups = grid_for((n + 15) / 16, *lc.dev);  // 4 vectors of 4 per lane
+    const int64_t chunks = (n / 4 + kGradVecs * kBlock - 1) / (kGradVecs * kBlock);
+    const int64_t cap = NP > 0 ? (int64_t)lc.dev->cus * 8 : INT64_C(1) << 30;
+    const int groups = (int)std::max<int64_t>(1, std::min(chunks, cap));
     float* partials = nullptr;
     if (NP > 0 && dparams) {
         void* mem = nullptr;
@@ -251,7 +294,7 @@ skel_status map_grad_op(float p0, float p1, const float* x, const float* y, cons
         map_grad<OP, false><<<groups, kBlock, 0, lc.stream>>>(x, y, g, dx, dy, n, p0, p1, partials);
     skel_status e = launch_check("map_grad");
     if (e != SKEL_OK || !partials) return e;
-    map_grad_finish<<<1, kBlock, 0, lc.stream>>>(partials, groups, NP, dparams);
+    map_grad_finish<<<1, kFinish, 0, lc.stream>>>(partials, groups, NP, dparams);
     return launch_check("map_grad_finish");
 }
 
