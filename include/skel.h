@@ -328,11 +328,10 @@ skel_status skel_scan(skel_container *in, skel_container *out,
  * (SKEL_SK_SCAN_ROWS): 0 runs one flat single-pass Scan per row (the plan's
  * choice for the row length; selectable only when every row starts 16-byte
  * aligned, i.e. cols * element size is a multiple of 16 for both types); 1
- * runs one wavefront per row in a single launch, with 16-byte accesses when
- * the rows are so aligned and element accesses otherwise.  The static rule
- * takes 0 for fewer than 64 aligned rows of at least 2^20 elements, else 1
- * (a few long rows that are not 16-byte aligned therefore run at one
- * wavefront per row, far below the device's bandwidth). */
+ * scans all rows in a single launch, whatever their alignment, in a form
+ * chosen by the shape: several short rows per wavefront, one wavefront per
+ * row, or a few long rows cut into tiles.  The static rule takes 0 for fewer
+ * than 64 aligned rows of at least 2^20 elements, else 1. */
 skel_status skel_scan_rows(skel_container *in, skel_container *out,
                            skel_scan_kind kind, skel_reduce_op op, int variant,
                            void *stream);
@@ -449,7 +448,8 @@ skel_status skel_map_backward(skel_map_op op, const double *params, int nparams,
  * SKEL_SK_MAPOVERLAP1D_BACKWARD): 0 gathers the transpose directly for every
  * element; 1 runs the forward stencil kernel on g with the weights reversed
  * (the transpose of a correlation inside the array) and a zero pad or the
- * cyclic rule, then recomputes the two end elements for CLAMP. */
+ * cyclic rule; the two end elements, which differ for CLAMP, are gathered in
+ * the same launch. */
 skel_status skel_mapoverlap1d_backward(skel_container *g, skel_container *grad_in,
                                        const float *w, int radius, skel_edge edge,
                                        int variant, void *stream);
@@ -461,8 +461,8 @@ skel_status skel_mapoverlap1d_backward(skel_container *g, skel_container *grad_i
  * edge rule; grad_in != g.  Variants (skeleton id
  * SKEL_SK_MAPOVERLAP2D_BACKWARD): 0 gathers directly for every pixel; 1 runs
  * the forward stencil kernels on g with the weights reversed along both axes
- * and a zero pad or the cyclic rule, then recomputes the first and last rows
- * and columns for CLAMP. */
+ * and a zero pad or the cyclic rule; the first and last rows and columns,
+ * which differ for CLAMP, are gathered beside them. */
 skel_status skel_mapoverlap2d_backward(skel_container *g, skel_container *grad_in,
                                        const float *w2d, const float *wy,
                                        const float *wx, int ry, int rx, skel_edge edge,

@@ -137,7 +137,7 @@ int static_rule(const CallContext& c) {
     case SKEL_SK_REDUCE_SEGMENTS: return B1_PERSISTENT;
     case SKEL_SK_SCAN_ROWS:
         // a few long rows: one single-pass scan per row fills the device;
-        // otherwise one wavefront per row
+        // otherwise one launch for all rows, in a form chosen by the shape
         return c.rows_aligned && c.rows < 64 && c.cols >= (INT64_C(1) << 20) ? SR0_PER_ROW
                                                                               : SR1_WAVE_PER_ROW;
     case SKEL_SK_MAPOVERLAP1D_BACKWARD:

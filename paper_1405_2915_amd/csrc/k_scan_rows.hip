@@ -294,15 +294,16 @@ skel_status run_wave(const RowsCall& c, LaunchCtx& lc) {
     return launch_check("scan_rows_wave");
 }
 
-// the descriptor array for a tiled form, or NULL where it cannot be had inside a
-// graph capture (the form that needs none then serves the call)
+// the descriptor array for a tiled form, or NULL (the form that needs none then
+// serves the call) where it cannot be allocated, and inside a graph capture: the
+// graph may be replayed beside other calls that use the stream's descriptors
 skel_status tile_status(LaunchCtx& lc, int64_t tiles, void** status) {
     *status = nullptr;
-    if (ws_status_ready(lc, (size_t)tiles * 16, 1) != SKEL_OK) {
-        clear_error();
-        return SKEL_OK;
-    }
-    return ws_status(lc, (size_t)tiles * 16, status);
+    if (capturing(lc)) return SKEL_OK;
+    const skel_status e = ws_status(lc, (size_t)tiles * 16, status);
+    if (e != SKEL_E_NOMEM) return e;
+    clear_error();
+    return SKEL_OK;
 }
 
 template <class P>

@@ -66,6 +66,7 @@ const DevInfo& device_info();
 skel_status workspace_for(void* stream, Workspace** out);
 skel_status ws_scratch(LaunchCtx& lc, size_t bytes, void** p);
 void retire(Workspace* w, void* p);  // free at skel_finalize, not before
+bool capturing(const LaunchCtx& lc);  // lc.stream is being captured into a graph
 // descriptor array of at least `bytes` for one call that advances the device
 // epoch; fails with SKEL_E_STATE if the array would have to grow (or be
 // cleared) while the stream is being captured into a graph

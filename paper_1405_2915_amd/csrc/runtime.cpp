@@ -180,15 +180,19 @@ skel_status workspace_for(void* stream, Workspace** out) {
     return SKEL_OK;
 }
 
+bool capturing(const LaunchCtx& lc) {
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(lc.stream, &cs) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return cs != hipStreamCaptureStatusNone;
+}
+
 skel_status ws_scratch(LaunchCtx& lc, size_t bytes, void** p) {
     Workspace* w = lc.ws;
     if (w->scratch_bytes < bytes) {
-        hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-        if (hipStreamIsCapturing(lc.stream, &cs) != hipSuccess) {
-            (void)hipGetLastError();
-            cs = hipStreamCaptureStatusNone;
-        }
-        if (cs != hipStreamCaptureStatusNone)
+        if (capturing(lc))
             return fail(SKEL_E_STATE,
                         "the scratch workspace must grow to %zu bytes while the stream is "
                         "captured; run the same call once before capture", bytes);
@@ -208,18 +212,14 @@ skel_status ws_scratch(LaunchCtx& lc, size_t bytes, void** p) {
 
 skel_status ws_status(LaunchCtx& lc, size_t bytes, void** p) {
     Workspace* w = lc.ws;
-    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(lc.stream, &cs) != hipSuccess) {
-        (void)hipGetLastError();
-        cs = hipStreamCaptureStatusNone;
-    }
-    const bool capturing = cs != hipStreamCaptureStatusNone;
-    // Growing the array, or clearing it before the device epoch can wrap onto
-    // words of an earlier cycle, resets the epoch; both enqueue fills, which
-    // must not happen inside a captured graph.
+    // A new array is cleared, and so is the present one before the device epoch
+    // can wrap onto words of an earlier cycle; both enqueue fills, which must not
+    // happen inside a captured graph.  Growth leaves the epoch alone: a graph
+    // captured before it replays on the old array, whose words are tagged with
+    // the epochs so far and would pass for its own if those came again.
     const bool grow = w->status_bytes < bytes;
     const bool wrap = w->epoch_calls >= (uint64_t)kEpochMax - 1;
-    if ((grow || wrap) && capturing)
+    if ((grow || wrap) && capturing(lc))
         return fail(SKEL_E_STATE,
                     "the descriptor workspace must be %s while the stream is captured; "
                     "run the same call once before capture",
@@ -238,11 +238,11 @@ skel_status ws_status(LaunchCtx& lc, size_t bytes, void** p) {
     if (grow || wrap) {
         skel_status st = hip_check(hipMemsetAsync(w->status, 0, w->status_bytes, lc.stream),
                                    "hipMemsetAsync");
-        if (st == SKEL_OK)
+        if (st == SKEL_OK && wrap)
             st = hip_check(hipMemsetAsync(w->sync + SYNC_EPOCH, 0, 8, lc.stream),
                            "hipMemsetAsync");
         if (st != SKEL_OK) return st;
-        w->epoch_calls = 0;
+        if (wrap) w->epoch_calls = 0;
     }
     w->epoch_calls += 1;
     *p = w->status;
@@ -251,12 +251,7 @@ skel_status ws_status(LaunchCtx& lc, size_t bytes, void** p) {
 
 skel_status ws_status_ready(LaunchCtx& lc, size_t bytes, int64_t calls) {
     if (calls <= 0) return SKEL_OK;
-    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(lc.stream, &cs) != hipSuccess) {
-        (void)hipGetLastError();
-        cs = hipStreamCaptureStatusNone;
-    }
-    if (cs == hipStreamCaptureStatusNone) return SKEL_OK;
+    if (!capturing(lc)) return SKEL_OK;
     const Workspace* w = lc.ws;
     if (w->status_bytes < bytes || w->epoch_calls + (uint64_t)calls >= (uint64_t)kEpochMax - 1)
         return fail(SKEL_E_STATE,

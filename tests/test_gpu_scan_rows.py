@@ -230,3 +230,47 @@ def test_scan_rows_tiled_form_under_capture(skel):
     assert torch.equal(yt, want)
     for c in (cx, cy, small):
         c.destroy()
+
+
+def test_row_scans_leave_captured_scans_intact(skel):
+    """A flat scan captured on a stream replays correctly after row scans on the
+    same stream have enlarged the descriptor array: words left on the array that
+    the graph uses never pass for a new call's."""
+    import torch
+    n = 5 * 32768 + 3
+    xt = torch.randint(0, 1000, (n,), device="cuda", dtype=torch.int32)
+    yt = torch.empty_like(xt)
+    cx, cy = skel.wrap_tensor(xt), skel.wrap_tensor(yt)
+    rows, cols = 700, 16 * 32768  # 700 x 16 tiles: more than the first array's words
+    rx = torch.ones((rows, cols), device="cuda", dtype=torch.int32)
+    crx = skel.wrap_tensor(rx)
+    s = torch.cuda.Stream()
+    s.wait_stream(torch.cuda.current_stream())
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.stream(s):
+        skel.skel_scan(cx, cy, skel.INCLUSIVE, skel.SUM, variant=2)
+    torch.cuda.synchronize()
+    with torch.cuda.graph(g, stream=s):
+        skel.skel_scan(cx, cy, skel.INCLUSIVE, skel.SUM, variant=2)
+    with torch.cuda.stream(s):
+        for _ in range(4):
+            g.replay()
+        skel.skel_scan_rows(crx, crx, skel.INCLUSIVE, skel.SUM, variant=SR1)
+    torch.cuda.synchronize()
+    assert int(rx[:, -1].min()) == cols == int(rx[:, -1].max())
+    # the old array holds the tags of the 5th call; were the epoch counted anew
+    # from the enlarging call, the next replay would be the 5th again
+    with torch.cuda.stream(s):
+        for _ in range(3):
+            skel.skel_scan_rows(crx, crx, skel.INCLUSIVE, skel.MAX, variant=SR1)
+    torch.cuda.synchronize()
+    for k in range(3):
+        xt.copy_(torch.randint(0, 1000, (n,), device="cuda", dtype=torch.int32))
+        yt.zero_()
+        torch.cuda.synchronize()
+        with torch.cuda.stream(s):
+            g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(yt, torch.cumsum(xt.to(torch.int64), 0).to(torch.int32)), k
+    for c in (cx, cy, crx):
+        c.destroy()
