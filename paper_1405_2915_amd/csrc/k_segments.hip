@@ -9,19 +9,20 @@
 //       plain loop a caller would write
 //   B1  whole batch: the work is divided over the elements, not over the
 //       segments.  Every workgroup takes one chunk of kChunk consecutive
-//       elements and finds the segments that start in it by a 64-ary search
-//       of the offsets, so many short segments and a few long ones load the
-//       device alike.  A chunk inside one segment is a plain reduction; a
+//       elements and reads which segments start in it from a table that the
+//       check of the offsets writes, so many short segments and a few long
+//       ones load the device alike.  A chunk inside one segment is a plain reduction; a
 //       chunk with segment starts is scanned once (a segmented scan in
 //       registers, its values in LDS) and every segment that ends in it reads
 //       its total at its last element.  What a segment has in other chunks is
 //       kept as partials, combined in chunk order by a last small launch
 //       (deterministic; no workgroup waits on another).
-//       Measured: 200003 segments of 1..256 elements (36 MB) 20.6 us, against
+//       Measured: 200003 segments of 1..256 elements (36 MB) 17.6 us, against
 //       1058 us for one work item per segment (each item costs a workgroup a
 //       search, two barriers and a ticket: 0.8 us of the 1024 resident
 //       workgroups' time, and the item table took one workgroup 0.5 ms);
-//       4096 log-uniform segments of 32..2^20 (1.65 GB) 251 us against 282.
+//       4096 log-uniform segments of 32..2^20 (1.65 GB) 258 us against 283;
+//       20011 of 1000..9000 62 us against 162.
 // B1 checks the offsets first: if they decrease or leave [0, n] nothing is
 // computed and error flag 4 is raised.
 #include "kcommon.hpp"
@@ -43,7 +44,10 @@ constexpr int kRows = 4;
 constexpr int kSlice = kWave * 4 * kRows;       // elements per wavefront: 1024
 constexpr int kChunk = kWaves * kSlice;         // elements per workgroup: 4096
 constexpr int kCheckBlocks = 64;                // workgroups of the offsets check
+constexpr int kOwnChunks = 4;                   // first[] entries one lane writes alone
+constexpr int kGroup = kWave;                   // chunks per group[] entry
 constexpr int kSerialPieces = 16;               // partials one lane combines alone
+constexpr int kWavePieces = 1024;               // and one wavefront, in one round of loads
 
 template <int OP>
 using CF = Comb<float, OP>;
@@ -103,24 +107,75 @@ __device__ __forceinline__ float range_reduce(const float* x, int64_t a, int64_t
 // Scratch of one call.  Every chunk writes its own entries, so nothing needs
 // clearing.
 //   bad[b]   workgroup b of the check saw an offset out of order or range
+//   group[g] the first s with off[s] >= the start of chunk c for every chunk c
+//            of group g (kGroup chunks), if that is one s; -1: see
+//   first[c] the same of chunk c alone
+//            (both for the chunks that begin in [0, off[nseg]] and end beyond
+//            off[0])
 //   fin[c]   the segment that began before chunk c and ends in it, or -1
 //   head[c]  op over chunk c's part of the segment that began before it
 //   tail[c]  op over chunk c's part of the segment that begins in c and ends
 //            after it
 struct SegWork {
     uint32_t* bad;
+    int64_t* group;
+    int64_t* first;
     int64_t* fin;
     float* head;
     float* tail;
 };
 
+// Checks the offsets and finds each chunk's first segment from the other side:
+// segment s (off[s] = lo, off[s + 1] = hi) is followed by s + 1 in the chunks
+// that begin in (lo, hi].  A lane writes up to kOwnChunks of them itself; a
+// wavefront writes a longer segment's together, one entry per whole group, so
+// that a segment of 2^28 elements takes 1024 stores instead of 65536 (30 us by
+// one wavefront).  Nothing is written for an offset that is out of order or
+// range.  The table saves every chunk a search of the offsets, two or three rounds
+// of dependent loads (200003 short segments 19.4 -> 17.1 us, 20011 of about 5000
+// elements 77 -> 63).
 __global__ __launch_bounds__(1024) void seg_check(const int64_t* off, int64_t nseg, int64_t n,
-                                                  SegWork wk, u64* err) {
+                                                  int64_t nchunks, SegWork wk, u64* err) {
     int b = 0;
-    for (int64_t s = (int64_t)blockIdx.x * 1024 + threadIdx.x; s < nseg;
-         s += (int64_t)kCheckBlocks * 1024) {
-        const int64_t lo = off[s], hi = off[s + 1];
-        b |= lo < 0 || hi < lo || hi > n;
+    const int64_t wave = (int64_t)(threadIdx.x / kWave) * kCheckBlocks + blockIdx.x;
+    for (int64_t base = wave * kWave; base < nseg; base += (int64_t)kCheckBlocks * 1024) {
+        const int64_t s = base + lane();
+        int64_t c = 0, count = 0;  // chunks c .. c + count - 1 follow segment s
+        if (s < nseg) {
+            const int64_t lo = off[s], hi = off[s + 1];
+            if (lo < 0 || hi < lo || hi > n) {
+                b = 1;
+            } else {
+                c = lo / kChunk + 1;
+                const int64_t end = hi / kChunk;
+                count = (end < nchunks ? end : nchunks - 1) - c + 1;
+                if (s == 0) {  // the chunk that off[0] lies in
+                    const int64_t c0 = c - 1 < nchunks ? c - 1 : nchunks - 1;
+                    wk.first[c0] = 0;
+                    wk.group[c0 / kGroup] = -1;
+                }
+            }
+        }
+        if (count <= kOwnChunks)
+            for (int64_t k = c; k < c + count; ++k) {
+                wk.first[k] = s + 1;
+                if (k % kGroup == 0) wk.group[k / kGroup] = -1;
+            }
+        for (u64 many = __ballot(count > kOwnChunks); many; many &= many - 1) {
+            const int l = __ffsll(many) - 1;
+            const int64_t a = lane_value(c, l), end = a + lane_value(count, l) - 1;
+            // groups that begin in a .. end; only the last may be cut short
+            const int64_t g0 = (a + kGroup - 1) / kGroup, g1 = end / kGroup;
+            for (int64_t g = g0 + lane(); g <= g1; g += kWave) {
+                const int64_t ge = g * kGroup + kGroup - 1;
+                wk.group[g] = end >= (ge < nchunks ? ge : nchunks - 1) ? base + l + 1 : -1;
+            }
+            // the chunks before the first group, and those of a last one cut short
+            int64_t k = a + lane();
+            if (k < g0 * kGroup && k <= end) wk.first[k] = base + l + 1;
+            k = g1 * kGroup + lane();
+            if (g1 >= g0 && k <= end) wk.first[k] = base + l + 1;
+        }
     }
     b = __syncthreads_or(b);
     if (threadIdx.x == 0) {
@@ -129,26 +184,11 @@ __global__ __launch_bounds__(1024) void seg_check(const int64_t* off, int64_t ns
     }
 }
 
-// first s in [0, nseg] with s == nseg or off[s] >= v, by one wavefront: every
-// round probes the last entry of 64 equal parts at once (200003 segments: 3
-// rounds of parallel loads).  The probes that lie below v form a prefix.
-__device__ __forceinline__ int64_t lower_bound(const int64_t* off, int64_t nseg, int64_t v) {
-    int64_t lo = 0, hi = nseg;  // the answer lies in [lo, hi]
-    while (hi > lo) {
-        const int64_t step = (hi - lo + kWave - 1) / kWave;
-        const int64_t p = lo + (int64_t)(lane() + 1) * step - 1;
-        const int below = __popcll(__ballot(p < hi && off[p] < v));
-        lo += (int64_t)below * step;
-        const int64_t nhi = lo + step - 1;
-        hi = nhi < hi ? nhi : hi;
-    }
-    return lo;
-}
-
 // What bounds it: long segments, HBM (one 16 KiB chunk per workgroup, all of
 // it in flight at once: 6.6 TB/s); short segments, the chain of dependent
-// loads of a chunk (flags and bounds, search, offsets) and the segmented scan's
-// arithmetic.
+// loads of a chunk (flags and table, offsets) and the segmented scan's latency
+// (its arithmetic does not show: a scan that moves one word per step instead of
+// two took as long).
 template <int OP>
 __global__ __launch_bounds__(kBlock) void seg_reduce_chunks(const float* x, int64_t n,
                                                             const int64_t* off, int64_t nseg,
@@ -159,19 +199,10 @@ __global__ __launch_bounds__(kBlock) void seg_reduce_chunks(const float* x, int6
     __shared__ uint32_t starts[kChunk / 32];  // bit e: a segment starts at element e
     __shared__ float slice_sum[kWaves];       // each slice's value since its last start
     __shared__ float lds[kWaves];
-    __shared__ int64_t bound[2];
     const int l = lane(), w = threadIdx.x / kWave;
     const int64_t c = blockIdx.x, c0 = c * kChunk, c1 = c0 + kChunk;
     const bool last = c == (int64_t)gridDim.x - 1;
-    uint32_t bad = 0;
-#pragma unroll
-    for (int k = 0; k < kCheckBlocks; ++k) bad |= wk.bad[k];
-    // offsets out of order, or a chunk outside [off[0], off[nseg]] (the last
-    // chunk also owns the empty segments at n)
-    if (bad || c0 > off[nseg] || (!last && c1 <= off[0])) {
-        if (threadIdx.x == 0) wk.fin[c] = -1;
-        return;
-    }
+    // the loads that depend on nothing go first
     f32x4 v[kRows];
 #pragma unroll
     for (int r = 0; r < kRows; ++r) {
@@ -183,15 +214,23 @@ __global__ __launch_bounds__(kBlock) void seg_reduce_chunks(const float* x, int6
             for (int e = 0; e < 4; ++e) v[r][e] = i + e < n ? x[i + e] : 0.0f;
         }
     }
-    if (w < 2) {
-        const int64_t b = w == 1 && last ? nseg : lower_bound(off, nseg, w == 0 ? c0 : c1);
-        if (l == 0) bound[w] = b;
+    uint32_t bad = 0;
+#pragma unroll
+    for (int k = 0; k < kCheckBlocks; ++k) bad |= wk.bad[k];
+    const int64_t off_end = off[nseg], off_begin = off[0];
+    const int64_t d = last ? c : c + 1;
+    const int64_t g0 = wk.group[c / kGroup], g1 = wk.group[d / kGroup];
+    const int64_t f0 = wk.first[c], f1 = wk.first[d];
+    // offsets out of order, or a chunk outside [off[0], off[nseg]] (the last
+    // chunk also owns the empty segments at n)
+    if (bad || c0 > off_end || (!last && c1 <= off_begin)) {
+        if (threadIdx.x == 0) wk.fin[c] = -1;
+        return;
     }
-    if (threadIdx.x < kChunk / 32) starts[threadIdx.x] = 0;
-    __syncthreads();
     // segments s0 .. s1 - 1 start in this chunk; segment s0 - 1 covers its
     // first element if it ends beyond c0
-    const int64_t s0 = bound[0], s1 = bound[1];
+    const int64_t s0 = g0 >= 0 ? g0 : f0;
+    const int64_t s1 = last || c1 > off_end ? nseg : g1 >= 0 ? g1 : f1;
     const int64_t he = off[s0];
     const bool has_head = s0 > 0 && he > c0;
     if (s0 == s1) {
@@ -215,6 +254,8 @@ __global__ __launch_bounds__(kBlock) void seg_reduce_chunks(const float* x, int6
         }
         return;
     }
+    if (threadIdx.x < kChunk / 32) starts[threadIdx.x] = 0;
+    __syncthreads();
     for (int64_t s = s0 + threadIdx.x; s < s1; s += kBlock) {
         const uint64_t p = (uint64_t)(off[s] - c0);  // (a start at n may equal kChunk)
         if (p < kChunk) atomicOr(&starts[p >> 5], 1u << (p & 31));
@@ -272,15 +313,20 @@ __global__ __launch_bounds__(kBlock) void seg_reduce_chunks(const float* x, int6
 
 // the segments that span chunks: lane t looks at one chunk and, if such a
 // segment ends in it, combines its partials in chunk order -- alone for a few
-// pieces, by the whole workgroup for many
+// pieces, by a wavefront (one round of loads) for more, by the whole workgroup
+// for many (4096 long segments: 4 us less than the workgroup for all but a few
+// pieces, one segment after another)
 template <int OP>
 __global__ __launch_bounds__(kBlock) void seg_finish(const int64_t* off, int64_t nchunks,
                                                      SegWork wk, float* out) {
     using C = CF<OP>;
+    struct Span {
+        int64_t seg, a, e;  // the pieces: tail[a], head[a + 1 .. e]
+    };
     __shared__ float lds[kWaves];
-    __shared__ int64_t todo[kBlock];
-    __shared__ int ntodo;
-    if (threadIdx.x == 0) ntodo = 0;
+    __shared__ Span todo[kBlock];  // a wavefront's from the front, the workgroup's from the back
+    __shared__ int ntodo, nlarge;
+    if (threadIdx.x == 0) ntodo = nlarge = 0;
     __syncthreads();
     const int64_t c = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     const int64_t seg = c < nchunks ? wk.fin[c] : -1;
@@ -297,26 +343,42 @@ __global__ __launch_bounds__(kBlock) void seg_finish(const int64_t* off, int64_t
 #pragma unroll
             for (int u = 0; u < kSerialPieces; ++u) t = C::op(t, h[u]);
             out[seg] = t;
+        } else if (c - a <= kWavePieces) {
+            todo[atomicAdd(&ntodo, 1)] = {seg, a, c};  // (any order: each is one segment)
         } else {
-            todo[atomicAdd(&ntodo, 1)] = c;  // (any order: each is one segment)
+            todo[kBlock - 1 - atomicAdd(&nlarge, 1)] = {seg, a, c};
         }
     }
     __syncthreads();
     const int m = ntodo;
-    for (int k = 0; k < m; ++k) {
-        const int64_t e = todo[k], s = wk.fin[e], a = off[s] / kChunk;
-        float t = threadIdx.x == 0 ? wk.tail[a] : C::id();
-        int64_t q = a + 1 + threadIdx.x;
-        for (; q + 15 * kBlock <= e; q += 16 * kBlock) {
+    for (int k = threadIdx.x / kWave; k < m; k += kWaves) {
+        const Span sp = todo[k];
+        float t = lane() == 0 ? wk.tail[sp.a] : C::id();
+        const int64_t q = sp.a + 1 + lane();
+        float h[kWavePieces / kWave];
+#pragma unroll
+        for (int u = 0; u < kWavePieces / kWave; ++u)
+            h[u] = q + u * kWave <= sp.e ? wk.head[q + u * kWave] : C::id();
+#pragma unroll
+        for (int u = 0; u < kWavePieces / kWave; ++u) t = C::op(t, h[u]);
+        t = wave_reduce<C>(t);
+        if (lane() == 0) out[sp.seg] = t;
+    }
+    const int big = nlarge;
+    for (int k = 0; k < big; ++k) {
+        const Span sp = todo[kBlock - 1 - k];
+        float t = threadIdx.x == 0 ? wk.tail[sp.a] : C::id();
+        int64_t q = sp.a + 1 + threadIdx.x;
+        for (; q + 15 * kBlock <= sp.e; q += 16 * kBlock) {
             float h[16];
 #pragma unroll
             for (int u = 0; u < 16; ++u) h[u] = wk.head[q + u * kBlock];
 #pragma unroll
             for (int u = 0; u < 16; ++u) t = C::op(t, h[u]);
         }
-        for (; q <= e; q += kBlock) t = C::op(t, wk.head[q]);
+        for (; q <= sp.e; q += kBlock) t = C::op(t, wk.head[q]);
         t = block_reduce<C>(t, lds);
-        if (threadIdx.x == 0) out[s] = t;
+        if (threadIdx.x == 0) out[sp.seg] = t;
         __syncthreads();  // lds is reused by the next segment
     }
 }
@@ -373,18 +435,23 @@ skel_status run_segments(int v, const float* x, int64_t n, const int64_t* off_de
     // B1: check, chunks, then the segments that span chunks
     const int64_t nchunks = n > 0 ? (n + kChunk - 1) / kChunk : 1;
     const auto up = [](size_t b) { return (b + 255) & ~size_t(255); };
-    const size_t bad_b = up(kCheckBlocks * sizeof(uint32_t)), fin_b = up((size_t)nchunks * 8),
+    const size_t bad_b = up(kCheckBlocks * sizeof(uint32_t)),
+                 group_b = up((size_t)((nchunks + kGroup - 1) / kGroup) * 8),
+                 first_b = up((size_t)nchunks * 8), fin_b = first_b,
                  part_b = up((size_t)nchunks * 4);
     void* mem = nullptr;
-    skel_status e = ws_scratch(lc, bad_b + fin_b + 2 * part_b, &mem);
+    skel_status e = ws_scratch(lc, bad_b + group_b + first_b + fin_b + 2 * part_b, &mem);
     if (e != SKEL_OK) return e;
     char* p = static_cast<char*>(mem);
     SegWork wk;
     wk.bad = reinterpret_cast<uint32_t*>(p);
-    wk.fin = reinterpret_cast<int64_t*>(p + bad_b);
-    wk.head = reinterpret_cast<float*>(p + bad_b + fin_b);
-    wk.tail = reinterpret_cast<float*>(p + bad_b + fin_b + part_b);
-    seg_check<<<kCheckBlocks, 1024, 0, st>>>(off_dev, nseg, n, wk, lc.ws->sync + SYNC_ERROR);
+    wk.group = reinterpret_cast<int64_t*>(p += bad_b);
+    wk.first = reinterpret_cast<int64_t*>(p += group_b);
+    wk.fin = reinterpret_cast<int64_t*>(p += first_b);
+    wk.head = reinterpret_cast<float*>(p += fin_b);
+    wk.tail = reinterpret_cast<float*>(p += part_b);
+    seg_check<<<kCheckBlocks, 1024, 0, st>>>(off_dev, nseg, n, nchunks, wk,
+                                             lc.ws->sync + SYNC_ERROR);
     if ((e = launch_check("reduce_segments_check")) != SKEL_OK) return e;
     seg_reduce_chunks<OP><<<(unsigned)nchunks, kBlock, 0, st>>>(x, n, off_dev, nseg, wk, out);
     if ((e = launch_check("reduce_segments_chunks")) != SKEL_OK || nchunks == 1) return e;

@@ -72,6 +72,24 @@ def test_segments_across_chunks(skel, oracle_mod, op, lens):
     skel.skel_sync()
 
 
+@pytest.mark.parametrize("op", list(RED_OPS))
+@pytest.mark.parametrize("lens,lead,trail", [
+    ([4 * 4096, 4 * 4096 + 1, 5 * 4096, 5 * 4096 - 1, 6 * 4096, 1], 4096, 3 * 4096),
+    ([7, 0, 90 * 4096, 0, 3, 70 * 4096 + 5] * 3, 2 * 4096 + 7, 1),
+    ([0, 0, 0], 3 * 4096, 0),                                  # all at the end of the data
+    ([0, 5, 0, 0], 0, 4 * 4096),                               # chunks past the last offset
+    ([3, 1023 * 4096, 1024 * 4096, 1025 * 4096, 2], 0, 0),     # pieces of one wavefront
+], ids=["own", "shared", "end", "past", "pieces"])
+def test_segments_first_of_each_chunk(skel, oracle_mod, op, lens, lead, trail):
+    """The table of each chunk's first segment: entries written by one lane (up
+    to four chunks per segment) and by a wavefront, chunks before the first and
+    after the last offset, and segments of about 1024 chunks."""
+    off = (lead + np.concatenate([[0], np.cumsum(lens)])).astype(np.int64)
+    x = si.normal_f32(int(off[-1]) + trail, 2, 33)
+    check_segments(skel, oracle_mod, x, off, op, 1)
+    skel.skel_sync()
+
+
 def test_segments_log_uniform_batch(skel, oracle_mod):
     lens = si.log_uniform_lengths(512, 32, 1 << 20, config=2, index=10)
     off = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
