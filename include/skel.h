@@ -462,7 +462,8 @@ skel_status skel_mapoverlap1d_backward(skel_container *g, skel_container *grad_i
  * SKEL_SK_MAPOVERLAP2D_BACKWARD): 0 gathers directly for every pixel; 1 runs
  * the forward stencil kernels on g with the weights reversed along both axes
  * and a zero pad or the cyclic rule; the first and last rows and columns,
- * which differ for CLAMP, are gathered beside them. */
+ * which differ for CLAMP, are gathered beside them (weights of radii up to 1
+ * that mirror along both axes need neither: the clamped map is symmetric). */
 skel_status skel_mapoverlap2d_backward(skel_container *g, skel_container *grad_in,
                                        const float *w2d, const float *wy,
                                        const float *wx, int ry, int rx, skel_edge edge,

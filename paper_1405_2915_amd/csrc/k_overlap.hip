@@ -1238,12 +1238,31 @@ skel_status launch_overlap2d_transposed(const float* g, float* dx, int64_t rows,
     const int r = ry > rx ? ry : rx;
     const int v = w2d ? overlap2d_dense_variant(n, rows, cols, r)
                       : overlap2d_separable_variant(n, rows, cols, r);
+    // A clamped map of radii up to 1 whose weights mirror along both axes is its
+    // own transpose: along an axis it is w1 I + w0 (down + up), and the shifts
+    // down and up, each with its clamped end, add up to a symmetric matrix (the
+    // diagonal entries of the two ends, the off-diagonals 1).  Every output is a
+    // sum of the same products, and no border has to be gathered (64 images of
+    // 2048^2, 5-point: a launch of 23 us in the kernel trace; a training pass
+    // over them 2117 -> 2077 us).  At radius 2 the clamped shifts are not
+    // symmetric (row 1 reads element 0 at distance 2, row 0 never reads row 1
+    // at that distance).
+    const auto mirrored = [](const float* w, int n, int step) {
+        return w[0] == w[(n - 1) * step];
+    };
+    bool self = edge == SKEL_EDGE_CLAMP && ry <= 1 && rx <= 1;
+    if (w2d) {
+        for (int a = 0; self && a < ny; ++a) self = mirrored(w2d + a * nx, nx, 1);
+        for (int b = 0; self && b < nx; ++b) self = mirrored(w2d + b, ny, nx);
+    } else if (self) {
+        self = mirrored(wy, ny, 1) && mirrored(wx, nx, 1);
+    }
     int nbb = 0;
-    if (edge == SKEL_EDGE_CLAMP)
+    if (edge == SKEL_EDGE_CLAMP && !self)
         nbb = (int)div_up(((rows > 1 ? 2 : 1) * cols +
                            (cols > 1 ? 2 : 1) * (rows > 2 ? rows - 2 : 0)) * kBorderG, kBlock);
     const Call2 c{g, dx, rows, cols, 0, wk, !w2d, ry, rx,
-                  edge == SKEL_EDGE_CYCLIC ? SKEL_EDGE_CYCLIC : SKEL_EDGE_CONST, 0.0f, nbb,
+                  edge == SKEL_EDGE_CYCLIC || self ? edge : SKEL_EDGE_CONST, 0.0f, nbb,
                   lc.dev->cus, lc.stream};
     return run2d_fields(v, c, fields);
 }

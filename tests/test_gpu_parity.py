@@ -355,6 +355,35 @@ def test_mapoverlap2d_tiles_and_transpose(skel, oracle_mod, edge, ry, rx):
             assert not bad.any(), (edge, ry, rx, shape, "transpose", np.argwhere(bad)[:3])
 
 
+@pytest.mark.parametrize("mirror", ["both", "rows", "cols"])
+@pytest.mark.parametrize("ry,rx", [(1, 1), (0, 1), (1, 0), (0, 0), (1, 2), (2, 1)])
+def test_mapoverlap2d_transpose_of_mirrored_weights(skel, oracle_mod, ry, rx, mirror):
+    """Weights that mirror along both axes make a clamped map of radii up to 1
+    its own transpose; along one axis only, or beyond radius 1, they do not.
+    Tolerance as for the tiles, on images of one tile and of marching strips."""
+    ny, nx = 2 * ry + 1, 2 * rx + 1
+    w2d = si.uniform_f32(ny * nx, -1.0, 1.0, 53, 1).reshape(ny, nx)
+    wy, wx = si.uniform_f32(ny, -1.0, 1.0, 53, 2), si.uniform_f32(nx, -1.0, 1.0, 53, 3)
+    if mirror != "cols":
+        w2d, wy = np.maximum(w2d, w2d[::-1]), np.maximum(wy, wy[::-1])
+    if mirror != "rows":
+        w2d, wx = np.maximum(w2d, w2d[:, ::-1]), np.maximum(wx, wx[::-1])
+    tol = (ny * nx + 8) * 2.0 ** -24
+    for shape, fields in (((1, 70), 1), ((70, 1), 1), ((2, 2), 1), ((17, 65), 3), ((12, 1024), 90)):
+        x = si.uniform_f32(fields * shape[0] * shape[1], -1.0, 1.0, 53, 4)
+        x = x.reshape(fields * shape[0], shape[1])
+        for kw in ({"w2d": w2d}, {"wy": wy, "wx": wx}):
+            out = skel.Container.empty(skel.F32, *x.shape)
+            skel.skel_mapoverlap2d_fields_backward(cont(skel, x), out, fields, ry=ry, rx=rx,
+                                                   edge=EDGES["clamp"], **kw)
+            got = out.to_numpy().reshape(x.shape).astype(np.float64)
+            for f in (0, fields - 1):
+                part = slice(f * shape[0], (f + 1) * shape[0])
+                ref, mag = oracle_mod.mapoverlap2d_adjoint(x[part], ry, rx, edge="clamp", **kw)
+                bad = np.abs(got[part] - ref) > tol * mag + 1e-30
+                assert not bad.any(), (shape, f, list(kw), np.argwhere(bad)[:3])
+
+
 @pytest.mark.parametrize("sep", [False, True])
 def test_mapoverlap2d_two_row_tiles(skel, oracle_mod, sep):
     """2^23 pixels and more: two rows per lane; unaligned rows, a ragged last
