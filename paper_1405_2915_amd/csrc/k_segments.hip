@@ -21,7 +21,7 @@
 //       1058 us for one work item per segment (each item costs a workgroup a
 //       search, two barriers and a ticket: 0.8 us of the 1024 resident
 //       workgroups' time, and the item table took one workgroup 0.5 ms);
-//       4096 log-uniform segments of 32..2^20 (1.65 GB) 258 us against 283;
+//       4096 log-uniform segments of 32..2^20 (1.65 GB) 249 us against 277;
 //       20011 of 1000..9000 62 us against 162.
 // B1 checks the offsets first: if they decrease or leave [0, n] nothing is
 // computed and error flag 4 is raised.
@@ -44,6 +44,7 @@ constexpr int kRows = 4;
 constexpr int kSlice = kWave * 4 * kRows;       // elements per wavefront: 1024
 constexpr int kChunk = kWaves * kSlice;         // elements per workgroup: 4096
 constexpr int kCheckBlocks = 64;                // workgroups of the offsets check
+constexpr int kCheckWaves = kCheckBlocks * 1024 / kWave;
 constexpr int kOwnChunks = 4;                   // first[] entries one lane writes alone
 constexpr int kGroup = kWave;                   // chunks per group[] entry
 constexpr int kSerialPieces = 16;               // partials one lane combines alone
@@ -138,8 +139,13 @@ __global__ __launch_bounds__(1024) void seg_check(const int64_t* off, int64_t ns
                                                   int64_t nchunks, SegWork wk, u64* err) {
     int b = 0;
     const int64_t wave = (int64_t)(threadIdx.x / kWave) * kCheckBlocks + blockIdx.x;
-    for (int64_t base = wave * kWave; base < nseg; base += (int64_t)kCheckBlocks * 1024) {
-        const int64_t s = base + lane();
+    // few segments are spread over the wavefronts, whose long ones go in turn
+    // (4096 long segments 258.4 -> 254.3 us); fewer than four per wavefront cost
+    // short ones more (900: 9.3 -> 9.5 us at one)
+    const int64_t share = (nseg + kCheckWaves - 1) / kCheckWaves;
+    const int64_t per = share < 4 ? 4 : share < kWave ? share : kWave;
+    for (int64_t base = wave * per; base < nseg; base += kCheckWaves * per) {
+        const int64_t s = lane() < per ? base + lane() : nseg;
         int64_t c = 0, count = 0;  // chunks c .. c + count - 1 follow segment s
         if (s < nseg) {
             const int64_t lo = off[s], hi = off[s + 1];
