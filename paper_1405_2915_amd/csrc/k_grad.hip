@@ -128,7 +128,7 @@ __global__ __launch_bounds__(kBlock) void map_grad(const float* x, const float* 
         using C = dev::Comb<float, SKEL_SUM>;
         a0 = dev::block_reduce<C>(a0, l0);
         a1 = dev::block_reduce<C>(a1, l1);
-        if (threadIdx.x == 0) {
+        if (threadIdx.x == 0 && partials) {  // (NULL: no parameter gradients wanted)
             partials[2 * blockIdx.x] = a0;
             partials[2 * blockIdx.x + 1] = a1;
         }

@@ -142,6 +142,25 @@ def test_map_backward(skel, oracle_mod, op, bcast):
             assert np.all(np.abs(got - dp_ref) <= 1e-5 * dp_mag + 1e-30), (op, n, got, dp_ref)
 
 
+@pytest.mark.parametrize("op", list(PARAMS))
+def test_map_backward_without_parameter_gradients(skel, oracle_mod, op):
+    """grad_params is optional for the ops that have parameters."""
+    p = PARAMS[op]
+    two = op in oracle_mod.TWO_INPUT_MAP_OPS
+    for n in (0, 3, 4097, (1 << 20) + 3):
+        x, y, g = (si.normal_f32(n, 9, k) for k in range(3))
+        dx_ref, dy_ref, _, _ = oracle_mod.map_grad(op, p, x, g, y if two else None)
+        gx, gy = skel.Container.empty(skel.F32, n), skel.Container.empty(skel.F32, n)
+        skel.skel_map_backward(MAP_OPS[op], p, [cont(skel, x), cont(skel, y)][:1 + two],
+                               cont(skel, g), [gx, gy][:1 + two])
+        sx, sy = grad_scale(op, p, x, y)
+        ag = np.abs(g.astype(np.float64))
+        assert np.all(np.abs(gx.to_numpy() - dx_ref) <= 1e-6 * ag * sx + 1e-30), (op, n)
+        if two:
+            assert np.all(np.abs(gy.to_numpy() - dy_ref) <= 1e-6 * ag * sy + 1e-30), (op, n)
+    skel.skel_sync()
+
+
 def test_map_backward_rejects_bad_calls(skel):
     x = cont(skel, np.ones(8, np.float32))
     g = cont(skel, np.ones(8, np.float32))
