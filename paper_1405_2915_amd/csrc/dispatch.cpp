@@ -13,8 +13,15 @@ namespace skel {
 static bool whole_strips(int64_t cols) { return cols % 256 == 0; }
 
 static bool overlap2d_march(int64_t n, int64_t rows, int64_t cols, int radius) {
-    if (radius > 2) return false;
-    return rows < 16 ? n >= (INT64_C(1) << 20) : whole_strips(cols) && n >= (INT64_C(1) << 24);
+    if (radius > 2 || n < (INT64_C(1) << 20)) return false;
+    const bool whole = whole_strips(cols), one = radius <= 1;
+    const bool wide = 5 * ((cols + 255) / 256 * 256) <= 6 * cols;  // strips at least 5/6 full
+    if (wide && rows <= (one ? 8 : 4)) return true;
+    if (n < (INT64_C(1) << 21) || (rows > 8 && rows < 16)) return false;
+    const int over = (int)(rows % 16);  // rows past the last whole strips
+    if (!whole) return one && cols >= 256 && over == 1 && rows < 64;
+    return n >= (INT64_C(1) << 24) || over == 0 || (over <= 4 && rows < 128) ||
+           (one && rows <= 256);
 }
 
 int overlap2d_dense_variant(int64_t n, int64_t rows, int64_t cols, int radius) {
@@ -22,7 +29,8 @@ int overlap2d_dense_variant(int64_t n, int64_t rows, int64_t cols, int radius) {
 }
 
 int overlap2d_separable_variant(int64_t n, int64_t rows, int64_t cols, int radius) {
-    return overlap2d_march(n, rows, cols, radius) ? O2E_MARCH : O2D_SEPARABLE_L1;
+    if (overlap2d_march(n, rows, cols, radius)) return O2E_MARCH;
+    return radius <= 2 ? O2C_LDS_SEPARABLE : O2D_SEPARABLE_L1;
 }
 
 namespace {

@@ -50,16 +50,23 @@ struct CallContext {
 };
 
 // 2D neighbourhood map of n pixels in images of rows x cols: the marching
-// window where it beats the tiles, else the LDS tile (dense weights) or the
-// separable L1 tile (factors).  Also the forward pass that the flipped transpose
-// runs.  The marching window holds a strip of 256 columns x 16 rows per
-// wavefront, so it wants whole strips, enough of them to fill the device several
-// times (2^24 pixels) and a radius of at most 2; images of fewer than 16 rows,
-// which leave most of a tile idle, take it from 2^20 pixels on at any width.
-// Measured, map and clamped transpose, marching / tile: 5 x 5 on 64 fields of
-// 2048^2 781 / 871 us, separable 3 x 3 756 / 841, 5 x 5 740 / 900, 5-point 740 /
-// 740; on 8192^2 206 / 201 (5-point) and 209 / 213 (separable 5 x 5); but 5-point
-// on 1024^2 15.3 / 10.1, 2896^2 34 / 27, 3000^2 48 / 29, 1501 x 1999 43 / 18.
+// window where it beats the tiles, else the LDS tile (dense weights), the
+// separable LDS tile (factors of radius <= 2) or the separable L1 tile (larger
+// factors).  Also the forward pass that the flipped transpose runs.  The marching
+// window holds a strip of 256 columns x 16 rows per wavefront and walks the rows
+// past the last whole strip one by one; a tile holds 64 x 16 or 64 x 32.  So the
+// marching window wants whole strips, 2^21 pixels of them and a radius of at most
+// 2; it also takes images whose tiles would be mostly idle rows.
+// Measured (marching / tile, us, the map alone, binary32, 2^20 to 2^24 pixels in
+// all): 5-point on one image of 1024^2 6.3 / 5.7, 2048^2 6.6 / 9.4, 4096^2 24.9 /
+// 23.8, 1500 x 1536 11.0 / 6.9, 3000 x 3072 19.3 / 14.5, 1501 x 1999 16.7 / 9.0; on
+// many images of 3 x 256 15.9 / 40.1, 3 x 1000 22.2 / 41.4, 12 x 256 13.2 / 12.4,
+// 12 x 1000 19.5 / 13.3, 16 x 256 7.9 / 11.0, 17 x 256 7.9 / 18.6, 17 x 1000 12.0 /
+// 19.3, 64 x 256 7.0 / 11.2, 64 x 64 17.3 / 11.4, 64 x 1000 16.7 / 11.6, 100 x 256
+// 8.3 / 11.9, 250 x 256 10.8 / 11.9; dense 5 x 5 on 3 x 256 39.9 / 56.0, 8 x 256 27.8
+// / 25.4, 24 x 256 21.8 / 16.4, 64 x 256 9.1 / 12.6, 2048^2 9.0 / 10.6.
+// The separable tile against the L1 tile, 3 x 3: 4096^2 24.1 / 27.6, 1501 x 1999 9.3 /
+// 10.7, 419 images of 100 x 100 15.0 / 19.3.
 int overlap2d_dense_variant(int64_t n, int64_t rows, int64_t cols, int radius);
 int overlap2d_separable_variant(int64_t n, int64_t rows, int64_t cols, int radius);
 

@@ -436,6 +436,34 @@ def test_static_plan(rt):
     assert rt.skel_select_variant(17, F32, 10, 1, 10, 0) == -1
 
 
+def test_2d_form_by_image_shape(rt):
+    """The static rule's form for images of one shape: aux = separable + 2 * radius."""
+    def form(fields, rows, cols, aux):
+        return name_of(rt, SK_OV2, rt.skel_select_variant(SK_OV2, F32, fields * rows * cols, rows,
+                                                          cols, aux))
+    for aux, tile in ((2 * 1, "O2b_lds_tile"), (2 * 2, "O2b_lds_tile"),
+                      (1 + 2 * 1, "O2c_lds_separable"), (1 + 2 * 2, "O2c_lds_separable")):
+        one = aux // 2 == 1
+        march = lambda yes: "O2e_march" if yes else tile  # noqa: E731
+        assert form(1, 1024, 1024, aux) == tile           # too few strips to fill the device
+        assert form(1, 2048, 2048, aux) == march(True)    # whole strips
+        assert form(64, 2048, 2048, aux) == march(True)
+        assert form(1, 1500, 1536, aux) == tile           # rows past the last strips
+        assert form(1, 1501, 1999, aux) == tile
+        assert form(16384, 16, 16, aux) == tile           # strips mostly empty
+        assert form(1000, 100, 100, aux) == tile
+        assert form(1365, 12, 256, aux) == tile
+        assert form(1398, 3, 1000, aux) == march(True)    # tiles mostly empty
+        assert form(2048, 8, 256, aux) == march(one)
+        assert form(963, 17, 256, aux) == march(True)
+        assert form(246, 17, 1000, aux) == march(one)
+        assert form(163, 100, 256, aux) == march(True)
+        assert form(64, 250, 256, aux) == march(one)
+        assert form(1, 1 << 22, 3, aux) == tile
+    assert form(1, 2048, 2048, 2 * 3) == "O2b_lds_tile"
+    assert form(1, 2048, 2048, 1 + 2 * 3) == "O2d_separable_l1"
+
+
 def test_plan_table(rt, tmp_path):
     p = tmp_path / "plan.txt"
     p.write_text("# tuned\nREDUCE f32 10 R1_two_pass\nREDUCE f32 20 R3_atomic\n"

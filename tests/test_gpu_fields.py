@@ -57,6 +57,38 @@ def test_fields_forward_and_backward(skel, oracle_mod, edge, sep, r):
     skel.skel_sync()
 
 
+# images of 1, 2, 3, 6, 8, 9, 12 and 17 tiles of 64 x 16: every remainder of the tile
+# count over the eight XCDs that matters, and axes shorter than the halo
+@pytest.mark.parametrize("edge", list(EDGES))
+@pytest.mark.parametrize("r", [1, 2, 6])
+def test_fields_of_few_tiles(skel, oracle_mod, edge, r):
+    for f, h, wd in ((7, 16, 16), (3, 5, 70), (3, 3, 130), (2, 33, 65), (2, 49, 100),
+                     (2, 33, 131), (2, 49, 130), (2, 260, 3)):
+        x = si.uniform_f32(f * h * wd, -1.0, 1.0, 26, f * 1000 + h).reshape(f * h, wd)
+        cx = skel.Container.from_numpy(x)
+        for sep in (False, True):
+            w = weights(sep, r, 50 * r + sep)
+            calls = [("map", v) for v in (1, 2, 3, 4) if (sep or v in (1, 4)) and (v < 4 or r <= 4)]
+            for what, v in calls + [("transpose", 1)]:
+                out = skel.Container.empty(skel.F32, f * h, wd)
+                if what == "map":
+                    skel.skel_mapoverlap2d_fields(cx, out, f, edge=EDGES[edge], pad=0.25,
+                                                  variant=v, **w)
+                else:
+                    skel.skel_mapoverlap2d_fields_backward(cx, out, f, edge=EDGES[edge],
+                                                           variant=v, **w)
+                got = out.to_numpy().reshape(f, h, wd)
+                for k in range(f):
+                    img = x[k * h:(k + 1) * h]
+                    ref, mag = (oracle_mod.mapoverlap2d(img, r, r, edge=edge, pad=0.25, **w)
+                                if what == "map" else
+                                oracle_mod.mapoverlap2d_adjoint(img, r, r, edge=edge, **w))
+                    bad = np.abs(got[k] - ref) > 1e-6 * mag + 1e-30
+                    assert not bad.any(), (edge, sep, r, (f, h, wd), what, v, k,
+                                           np.argwhere(bad)[:3])
+    skel.skel_sync()
+
+
 def test_fields_beyond_one_launch(skel, oracle_mod):
     # more fields than one launch's grid holds (65535): the launcher splits them
     f, h, wd = 70001, 2, 4
