@@ -331,13 +331,17 @@ skel_status scan_rows_typed(const RowsCall& c, LaunchCtx& lc) {
     if (c.cols <= 32 * E) {
         const int G = c.cols <= 8 * E ? 8 : c.cols <= 16 * E ? 16 : 32;
         const auto kern = c.rev ? scan_rows_short<PS, true> : scan_rows_short<PS, false>;
-        const int64_t grid = (c.rows * G + kShortBlock - 1) / kShortBlock;
-        if (grid < (INT64_C(1) << 31)) {
-            kern<<<(unsigned)grid, kShortBlock, 0, lc.stream>>>(
-                static_cast<const typename PS::in_t*>(c.x), static_cast<typename PS::out_t*>(c.y),
-                c.rows, (int)c.cols, c.excl, G);
-            return launch_check("scan_rows_short");
+        // (2^29 rows at 8 lanes are more work items than one launch numbers)
+        const int64_t per_group = kShortBlock / G, most = max_groups(kShortBlock) * per_group;
+        for (int64_t r = 0; r < c.rows; r += most) {
+            const int64_t rows = std::min(c.rows - r, most);
+            kern<<<(unsigned)((rows + per_group - 1) / per_group), kShortBlock, 0, lc.stream>>>(
+                static_cast<const typename PS::in_t*>(c.x) + r * c.cols,
+                static_cast<typename PS::out_t*>(c.y) + r * c.cols, rows, (int)c.cols, c.excl, G);
+            const skel_status e = launch_check("scan_rows_short");
+            if (e != SKEL_OK) return e;
         }
+        return SKEL_OK;
     }
     if (c.rows < kFewRows && c.cols > kLongRow) {
         const int64_t tpr = (c.cols + PS::kTile - 1) / PS::kTile;

@@ -66,6 +66,9 @@ const DevInfo& device_info();
 skel_status workspace_for(void* stream, Workspace** out);
 skel_status ws_scratch(LaunchCtx& lc, size_t bytes, void** p);
 void retire(Workspace* w, void* p);  // free at skel_finalize, not before
+// most workgroups of `block` lanes along one dimension of a launch (work items
+// are numbered with 32 bits)
+constexpr int64_t max_groups(int block) { return ((INT64_C(1) << 32) - 1) / block; }
 bool capturing(const LaunchCtx& lc);  // lc.stream is being captured into a graph
 // descriptor array of at least `bytes` for one call that advances the device
 // epoch; fails with SKEL_E_STATE if the array would have to grow (or be

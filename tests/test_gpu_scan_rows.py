@@ -119,6 +119,23 @@ def test_scan_rows_more_rows_than_one_grid(skel, oracle_mod):
 
 
 
+def test_scan_rows_more_rows_than_one_launch_of_short_rows(skel):
+    """2^29 rows of one element at 8 lanes each are more work items than one
+    launch can number: they take two."""
+    import torch
+    rows = (1 << 29) + 3
+    x = torch.empty(rows, 1, dtype=torch.int32, device="cuda").random_(-1000, 1000)
+    y = torch.full_like(x, 7)
+    cx, cy = skel.wrap_tensor(x), skel.wrap_tensor(y)
+    skel.skel_scan_rows(cx, cy, skel.INCLUSIVE, skel.SUM, variant=SR1)
+    assert torch.equal(x, y)
+    skel.skel_scan_rows(cx, cy, skel.REVERSE_EXCLUSIVE, skel.SUM, variant=SR1)
+    assert not y.any()
+    skel.skel_sync()
+    for c in (cx, cy):
+        c.destroy()
+
+
 from hypothesis import HealthCheck, given, settings, strategies as st  # noqa: E402
 
 
