@@ -317,14 +317,14 @@ struct Cols {
 };
 constexpr int kHW = kTX + 4;  // LDS row width of a row-filtered tile (padded)
 
-// workgroup b of nb -> (tile x, tile y), in an XCD-contiguous order: the first
-// nb % 8 XCDs take one tile more than the others.  (A grid rounded up to whole
+// workgroup b of the nb that take tiles t0 .. t0 + nb - 1 -> (tile x, tile y), in an
+// XCD-contiguous order: the first nb % 8 XCDs take one tile more than the others.  (A grid rounded up to whole
 // turns of the XCDs launches up to seven idle workgroups per image: 16384 images
 // of 16 x 16, 5-point, 270 us against 37.)
-__device__ __forceinline__ void tile_coords(int64_t b, int64_t nbx, int64_t nb, int64_t& bx,
-                                            int64_t& by) {
+__device__ __forceinline__ void tile_coords(int64_t b, int64_t nbx, int64_t nb, int64_t t0,
+                                            int64_t& bx, int64_t& by) {
     const int64_t xcd = b & 7, more = nb & 7;
-    const int64_t L = xcd * (nb >> 3) + (xcd < more ? xcd : more) + (b >> 3);
+    const int64_t L = t0 + xcd * (nb >> 3) + (xcd < more ? xcd : more) + (b >> 3);
     bx = L % nbx;
     by = L / nbx;
 }
@@ -405,6 +405,7 @@ __device__ __forceinline__ void stage_tile(const float* x, int64_t rows, int64_t
 // on 24 fields of 121 x 163 and 30 on 64 of 2048^2 (5-point); beside the tiles
 // the first two cost nothing measurable, the last (own launch) 12 us.
 constexpr int kBorderG = 4;
+constexpr int64_t kMaxBorderGroups = 1 << 20;  // (they take further pixels in turns)
 constexpr int kBorderTab = (2 * SKEL_MAX_RADIUS_2D + 1) * (2 * SKEL_MAX_RADIUS_2D + 1) +
                            2 * (SKEL_MAX_RADIUS_2D + 1) * (2 * SKEL_MAX_RADIUS_2D + 1);
 
@@ -414,7 +415,7 @@ __device__ __forceinline__ int64_t border_pixels(int64_t rows, int64_t cols) {
 
 __device__ __forceinline__ void border_transposed(const float* g, float* dx, int64_t rows,
                                                   int64_t cols, const W2& w, int ry, int rx,
-                                                  float* tab) {
+                                                  int groups, float* tab) {
     const int nx = 2 * rx + 1, ny = 2 * ry + 1;
     float* lo = tab + ny * nx;
     float* hi = lo + (ry + 1) * nx;
@@ -433,61 +434,64 @@ __device__ __forceinline__ void border_transposed(const float* g, float* dx, int
         hi[q] = sh;
     }
     __syncthreads();
-    const int64_t p = ((int64_t)blockIdx.x * kBlock + threadIdx.x) / kBorderG;
     const int lg = threadIdx.x % kBorderG;
-    const bool live = p < border_pixels(rows, cols);  // (the butterfly needs every lane)
-    int64_t s = 0, t = 0;
-    const int64_t nrow = rows > 1 ? 2 : 1;
-    if (live && p < nrow * cols) {
-        s = p < cols ? 0 : rows - 1;
-        t = p < cols ? p : p - cols;
-    } else if (live) {
-        const int64_t q = p - nrow * cols;
-        s = 1 + (cols > 1 ? q >> 1 : q);
-        t = cols > 1 && (q & 1) ? cols - 1 : 0;
-    }
-    // row terms: table row k weighs input row i0 + di * k
-    const float* tr = s == 0 ? lo : s == rows - 1 ? hi : tab;
-    const int64_t i0 = s == 0 ? 0 : s == rows - 1 ? rows - 1 : s + ry;
-    const int di = s == 0 ? 1 : -1, terms = s == 0 || s == rows - 1 ? ry + 1 : ny;
-    float acc = 0.0f;
-    for (int k = live ? lg : terms; k < terms; k += kBorderG) {
-        const int64_t i = i0 + di * k;
-        if (i < 0 || i >= rows) continue;
-        const float* rk = tr + k * nx;
-        const float* gi = g + i * cols;
-        if (cols == 1) {
-            float c = 0.0f;
-            for (int b = 0; b < nx; ++b) c += rk[b];
-            acc = __builtin_fmaf(c, gi[0], acc);
-        } else if (t == 0 || t == cols - 1) {
-            // input column m from the edge, farthest first: the weights that
-            // reach the edge from it add up
-            const int dir = t == 0 ? 1 : -1;
-            const float* wm = t == 0 ? rk : rk + 2 * rx;  // weight of column m: wm[dir * (rx - m)]
-            const float* gm = gi + t;                     // column m: gm[dir * m]
-            float c = 0.0f;
-            int m = rx;
-            for (; m >= cols; --m) c += wm[dir * (rx - m)];
+    const int64_t pixels = border_pixels(rows, cols), nrow = rows > 1 ? 2 : 1;
+    constexpr int64_t kPer = kBlock / kBorderG;  // pixels per workgroup and turn
+    for (int64_t p0 = blockIdx.x * kPer; p0 < pixels; p0 += groups * kPer) {
+        const int64_t p = p0 + threadIdx.x / kBorderG;
+        const bool live = p < pixels;  // (the butterfly needs every lane)
+        int64_t s = 0, t = 0;
+        if (live && p < nrow * cols) {
+            s = p < cols ? 0 : rows - 1;
+            t = p < cols ? p : p - cols;
+        } else if (live) {
+            const int64_t q = p - nrow * cols;
+            s = 1 + (cols > 1 ? q >> 1 : q);
+            t = cols > 1 && (q & 1) ? cols - 1 : 0;
+        }
+        // row terms: table row k weighs input row i0 + di * k
+        const float* tr = s == 0 ? lo : s == rows - 1 ? hi : tab;
+        const int64_t i0 = s == 0 ? 0 : s == rows - 1 ? rows - 1 : s + ry;
+        const int di = s == 0 ? 1 : -1, terms = s == 0 || s == rows - 1 ? ry + 1 : ny;
+        float acc = 0.0f;
+        for (int k = live ? lg : terms; k < terms; k += kBorderG) {
+            const int64_t i = i0 + di * k;
+            if (i < 0 || i >= rows) continue;
+            const float* rk = tr + k * nx;
+            const float* gi = g + i * cols;
+            if (cols == 1) {
+                float c = 0.0f;
+                for (int b = 0; b < nx; ++b) c += rk[b];
+                acc = __builtin_fmaf(c, gi[0], acc);
+            } else if (t == 0 || t == cols - 1) {
+                // input column m from the edge, farthest first: the weights that
+                // reach the edge from it add up
+                const int dir = t == 0 ? 1 : -1;
+                const float* wm = t == 0 ? rk : rk + 2 * rx;  // weight of column m: wm[dir * (rx - m)]
+                const float* gm = gi + t;                     // column m: gm[dir * m]
+                float c = 0.0f;
+                int m = rx;
+                for (; m >= cols; --m) c += wm[dir * (rx - m)];
 #pragma unroll 4
-            for (; m >= 0; --m) {
-                c += wm[dir * (rx - m)];
-                acc = __builtin_fmaf(c, gm[dir * m], acc);
-            }
-        } else if (t >= rx && t + rx < cols) {
-            const float* gj = gi + t + rx;
+                for (; m >= 0; --m) {
+                    c += wm[dir * (rx - m)];
+                    acc = __builtin_fmaf(c, gm[dir * m], acc);
+                }
+            } else if (t >= rx && t + rx < cols) {
+                const float* gj = gi + t + rx;
 #pragma unroll 4
-            for (int b = 0; b < nx; ++b) acc = __builtin_fmaf(rk[b], gj[-b], acc);
-        } else {
-            for (int b = 0; b < nx; ++b) {
-                const int64_t j = t + rx - b;
-                if (j >= 0 && j < cols) acc = __builtin_fmaf(rk[b], gi[j], acc);
+                for (int b = 0; b < nx; ++b) acc = __builtin_fmaf(rk[b], gj[-b], acc);
+            } else {
+                for (int b = 0; b < nx; ++b) {
+                    const int64_t j = t + rx - b;
+                    if (j >= 0 && j < cols) acc = __builtin_fmaf(rk[b], gi[j], acc);
+                }
             }
         }
-    }
 #pragma unroll
-    for (int o = kBorderG >> 1; o > 0; o >>= 1) acc += __shfl_xor(acc, o);
-    if (live && lg == 0) dx[s * cols + t] = acc;
+        for (int o = kBorderG >> 1; o > 0; o >>= 1) acc += __shfl_xor(acc, o);
+        if (live && lg == 0) dx[s * cols + t] = acc;
+    }
 }
 
 template <int RY, int RX>
@@ -523,7 +527,7 @@ __global__ __launch_bounds__(kBlock) void ov2_border(const float* g, float* dx, 
                                                      int64_t cols, W2 w, int ry, int rx) {
     __shared__ float tab[kBorderTab];
     border_transposed(g + (int64_t)blockIdx.y * rows * cols, dx + (int64_t)blockIdx.y * rows * cols,
-                      rows, cols, w, ry, rx, tab);
+                      rows, cols, w, ry, rx, (int)gridDim.x, tab);
 }
 
 // store one 4-wide output segment of row i starting at column j (inner: leave
@@ -560,7 +564,7 @@ __device__ __forceinline__ void store4(float* out, int64_t rows, int64_t cols, i
 template <int RX, int RO>
 __global__ __launch_bounds__(kBlock) void ov2_lds(const float* x, float* out, int64_t rows,
                                                   int64_t cols, W2 w, int ry, int edge, float pad,
-                                                  int64_t nbx, int64_t nb, int nbb) {
+                                                  int64_t nbx, int64_t nb, int64_t t0, int nbb) {
     // blockIdx.y: one of several equally shaped images stored back to back
     x += (int64_t)blockIdx.y * rows * cols;
     out += (int64_t)blockIdx.y * rows * cols;
@@ -568,12 +572,13 @@ __global__ __launch_bounds__(kBlock) void ov2_lds(const float* x, float* out, in
     using CL = Cols<RX>;
     constexpr int NX = 2 * RX + 1, LW = CL::LW;
     extern __shared__ __attribute__((aligned(16))) float tin[];
-    if ((int)blockIdx.x < nbb) {
-        border_transposed(x, out, rows, cols, w, ry, RX, tin);
+    const int nbl = t0 == 0 ? nbb : 0;  // border workgroups of this launch
+    if ((int)blockIdx.x < nbl) {
+        border_transposed(x, out, rows, cols, w, ry, RX, nbl, tin);
         return;
     }
     int64_t bx, by;
-    tile_coords((int64_t)blockIdx.x - nbb, nbx, nb, bx, by);
+    tile_coords((int64_t)blockIdx.x - nbl, nbx, nb, t0, bx, by);
     const int64_t y0 = by * (16 * RO), x0 = bx * kTX;
     stage_tile<RX>(x, rows, cols, y0, x0, 16 * RO + 2 * ry, ry, edge, pad, tin);
     __syncthreads();
@@ -649,21 +654,22 @@ __device__ __forceinline__ void column_pass(const float* th, const W2& w, int ry
 template <int RX, int RO>
 __global__ __launch_bounds__(kBlock) void ov2_sep(const float* x, float* out, int64_t rows,
                                                   int64_t cols, W2 w, int ry, int edge, float pad,
-                                                  int64_t nbx, int64_t nb, int nbb) {
+                                                  int64_t nbx, int64_t nb, int64_t t0, int nbb) {
     // blockIdx.y: one of several equally shaped images stored back to back
     x += (int64_t)blockIdx.y * rows * cols;
     out += (int64_t)blockIdx.y * rows * cols;
     using CL = Cols<RX>;
     constexpr int LW = CL::LW;
     extern __shared__ __attribute__((aligned(16))) float tin[];
-    if ((int)blockIdx.x < nbb) {
-        border_transposed(x, out, rows, cols, w, ry, RX, tin);
+    const int nbl = t0 == 0 ? nbb : 0;  // border workgroups of this launch
+    if ((int)blockIdx.x < nbl) {
+        border_transposed(x, out, rows, cols, w, ry, RX, nbl, tin);
         return;
     }
     const int nrows = 16 * RO + 2 * ry;
     float* th = tin + nrows * LW;
     int64_t bx, by;
-    tile_coords((int64_t)blockIdx.x - nbb, nbx, nb, bx, by);
+    tile_coords((int64_t)blockIdx.x - nbl, nbx, nb, t0, bx, by);
     const int64_t y0 = by * (16 * RO), x0 = bx * kTX;
     stage_tile<RX>(x, rows, cols, y0, x0, nrows, ry, edge, pad, tin);
     __syncthreads();
@@ -708,19 +714,20 @@ template <int RX, int RO>
 // leave seven; 8192^2 9 x 9, map and transpose, 230 -> 225 us)
 __global__ __launch_bounds__(kBlock, RX <= 4 ? 8 : 1) void ov2_sep_l1(const float* x, float* out, int64_t rows,
                                                      int64_t cols, W2 w, int ry, int edge,
-                                                     float pad, int64_t nbx, int64_t nb, int nbb) {
+                                                     float pad, int64_t nbx, int64_t nb, int64_t t0, int nbb) {
     // blockIdx.y: one of several equally shaped images stored back to back
     x += (int64_t)blockIdx.y * rows * cols;
     out += (int64_t)blockIdx.y * rows * cols;
     using CL = Cols<RX>;
     constexpr int HX = CL::HX, NV = CL::NV;
     extern __shared__ __attribute__((aligned(16))) float th[];
-    if ((int)blockIdx.x < nbb) {
-        border_transposed(x, out, rows, cols, w, ry, RX, th);
+    const int nbl = t0 == 0 ? nbb : 0;  // border workgroups of this launch
+    if ((int)blockIdx.x < nbl) {
+        border_transposed(x, out, rows, cols, w, ry, RX, nbl, th);
         return;
     }
     int64_t bx, by;
-    tile_coords((int64_t)blockIdx.x - nbb, nbx, nb, bx, by);
+    tile_coords((int64_t)blockIdx.x - nbl, nbx, nb, t0, bx, by);
     const int64_t y0 = by * (16 * RO), x0 = bx * kTX;
     const int nrows = 16 * RO + 2 * ry;
     const bool interior = y0 - ry >= 0 && y0 - ry + nrows <= rows && x0 - HX >= 0 &&
@@ -1098,8 +1105,13 @@ void tile_launch(K kern, int ro, size_t bytes_per_row, const Call2& c) {
     const int64_t nbx = div_up(c.cols, kTX), nb = nbx * div_up(c.rows, 16 * ro);
     size_t lds = (16 * ro + 2 * c.ry) * bytes_per_row;
     if (c.nbb) lds = std::max(lds, kBorderTab * sizeof(float));
-    kern<<<dim3((unsigned)(nb + c.nbb), c.fields), kBlock, lds, c.st>>>(
-        c.x, c.out, c.rows, c.cols, c.w, c.ry, c.edge, c.pad, nbx, nb, c.nbb);
+    // (one launch, but for an image of more tiles than a launch has workgroups)
+    const int64_t most = (max_groups(kBlock) - c.nbb) / 8 * 8;
+    for (int64_t t0 = 0; t0 < nb; t0 += most) {
+        const int64_t here = std::min(nb - t0, most);
+        kern<<<dim3((unsigned)(here + (t0 == 0 ? c.nbb : 0)), c.fields), kBlock, lds, c.st>>>(
+            c.x, c.out, c.rows, c.cols, c.w, c.ry, c.edge, c.pad, nbx, here, t0, c.nbb);
+    }
 }
 
 // Rows per lane (a tile has 16 times as many).  One row per lane keeps more
@@ -1277,8 +1289,10 @@ skel_status launch_overlap2d_transposed(const float* g, float* dx, int64_t rows,
     }
     int nbb = 0;
     if (edge == SKEL_EDGE_CLAMP && !self)
-        nbb = (int)div_up(((rows > 1 ? 2 : 1) * cols +
-                           (cols > 1 ? 2 : 1) * (rows > 2 ? rows - 2 : 0)) * kBorderG, kBlock);
+        nbb = (int)std::min(div_up(((rows > 1 ? 2 : 1) * cols +
+                                    (cols > 1 ? 2 : 1) * (rows > 2 ? rows - 2 : 0)) * kBorderG,
+                                   kBlock),
+                            kMaxBorderGroups);
     const Call2 c{g, dx, rows, cols, 0, wk, !w2d, ry, rx,
                   edge == SKEL_EDGE_CYCLIC || self ? edge : SKEL_EDGE_CONST, 0.0f, nbb,
                   lc.dev->cus, lc.stream};

@@ -89,6 +89,38 @@ def test_fields_of_few_tiles(skel, oracle_mod, edge, r):
     skel.skel_sync()
 
 
+@pytest.mark.parametrize("edge", list(EDGES))
+def test_image_of_more_tiles_than_one_launch(skel, edge):
+    """A column of 2^29 + 37 pixels: its tiles and, clamped, the transpose's border
+    are more work items than one launch can number.  Weights are eighths and pixels
+    small integers, so that every sum is exact."""
+    import torch
+    n = (1 << 29) + 37
+    w = np.array([[1, 2, 0], [3, 1, 2], [2, 0, 5]], np.float32) / 8
+    x = torch.empty(n, 1, device="cuda").random_(-8, 9)
+    y = torch.empty_like(x)
+    cx, cy = skel.wrap_tensor(x), skel.wrap_tensor(y)
+    # one column: with a border rule that reads it back, a row's weights add up
+    a = (w[:, 1] if edge == "const" else w.sum(1)).astype(float)
+    up, down = torch.roll(x, 1, 0), torch.roll(x, -1, 0)  # x[i - 1], x[i + 1]
+    if edge != "cyclic":
+        up[0] = x[0] if edge == "clamp" else 0
+        down[-1] = x[-1] if edge == "clamp" else 0
+    skel.skel_mapoverlap2d_fields(cx, cy, 1, w2d=w, edge=EDGES[edge], pad=0.0)
+    assert torch.equal(y, a[0] * up + a[1] * x + a[2] * down)
+    skel.skel_mapoverlap2d_fields_backward(cx, cy, 1, w2d=w, edge=EDGES[edge])
+    if edge != "cyclic":
+        up[0] = down[-1] = 0
+    want = a[2] * up + a[1] * x + a[0] * down
+    if edge == "clamp":
+        want[0] += a[0] * x[0]
+        want[-1] += a[2] * x[-1]
+    assert torch.equal(y, want)
+    skel.skel_sync()
+    for c in (cx, cy):
+        c.destroy()
+
+
 def test_fields_beyond_one_launch(skel, oracle_mod):
     # more fields than one launch's grid holds (65535): the launcher splits them
     f, h, wd = 70001, 2, 4
