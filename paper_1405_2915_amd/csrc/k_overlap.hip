@@ -127,6 +127,23 @@ struct Ends1 {
     float lo[SKEL_MAX_RADIUS_1D + 1], hi[SKEL_MAX_RADIUS_1D + 1];
 };
 
+// The same element by element: first + step * lane of 0 or, HI, n - 1, from x
+// as x(i).  The prefix sums give the same result up to rounding, but for infinite
+// and NaN inputs, which must meet each weight (a sum of weights may be zero or
+// have another sign): a non-finite result is computed again from these terms.
+template <bool HI, class X>
+__device__ __forceinline__ float end_terms(const W1& w, int r, int64_t n, X x, int first, int step) {
+    float p = 0.0f;
+    for (int k = first; k <= 2 * r; k += step) {
+        // w is reversed: the forward tap 2r - k reads element i + r - k
+        const int reach = HI ? r - k : k - r;  // farthest output that reads the end through it
+        for (int64_t m = 0; m <= reach && m < n; ++m)
+            p = __builtin_fmaf(w.w[k], x(HI ? n - 1 - m : m), p);
+        if (n == 1 && reach < 0) p = __builtin_fmaf(w.w[k], x(0), p);
+    }
+    return p;
+}
+
 // O1b.  A workgroup of NT lanes stages the inputs of its 4 * NT outputs in LDS;
 // a lane owns four consecutive outputs and slides a window of eight inputs
 // along the taps: per four taps one 16-byte LDS read feeds sixteen
@@ -187,6 +204,9 @@ __global__ __launch_bounds__(NT) void ov1_window(const float* x, float* out, int
             float p = 0.0f;
             for (int i = l; i <= reach; i += dev::kWave) p = __builtin_fmaf(ends.lo[i], s[r + i], p);
             p = dev::wave_reduce<dev::Comb<float, SKEL_SUM>>(p);
+            if (!__builtin_isfinite(p))
+                p = dev::wave_reduce<dev::Comb<float, SKEL_SUM>>(end_terms<false>(
+                    w, r, n, [&](int64_t i) { return s[r + (int)i]; }, l, dev::kWave));
             if (l == 0) acc[0] = p;
         }
         const int64_t e = n - 1 - base;  // the last element, if this tile holds it
@@ -195,6 +215,9 @@ __global__ __launch_bounds__(NT) void ov1_window(const float* x, float* out, int
             for (int m = l; m <= reach; m += dev::kWave)
                 p = __builtin_fmaf(ends.hi[m], s[(int)e + r - m], p);
             p = dev::wave_reduce<dev::Comb<float, SKEL_SUM>>(p);
+            if (!__builtin_isfinite(p))
+                p = dev::wave_reduce<dev::Comb<float, SKEL_SUM>>(end_terms<true>(
+                    w, r, n, [&](int64_t i) { return s[(int)(i - base) + r]; }, l, dev::kWave));
 #pragma unroll
             for (int c = 0; c < 4; ++c)
                 if (4 * tid + c == (int)e) acc[c] = p;
@@ -287,6 +310,11 @@ __global__ __launch_bounds__(kBlock) void ov1_shfl(const float* x, float* out, i
                         for (int m = 0; m <= r && m < n; ++m)
                             acc = i == 0 ? __builtin_fmaf(ends.lo[m], x[m], acc)
                                          : __builtin_fmaf(ends.hi[m], x[n - 1 - m], acc);
+                        if (!__builtin_isfinite(acc)) {
+                            const auto at = [&](int64_t e) { return x[e]; };
+                            acc = i == 0 ? end_terms<false>(w, r, n, at, 0, 1)
+                                         : end_terms<true>(w, r, n, at, 0, 1);
+                        }
                     }
                 }
                 out[i] = acc;
@@ -317,16 +345,21 @@ struct Cols {
 };
 constexpr int kHW = kTX + 4;  // LDS row width of a row-filtered tile (padded)
 
-// workgroup b of the nb that take tiles t0 .. t0 + nb - 1 -> (tile x, tile y), in an
-// XCD-contiguous order: the first nb % 8 XCDs take one tile more than the others.  (A grid rounded up to whole
-// turns of the XCDs launches up to seven idle workgroups per image: 16384 images
-// of 16 x 16, 5-point, 270 us against 37.)
-__device__ __forceinline__ void tile_coords(int64_t b, int64_t nbx, int64_t nb, int64_t t0,
+// workgroup b of the nb that take tiles t0 .. t0 + nb - 1 -> (tile x, tile y), in
+// an XCD-contiguous order: the first nb % 8 XCDs take one tile more than the
+// others.  (A grid rounded up to whole turns of the XCDs launches up to seven
+// idle workgroups per image: 16384 images of 16 x 16, 5-point, 270 us against 37.)
+__device__ __forceinline__ void tile_coords(uint32_t b, int64_t nbx, uint32_t nb, int64_t t0,
                                             int64_t& bx, int64_t& by) {
-    const int64_t xcd = b & 7, more = nb & 7;
-    const int64_t L = t0 + xcd * (nb >> 3) + (xcd < more ? xcd : more) + (b >> 3);
-    bx = L % nbx;
-    by = L / nbx;
+    const uint32_t xcd = b & 7, more = nb & 7;
+    const uint32_t L = xcd * (nb >> 3) + (xcd < more ? xcd : more) + (b >> 3);
+    if (t0 == 0) {  // (a 64-bit division would cost every workgroup its start)
+        by = L / (uint32_t)nbx;
+        bx = L - (uint32_t)by * (uint32_t)nbx;
+    } else {
+        by = (t0 + L) / nbx;
+        bx = t0 + L - by * nbx;
+    }
 }
 
 // four consecutive columns starting at j of row rp, through the column rule
@@ -413,6 +446,15 @@ __device__ __forceinline__ int64_t border_pixels(int64_t rows, int64_t cols) {
     return (rows > 1 ? 2 : 1) * cols + (cols > 1 ? 2 : 1) * (rows > 2 ? rows - 2 : 0);
 }
 
+// outputs along an axis of len elements whose tap a (radius r) reads element s
+// under CLAMP: lo .. hi
+__device__ __forceinline__ void clamped_reads(int64_t s, int a, int r, int64_t len, int64_t& lo,
+                                              int64_t& hi) {
+    const int64_t i = s - a + r;
+    lo = s == 0 || i < 0 ? 0 : i;
+    hi = s == len - 1 || i > len - 1 ? len - 1 : i;
+}
+
 __device__ __forceinline__ void border_transposed(const float* g, float* dx, int64_t rows,
                                                   int64_t cols, const W2& w, int ry, int rx,
                                                   int groups, float* tab) {
@@ -490,6 +532,20 @@ __device__ __forceinline__ void border_transposed(const float* g, float* dx, int
         }
 #pragma unroll
         for (int o = kBorderG >> 1; o > 0; o >>= 1) acc += __shfl_xor(acc, o);
+        // an infinity or a NaN must meet each weight, not their sums (which may be
+        // zero or of another sign): such a pixel is gathered tap by tap
+        if (live && lg == 0 && !__builtin_isfinite(acc)) {
+            acc = 0.0f;
+            for (int q = 0; q <= lastw; ++q) {
+                const int a = q / nx, b = q - a * nx;
+                int64_t ilo, ihi, jlo, jhi;
+                clamped_reads(s, a, ry, rows, ilo, ihi);
+                clamped_reads(t, b, rx, cols, jlo, jhi);
+                for (int64_t i = ilo; i <= ihi; ++i)
+                    for (int64_t j = jlo; j <= jhi; ++j)
+                        acc = __builtin_fmaf(tab[q], g[i * cols + j], acc);
+            }
+        }
         if (live && lg == 0) dx[s * cols + t] = acc;
     }
 }
@@ -578,7 +634,7 @@ __global__ __launch_bounds__(kBlock) void ov2_lds(const float* x, float* out, in
         return;
     }
     int64_t bx, by;
-    tile_coords((int64_t)blockIdx.x - nbl, nbx, nb, t0, bx, by);
+    tile_coords(blockIdx.x - nbl, nbx, (uint32_t)nb, t0, bx, by);
     const int64_t y0 = by * (16 * RO), x0 = bx * kTX;
     stage_tile<RX>(x, rows, cols, y0, x0, 16 * RO + 2 * ry, ry, edge, pad, tin);
     __syncthreads();
@@ -669,7 +725,7 @@ __global__ __launch_bounds__(kBlock) void ov2_sep(const float* x, float* out, in
     const int nrows = 16 * RO + 2 * ry;
     float* th = tin + nrows * LW;
     int64_t bx, by;
-    tile_coords((int64_t)blockIdx.x - nbl, nbx, nb, t0, bx, by);
+    tile_coords(blockIdx.x - nbl, nbx, (uint32_t)nb, t0, bx, by);
     const int64_t y0 = by * (16 * RO), x0 = bx * kTX;
     stage_tile<RX>(x, rows, cols, y0, x0, nrows, ry, edge, pad, tin);
     __syncthreads();
@@ -727,7 +783,7 @@ __global__ __launch_bounds__(kBlock, RX <= 4 ? 8 : 1) void ov2_sep_l1(const floa
         return;
     }
     int64_t bx, by;
-    tile_coords((int64_t)blockIdx.x - nbl, nbx, nb, t0, bx, by);
+    tile_coords(blockIdx.x - nbl, nbx, (uint32_t)nb, t0, bx, by);
     const int64_t y0 = by * (16 * RO), x0 = bx * kTX;
     const int nrows = 16 * RO + 2 * ry;
     const bool interior = y0 - ry >= 0 && y0 - ry + nrows <= rows && x0 - HX >= 0 &&

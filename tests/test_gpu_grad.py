@@ -241,6 +241,55 @@ def test_mapoverlap2d_backward_large(skel, oracle_mod, edge, ry, rx):
 
 
 # ----------------------------------------------------------- autograd layer
+def same_class(got, ref):
+    """Where got and ref differ in kind: NaN, +inf, -inf or finite."""
+    kind = lambda a: np.where(np.isnan(a), 3, np.where(np.isinf(a), np.sign(a), 0))  # noqa: E731
+    return np.argwhere(kind(got) != kind(ref))
+
+
+# weights whose sums towards an end vanish, change sign or meet a zero weight
+CANCELLING = {2: [1, -1, 2, 1, -1], 3: [0, 2, -2, 1, 0, 3, -3], 7: [2, -3] * 7 + [0]}
+
+
+@pytest.mark.parametrize("r", list(CANCELLING))
+def test_mapoverlap1d_backward_non_finite(skel, oracle_mod, r):
+    """An infinity or a NaN next to a clamped end meets every weight by itself."""
+    w = np.array(CANCELLING[r], np.float32)
+    for n in (1, 2, 5, 300, 1025, 140000):
+        for at in {0, min(1, n - 1), max(0, n - 2), n - 1, min(r, n - 1)}:
+            for bad in (np.inf, -np.inf, np.nan):
+                g = si.uniform_f32(n, 0.5, 1.0, 9, 60 + r)
+                g[at] = bad
+                ref, _ = oracle_mod.mapoverlap1d_adjoint(g, w, r, "clamp")
+                for v in range(skel.skel_variant_count(skel.SK_MAPOVERLAP1D_BACKWARD)):
+                    out = skel.Container.empty(skel.F32, n)
+                    skel.skel_mapoverlap1d_backward(cont(skel, g), out, w, r, 0, variant=v)
+                    off = same_class(out.to_numpy(), ref)
+                    assert not off.size, (r, n, at, bad, v, off[:5])
+
+
+@pytest.mark.parametrize("sep", [False, True])
+@pytest.mark.parametrize("ry,rx", [(1, 1), (2, 3), (5, 2)])
+def test_mapoverlap2d_backward_non_finite(skel, oracle_mod, ry, rx, sep):
+    wy = np.array((CANCELLING[7] * 2)[:2 * ry + 1], np.float32)
+    wx = np.array((CANCELLING[3] * 2)[1:2 * rx + 2], np.float32)
+    kw = {"wy": wy, "wx": wx} if sep else {"w2d": np.outer(wy, wx).astype(np.float32)}
+    # (whole strips of 256 columns in images of 8 rows and fewer also reach the marching
+    # form, whose border runs in a launch of its own)
+    for h, wd in ((1, 1), (1, 9), (9, 1), (3, 4), (20, 70), (4, 1 << 18)):
+        for i, j in {(0, 0), (0, wd // 2), (h - 1, wd - 1), (h // 2, 0), (h - 1, min(1, wd - 1))}:
+            for bad in (np.inf, np.nan):
+                g = si.uniform_f32(h * wd, 0.5, 1.0, 9, 70).reshape(h, wd)
+                g[i, j] = bad
+                ref, _ = oracle_mod.mapoverlap2d_adjoint(g, ry, rx, edge="clamp", **kw)
+                for v in range(skel.skel_variant_count(skel.SK_MAPOVERLAP2D_BACKWARD)):
+                    out = skel.Container.empty(skel.F32, h, wd)
+                    skel.skel_mapoverlap2d_backward(cont(skel, g), out, ry=ry, rx=rx, edge=0,
+                                                    variant=v, **kw)
+                    off = same_class(out.to_numpy().reshape(h, wd), ref)
+                    assert not off.size, (ry, rx, sep, (h, wd), (i, j), bad, v, off[:5])
+
+
 def test_autograd_functions(skel, oracle_mod):
     import torch
 
