@@ -102,12 +102,15 @@ SCAN_STRESS_LIB = os.path.join(PKG, "libskel_scan_w2.so")
 def build_scan_stress(verbose: bool = False) -> str:
     """libskel_scan_w2.so: the library with the scan tiles shrunk to two
     wavefronts (4096 elements for 4-byte inputs instead of 32768), eight times
-    as many tiles and a deeper decoupled look-back, for the look-back stress
-    test.  The other objects are those of the product build."""
-    obj = os.path.join(BUILD, "k_scan.hip.w2.o")
-    _run([HIPCC] + HIP_FLAGS + ["-DSKEL_SCAN_WAVES=2", "-x", "hip", "-c",
-                                os.path.join(CSRC, "k_scan.hip"), "-o", obj], verbose)
-    objs = [os.path.join(BUILD, s + ".o") for s in HIP_SOURCES if s != "k_scan.hip"] + [obj]
+    as many tiles and a deeper decoupled look-back, and with flat tiles that
+    wait for one poll only before they compute the totals they miss, for the
+    stress tests of both.  The other objects are those of the product build."""
+    flags = ["-DSKEL_SCAN_WAVES=2", "-DSKEL_FLAT_PATIENCE=1"]
+    own = {s: os.path.join(BUILD, s + ".w2.o") for s in ("k_scan.hip", "k_scan_rows.hip")}
+    with cf.ThreadPoolExecutor(max_workers=len(own)) as ex:
+        list(ex.map(lambda s: _run([HIPCC] + HIP_FLAGS + flags + [
+            "-x", "hip", "-c", os.path.join(CSRC, s), "-o", own[s]], verbose), own))
+    objs = [own.get(s, os.path.join(BUILD, s + ".o")) for s in HIP_SOURCES]
     tmp = SCAN_STRESS_LIB + ".tmp"
     _run([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", tmp] + objs, verbose)
     os.replace(tmp, SCAN_STRESS_LIB)

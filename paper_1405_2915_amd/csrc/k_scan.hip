@@ -175,49 +175,19 @@ __global__ __launch_bounds__(P::kBlock) void scan_lookback_persist(
     }
 }
 
-template <class P, bool FULL, bool REV>
-__device__ __forceinline__ void flat_tile(const typename P::in_t* in, typename P::out_t* out,
-                                          int64_t n, int64_t seq, int64_t tile, int64_t ntiles,
-                                          int exclusive, u64* status, u64* sync) {
-    using acc_t = typename P::acc_t;
-    using C = typename P::C;
-    __shared__ acc_t s_wtot[P::NW];
-    __shared__ acc_t s_red[P::NW];
-    __shared__ acc_t s_prefix;
-    __shared__ uint32_t s_epoch;
-    uint32_t ep = 0;
-    if (threadIdx.x == 0) ep = epoch_of_call(sync);  // in flight with the tile's loads
-    Raw<P> raw;
-    tile_load<P, FULL, true>(in, n, tile, raw);
-    acc_t wex, agg;
-    tile_totals<P, REV>(lane_total<P, FULL>(n, tile, raw), s_wtot, &wex, &agg);
-    if (threadIdx.x == 0) {
-        s_epoch = ep;
-        if (seq + 1 < ntiles) publish(status, seq, ST_AGG, agg, ep);
-    }
-    __syncthreads();
-    const acc_t part = flat_prefix<P>(status, seq, s_epoch, sync + SYNC_ERROR);
-    const acc_t pre = block_reduce<C>(part, s_red);
-    if (threadIdx.x == 0) {
-        s_prefix = pre;
-        if (seq == ntiles - 1) epoch_advance(sync);
-    }
-    __syncthreads();
-    keep_raw_only<P>(raw);
-    tile_scan_store<P, FULL, REV>(out, n, tile, raw, C::op(s_prefix, wex), exclusive != 0);
-}
-
-template <class P, bool REV>
-__global__ __launch_bounds__(P::kBlock) void scan_flat(const typename P::in_t* in,
-                                                       typename P::out_t* out, int64_t n,
-                                                       int64_t ntiles, int exclusive,
-                                                       u64* status, u64* sync) {
+template <class P, bool REV, bool RESCUE>
+__global__ __launch_bounds__(P::kBlock, flat_waves<P>()) void scan_flat(
+    const typename P::in_t* in, typename P::out_t* out, int64_t n, int64_t ntiles, int exclusive,
+    u64* status, u64* sync) {
     const int64_t seq = blockIdx.x;
     const int64_t tile = REV ? ntiles - 1 - seq : seq;  // data tile in scan order
+    const bool last = seq == ntiles - 1;
     if ((tile + 1) * P::kTile <= n)
-        flat_tile<P, true, REV>(in, out, n, seq, tile, ntiles, exclusive, status, sync);
+        flat_tile<P, true, REV, RESCUE, false>(in, out, n, seq, tile, ntiles, exclusive, status,
+                                               sync, last, status, ntiles - 1);
     else
-        flat_tile<P, false, REV>(in, out, n, seq, tile, ntiles, exclusive, status, sync);
+        flat_tile<P, false, REV, RESCUE, false>(in, out, n, seq, tile, ntiles, exclusive, status,
+                                                sync, last, status, ntiles - 1);
 }
 
 // S1 pass 1: tile totals
@@ -352,6 +322,10 @@ skel_status scan_typed(int v, int kind, const void* x, void* y, int64_t n, Launc
     const bool rev = kind == SKEL_REVERSE_INCLUSIVE || kind == SKEL_REVERSE_EXCLUSIVE;
     const int excl = (kind == SKEL_EXCLUSIVE || kind == SKEL_REVERSE_EXCLUSIVE) ? 1 : 0;
     hipStream_t st = lc.stream;
+    // the output leaves the input in place: a flat tile may read it again
+    const uintptr_t x0 = reinterpret_cast<uintptr_t>(x), y0 = reinterpret_cast<uintptr_t>(y);
+    const bool apart = x0 + (uintptr_t)n * sizeof(in_t) <= y0 ||
+                       y0 + (uintptr_t)n * sizeof(out_t) <= x0;
     if (rev && v != S2_LOOKBACK && v != S3_PERSISTENT_LOOKBACK && v != S4_SMALL_TILE_LOOKBACK &&
         v != S5_FLAT_LOOKBACK)
         return fail(SKEL_E_UNSUPPORTED, "reverse scans run in the single-pass variants only");
@@ -365,12 +339,18 @@ skel_status scan_typed(int v, int kind, const void* x, void* y, int64_t n, Launc
         void* status = nullptr;
         skel_status e = ws_status(lc, (size_t)nts * 16, &status);
         if (e != SKEL_OK) return e;
-        if (rev)
-            scan_flat<PS, true><<<(unsigned)nts, PS::kBlock, 0, st>>>(
-                in, out, n, nts, excl, static_cast<u64*>(status), lc.ws->sync);
-        else
-            scan_flat<PS, false><<<(unsigned)nts, PS::kBlock, 0, st>>>(
-                in, out, n, nts, excl, static_cast<u64*>(status), lc.ws->sync);
+        // up to an eighth of the device's slots the tiles of several launches on as
+        // many streams are resident together (HIP runs four queues at once), and
+        // every wait ends without the means to compute a missing total (5.3 us
+        // with them at 2^20 elements, 5.2 without)
+        const auto plain = rev ? scan_flat<PS, true, false> : scan_flat<PS, false, false>;
+        const bool few =
+            8 * nts <= resident_slots(reinterpret_cast<const void*>(plain), PS::kBlock, lc);
+        const auto kern = few || !apart ? plain
+                          : rev         ? scan_flat<PS, true, true>
+                                        : scan_flat<PS, false, true>;
+        kern<<<(unsigned)nts, PS::kBlock, 0, st>>>(in, out, n, nts, excl,
+                                                   static_cast<u64*>(status), lc.ws->sync);
         return launch_check("scan_flat");
     }
     if (v == S4_SMALL_TILE_LOOKBACK) {
@@ -398,12 +378,13 @@ skel_status scan_typed(int v, int kind, const void* x, void* y, int64_t n, Launc
         return reduce_then_scan<P>(in, out, n, excl, static_cast<acc_t*>(mem), st);
     }
     case S3_PERSISTENT_LOOKBACK: {
-        // middle sizes: flat, while the device holds every tile at once (so that
-        // a tile waits only on tiles that are running); 8192 elements per tile
+        // middle sizes: flat, while the device holds every tile at once; 8192
+        // elements per tile.  (In place the tiles below, whose ids from a counter
+        // make every wait end without reading the input again.)
         using PM = SP<DIN, DOUT, OP, DIN == SKEL_I64 ? 8 : 4>;
-        const auto flat = rev ? scan_flat<PM, true> : scan_flat<PM, false>;
+        const auto flat = rev ? scan_flat<PM, true, true> : scan_flat<PM, false, true>;
         const int64_t ntm = (n + PM::kTile - 1) / PM::kTile;
-        const bool mid = ntm <= kFlatMaxTiles &&
+        const bool mid = apart && ntm <= kFlatMaxTiles &&
                          ntm <= resident_slots(reinterpret_cast<const void*>(flat), PM::kBlock, lc);
         void* status = nullptr;
         skel_status e = ws_status(lc, (size_t)(mid ? ntm : ntiles) * 16, &status);

@@ -151,57 +151,25 @@ __global__ __launch_bounds__(kShortBlock) void scan_rows_short(const typename P:
 }
 
 // Flat look-back within each row: tile seq = row * tpr + t (t in scan order)
-// publishes its total and reads those of the t tiles before it in its row.  All
-// tiles are resident at once (the launcher checks), so every wait ends.  The last
-// workgroup advances the epoch once it has seen every tile's total: by then every
-// tile has read this call's epoch.
-template <class P, bool FULL, bool REV>
-__device__ __forceinline__ void flat_row_tile(const typename P::in_t* src, typename P::out_t* dst,
-                                              int64_t cols, int64_t first, int64_t t, int64_t tile,
-                                              int exclusive, u64* status, u64* sync) {
-    using acc_t = typename P::acc_t;
-    using C = typename P::C;
-    __shared__ acc_t s_wtot[P::NW];
-    __shared__ acc_t s_red[P::NW];
-    __shared__ acc_t s_prefix;
-    __shared__ uint32_t s_epoch;
-    uint32_t ep = 0;
-    if (threadIdx.x == 0) ep = epoch_of_call(sync);  // in flight with the tile's loads
-    Raw<P> raw;
-    tile_load<P, FULL, true>(src, cols, tile, raw);
-    acc_t wex, agg;
-    tile_totals<P, REV>(lane_total<P, FULL>(cols, tile, raw), s_wtot, &wex, &agg);
-    if (threadIdx.x == 0) {
-        s_epoch = ep;
-        publish(status, first + t, ST_AGG, agg, ep);
-    }
-    __syncthreads();
-    const acc_t pre = block_reduce<C>(
-        flat_prefix<P>(status + 2 * first, t, s_epoch, sync + SYNC_ERROR), s_red);
-    if (threadIdx.x == 0) s_prefix = pre;
-    __syncthreads();
-    keep_raw_only<P>(raw);
-    tile_scan_store<P, FULL, REV>(dst, cols, tile, raw, C::op(s_prefix, wex), exclusive != 0);
-    if (blockIdx.x == gridDim.x - 1) {
-        flat_prefix<P>(status, (int64_t)gridDim.x - 1, s_epoch, sync + SYNC_ERROR);
-        __syncthreads();
-        if (threadIdx.x == 0) epoch_advance(sync);
-    }
-}
-
+// publishes its total and reads those of the t tiles before it in its row.  The
+// last workgroup, which advances the epoch, waits for every tile's total.
 template <class P, bool REV>
-__global__ __launch_bounds__(P::kBlock) void scan_rows_flat(const typename P::in_t* in,
-                                                            typename P::out_t* out, int64_t cols,
-                                                            int64_t tpr, int exclusive,
-                                                            u64* status, u64* sync) {
+__global__ __launch_bounds__(P::kBlock, flat_waves<P>()) void scan_rows_flat(
+    const typename P::in_t* in, typename P::out_t* out, int64_t cols, int64_t tpr, int exclusive,
+    u64* status, u64* sync) {
     const int64_t row = (int64_t)blockIdx.x / tpr, t = (int64_t)blockIdx.x - row * tpr;
     const int64_t tile = REV ? tpr - 1 - t : t;
     const typename P::in_t* src = in + row * cols;
     typename P::out_t* dst = out + row * cols;
+    const bool last = blockIdx.x == gridDim.x - 1;
+    u64* const mine = status + 2 * row * tpr;
+    const int64_t all = (int64_t)gridDim.x - 1;
     if ((tile + 1) * P::kTile <= cols)
-        flat_row_tile<P, true, REV>(src, dst, cols, row * tpr, t, tile, exclusive, status, sync);
+        flat_tile<P, true, REV, true, true>(src, dst, cols, t, tile, tpr, exclusive, mine, sync,
+                                            last, status, all);
     else
-        flat_row_tile<P, false, REV>(src, dst, cols, row * tpr, t, tile, exclusive, status, sync);
+        flat_tile<P, false, REV, true, true>(src, dst, cols, t, tile, tpr, exclusive, mine, sync,
+                                             last, status, all);
 }
 
 // Tiles with the decoupled look-back within each row (tpr > 1), numbered by an
@@ -344,26 +312,32 @@ skel_status scan_rows_typed(const RowsCall& c, LaunchCtx& lc) {
         return SKEL_OK;
     }
     if (c.rows < kFewRows && c.cols > kLongRow) {
+        bool done = false;
+        skel_status e = SKEL_OK;
         const int64_t tpr = (c.cols + PS::kTile - 1) / PS::kTile;
         const auto flat = c.rev ? scan_rows_flat<PS, true> : scan_rows_flat<PS, false>;
-        if (c.rows * tpr <= kFlatMaxTiles &&
-            c.rows * tpr <= resident_slots(reinterpret_cast<const void*>(flat), PS::kBlock, lc)) {
+        const char *x0 = static_cast<const char*>(c.x), *y0 = static_cast<const char*>(c.y);
+        const int64_t n = c.rows * c.cols;
+        const bool apart = x0 + n * sizeof(typename PS::in_t) <= y0 ||
+                           y0 + n * sizeof(typename PS::out_t) <= x0;
+        if (apart && c.rows * tpr <= kFlatMaxTiles &&
+            c.rows * tpr <=
+                resident_slots(reinterpret_cast<const void*>(flat), PS::kBlock, lc)) {
             void* status = nullptr;
-            const skel_status e = tile_status(lc, c.rows * tpr, &status);
-            if (e != SKEL_OK) return e;
-            if (status) {
+            e = tile_status(lc, c.rows * tpr, &status);
+            if (e == SKEL_OK && status) {
                 flat<<<(unsigned)(c.rows * tpr), PS::kBlock, 0, lc.stream>>>(
                     static_cast<const typename PS::in_t*>(c.x),
                     static_cast<typename PS::out_t*>(c.y), c.cols, tpr, c.excl,
                     static_cast<u64*>(status), lc.ws->sync);
-                return launch_check("scan_rows_flat");
+                done = true;
+                e = launch_check("scan_rows_flat");
             }
         } else {
-            bool done = false;
-            const skel_status e = c.cols <= PM::kTile ? run_tiles<PM>(c, lc, &done)
-                                                      : run_tiles<PL>(c, lc, &done);
-            if (e != SKEL_OK || done) return e;
+            e = c.cols <= PM::kTile ? run_tiles<PM>(c, lc, &done)
+                                    : run_tiles<PL>(c, lc, &done);
         }
+        if (e != SKEL_OK || done) return e;
     }
     if (c.cols <= 256) return run_wave<DIN, DOUT, OP, 1>(c, lc);
     if (c.cols <= 512) return run_wave<DIN, DOUT, OP, 2>(c, lc);

@@ -14,6 +14,12 @@ namespace dev {
 
 constexpr uint32_t kSpinLimit = 1u << 22;
 constexpr int kFlatPerLane = 8;  // S5: descriptors each lane reads per round
+// polls (about 1 us each) before a flat tile computes the totals it still misses
+// itself; a test build sets it to 1
+#ifndef SKEL_FLAT_PATIENCE
+#define SKEL_FLAT_PATIENCE 1024
+#endif
+constexpr uint32_t kFlatPatience = SKEL_FLAT_PATIENCE;
 
 // ALIGNED: the data starts 16-byte aligned; otherwise (rows of a matrix) its
 // vectors are accessed at element alignment, by the same instructions
@@ -250,19 +256,66 @@ __device__ typename P::acc_t lookback(u64* status, int64_t tile, typename P::acc
     return excl;
 }
 
-// S5: flat look-back.  The tile is the workgroup index: workgroups start in
-// index order, so every tile waited on has already started (and with at most
-// kFlatMaxTiles small tiles all of them are resident at once).  Each tile
-// publishes its total, then every lane of the workgroup reads its share of the
-// totals of all preceding tiles -- one round of parallel loads, re-reading only
-// those not yet valid -- and the workgroup combines them.  A tile so waits for
-// one publish-to-read latency, not for a chain of prefixes, and takes no
-// ticket from an atomic counter (device-scope atomics on one word serialise).
-// The last tile in scan order advances the epoch once it has seen every other
-// tile's total: by then every tile has read this call's epoch.
-template <class P>
+// Flat look-back (S5, S3's middle sizes, row scans).  The tile is the workgroup
+// index.  Each tile publishes its total, then every lane of the workgroup reads
+// its share of the totals of all preceding tiles -- one round of parallel loads,
+// re-reading only those not yet valid -- and the workgroup combines them.  A tile
+// so waits for one publish-to-read latency, not for a chain of prefixes, and takes
+// no ticket from an atomic counter (device-scope atomics on one word serialise, 12 ns
+// each: 5000003 floats, 611 tiles, 10.2 us, 18.5 with a ticket).
+// Nothing orders the workgroups of one launch across XCDs when another stream's
+// kernels hold part of the device, so a preceding tile may not start while this
+// one waits.  A lane whose patience ends therefore computes the total it misses
+// from the input (flat_total), and the tile finishes; only the tile that advances
+// the epoch then waits for every tile to have started, and the slots that all
+// others leave let them.  The input must still be there: calls whose output
+// overlaps it take a form with tile ids from a counter, but for S5, which then (and
+// for few tiles) keeps waiting, bounded.
+
+// The total of tile `seq` by one lane, in the steps of lane_total, wave_reduce and
+// tile_totals (the same bits): a few milliseconds, for a tile that does not start.
+// Nothing is published: a valid descriptor says that its tile has started.
+template <class P, bool REV>
+__device__ __forceinline__ typename P::acc_t flat_total(const typename P::in_t* in, int64_t n,
+                                                        int64_t seq, int64_t ntiles) {
+    using acc_t = typename P::acc_t;
+    using C = typename P::C;
+    const int64_t tile = REV ? ntiles - 1 - seq : seq;
+    acc_t agg = C::id();
+#pragma unroll 1
+    for (int w = 0; w < P::NW; ++w) {
+        acc_t level[6], t = C::id();  // pending halves of the butterfly's tree
+#pragma unroll 1
+        for (int i = 0; i < kWave; ++i) {
+            const int l = (int)(__builtin_bitreverse32((uint32_t)i) >> 26);
+            const int64_t b = tile * P::kTile + (int64_t)w * P::kWaveElems + (int64_t)l * P::E;
+            t = C::id();
+#pragma unroll 1
+            for (int k = 0; k < P::R * P::E; ++k) {
+                const int64_t idx = b + (int64_t)(k / P::E) * kWave * P::E + k % P::E;
+                if (idx < n) t = C::op(t, widen<acc_t>(in[idx]));
+            }
+#pragma unroll
+            for (int v = 0; v < 6; ++v) {
+                if (!((i >> v) & 1)) {
+                    level[v] = t;
+                    break;
+                }
+                t = C::op(level[v], t);
+            }
+        }
+        agg = C::op(agg, t);
+    }
+    return agg;
+}
+
+// This lane's share of the totals of tiles 0 .. seq - 1.  missing: one was not there
+// after the last poll, and RESCUE: was computed from the n elements of in, else left out.
+template <class P, bool REV, bool RESCUE>
 __device__ __forceinline__ typename P::acc_t flat_prefix(u64* status, int64_t seq,
-                                                         uint32_t epoch, u64* err) {
+                                                         uint32_t epoch,
+                                                         const typename P::in_t* in, int64_t n,
+                                                         int64_t ntiles, bool* missing) {
     using acc_t = typename P::acc_t;
     using C = typename P::C;
     acc_t a = C::id();
@@ -285,8 +338,24 @@ __device__ __forceinline__ typename P::acc_t flat_prefix(u64* status, int64_t se
                 all = all && ready[k];
             }
             if (all) break;
-            if (++spins > kSpinLimit) {  // bounded: flag it and finish
-                atomicOr(err, 1ull);
+            if (++spins > (RESCUE ? kFlatPatience : kSpinLimit)) {  // bounded
+                *missing = true;
+                if constexpr (RESCUE) {
+#pragma unroll 1
+                    for (int k = 0; k < kFlatPerLane; ++k) {
+                        bool want = false;
+#pragma unroll
+                        for (int q = 0; q < kFlatPerLane; ++q) want = want || (q == k && !ready[q]);
+                        if (!want) continue;
+                        const acc_t t = flat_total<P, REV>(
+                            in, n, base + k * P::kBlock + threadIdx.x, ntiles);
+#pragma unroll
+                        for (int q = 0; q < kFlatPerLane; ++q) {
+                            v[q] = q == k ? t : v[q];
+                            ready[q] = ready[q] || q == k;
+                        }
+                    }
+                }
                 break;
             }
             __builtin_amdgcn_s_sleep(1);
@@ -295,6 +364,78 @@ __device__ __forceinline__ typename P::acc_t flat_prefix(u64* status, int64_t se
         for (int k = 0; k < kFlatPerLane; ++k) a = C::op(a, ready[k] ? v[k] : C::id());
     }
     return a;
+}
+
+// wavefronts per SIMD of the flat forms, as without the rescue
+template <class P>
+constexpr int flat_waves() { return sizeof(typename P::in_t) == 4 ? 4 : P::NW <= 1 ? 3 : 2; }
+
+// A flat tile: seq of ntiles in scan order, covering data tile `tile` of n elements;
+// descriptors at status.  last: this workgroup advances the epoch, once every one of
+// the `all` descriptors of the call (at `first`) has been seen valid: by then every
+// tile has read this call's epoch.
+template <class P, bool FULL, bool REV, bool RESCUE, bool ROWS>
+__device__ __forceinline__ void flat_tile(const typename P::in_t* in, typename P::out_t* out,
+                                          int64_t n, int64_t seq, int64_t tile, int64_t ntiles,
+                                          int exclusive, u64* status, u64* sync, bool last,
+                                          u64* first, int64_t all) {
+    using acc_t = typename P::acc_t;
+    using C = typename P::C;
+    __shared__ acc_t s_wtot[P::NW];
+    __shared__ acc_t s_red[P::NW];
+    __shared__ acc_t s_prefix;
+    __shared__ uint32_t s_epoch;
+    __shared__ int s_missing;
+    uint32_t ep = 0;
+    if (threadIdx.x == 0) ep = epoch_of_call(sync);  // in flight with the tile's loads
+    Raw<P> raw;
+    tile_load<P, FULL, true>(in, n, tile, raw);
+    acc_t wex, agg;
+    tile_totals<P, REV>(lane_total<P, FULL>(n, tile, raw), s_wtot, &wex, &agg);
+    if (threadIdx.x == 0) {
+        s_epoch = ep;
+        if (RESCUE) s_missing = 0;
+        if (!last) publish(status, seq, ST_AGG, agg, ep);
+    }
+    __syncthreads();
+    bool missing = false;
+    const acc_t part =
+        flat_prefix<P, REV, RESCUE>(status, seq, s_epoch, in, n, ntiles, &missing);
+    if (missing) {
+        if (RESCUE) s_missing = 1;
+        else atomicOr(sync + SYNC_ERROR, 1ull);
+    }
+    const acc_t pre = block_reduce<C>(part, s_red);
+    // (block_reduce's barrier orders s_missing) every tile seen, if the call's are
+    // this one's predecessors and none was missing
+    const bool seen = last && !(RESCUE && s_missing) && (!ROWS || (status == first && seq == all));
+    if (threadIdx.x == 0) {
+        s_prefix = pre;
+        if (seen) epoch_advance(sync);
+    }
+    __syncthreads();
+    keep_raw_only<P>(raw);
+    tile_scan_store<P, FULL, REV>(out, n, tile, raw, C::op(s_prefix, wex), exclusive != 0);
+    if ((ROWS || RESCUE) && last && !seen) {
+        bool expired = false;
+        if constexpr (ROWS) {
+            flat_prefix<P, REV, false>(first, all, s_epoch, in, n, ntiles, &expired);
+        } else {
+            // (only after a rescue: one descriptor after another, in little code)
+            acc_t v;
+#pragma unroll 1
+            for (int64_t j = threadIdx.x; j < all; j += P::kBlock)
+#pragma unroll 1
+                for (uint32_t spins = 0;
+                     tagged_get(first + 2 * j, s_epoch, v) == ST_INVALID && !expired;) {
+                    expired = ++spins > kSpinLimit;
+                    __builtin_amdgcn_s_sleep(1);
+                }
+        }
+        if (expired) atomicOr(sync + SYNC_ERROR, 1ull);
+        __syncthreads();
+        if (threadIdx.x == 0) epoch_advance(sync);
+    }
 }
 
 }  // namespace dev

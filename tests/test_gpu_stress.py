@@ -108,3 +108,21 @@ def test_shrunk_tile_lookback_stress(skel):
                          text=True, timeout=240)
     print(res.stdout[-2000:], res.stderr[-2000:])
     assert res.returncode == 0 and res.stdout.strip().endswith("ok")
+
+
+def test_flat_tiles_compute_the_totals_they_miss(skel):
+    """Flat tiles whose patience is one poll (the stress build, in a child process):
+    a tile that does not find its predecessors' totals computes them itself, so
+    that no tile depends on another one's start; same results, same bits."""
+    import os
+    import subprocess
+    import sys
+    from paper_1405_2915_amd import build_lib
+    if not os.path.exists(build_lib.SCAN_STRESS_LIB):
+        pytest.fail("libskel_scan_w2.so not built (paper_1405_2915_amd/build_lib.py)")
+    child = os.path.join(os.path.dirname(os.path.abspath(__file__)), "flat_rescue_child.py")
+    env = dict(os.environ, SKEL_LIBRARY=build_lib.SCAN_STRESS_LIB)
+    res = subprocess.run([sys.executable, "-u", child], env=env, capture_output=True,
+                         text=True, timeout=110)
+    print(res.stdout[-2000:], res.stderr[-2000:])
+    assert res.returncode == 0 and res.stdout.strip().endswith("ok")
