@@ -339,16 +339,14 @@ skel_status scan_typed(int v, int kind, const void* x, void* y, int64_t n, Launc
         void* status = nullptr;
         skel_status e = ws_status(lc, (size_t)nts * 16, &status);
         if (e != SKEL_OK) return e;
-        // up to an eighth of the device's slots the tiles of several launches on as
-        // many streams are resident together (HIP runs four queues at once), and
-        // every wait ends without the means to compute a missing total (5.3 us
-        // with them at 2^20 elements, 5.2 without)
-        const auto plain = rev ? scan_flat<PS, true, false> : scan_flat<PS, false, false>;
-        const bool few =
-            8 * nts <= resident_slots(reinterpret_cast<const void*>(plain), PS::kBlock, lc);
-        const auto kern = few || !apart ? plain
-                          : rev         ? scan_flat<PS, true, true>
-                                        : scan_flat<PS, false, true>;
+        // up to one tile per CU (which holds eight or more) the tiles of several
+        // launches on as many streams are resident together (HIP runs four queues
+        // at once), and every wait ends without the means to compute a missing
+        // total (5.3 us with them at 2^20 elements, 5.2 without)
+        const bool few = nts <= lc.dev->cus;
+        const auto kern =
+            few || !apart ? (rev ? scan_flat<PS, true, false> : scan_flat<PS, false, false>)
+                          : (rev ? scan_flat<PS, true, true> : scan_flat<PS, false, true>);
         kern<<<(unsigned)nts, PS::kBlock, 0, st>>>(in, out, n, nts, excl,
                                                    static_cast<u64*>(status), lc.ws->sync);
         return launch_check("scan_flat");

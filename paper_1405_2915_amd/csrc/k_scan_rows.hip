@@ -7,18 +7,25 @@
 //   a wavefront  per row, walking it in chunks of as many vectors per lane as the
 //                row needs (1, 2, 4 or 8 rows of 64 vectors) with a running carry;
 //                the form for many rows
-//   few rows     (fewer than 1024 wavefronts' worth of work in flight) of more
-//                than 4096 elements are cut into tiles: with up to 1024 tiles of
-//                two wavefronts in all, the flat look-back within each row;
-//                otherwise tiles of 16 wavefronts (4 for rows of at most 8192)
-//                with the decoupled look-back within each row, or without any
-//                where a row is one tile
+//   few rows     (fewer than 1024) of more than 4096 elements: a workgroup of four
+//                wavefronts per row that it holds (8192 elements, 4096 of 8 bytes); one
+//                of 16 per row (32768 and 16384) for at most one row per CU; longer
+//                rows, up to one and a half per CU, are cut: binary32 sums into the
+//                wavefront form's chunks in three launches that keep its order of
+//                additions, everything else into tiles, with up to 1024 tiles of two
+//                wavefronts in all the flat look-back within each row, otherwise tiles
+//                of 16 wavefronts with the decoupled look-back
 // All are HBM-bound once enough rows or tiles are in flight.  Measured, forward
 // and reverse together, against one wavefront per row in chunks of 2048 elements
 // (64-element chunks of single accesses where rows are not 16-byte aligned),
 // binary32: 65536 x 20 117 -> 7 us, 20000 x 100 43 -> 9.2, 3000 x 1001 18.2 -> 11.3,
-// 65536 x 512 121 -> 89 (6 TB/s), 900 x 5001 64 -> 20, 300 x 100001 1469 -> 112,
-// 40 x 50001 394 -> 18, 3 x 1000003 9800 -> 22; 16384 x 2048 92.6 both (5.8 TB/s).
+// 65536 x 512 121 -> 89 (6 TB/s), 900 x 5001 64 -> 20; 16384 x 2048 92.6 both (5.8
+// TB/s).  Longer rows, binary32 / int32 (one call, whose 64-element form took 562, 161
+// and 5149 us): 300 x 100001 66 / 56, 40 x 50001 12.4 / 9.1, 3 x 1000003 31.5 / 10.1.
+// Where the lines lie (one call): a wavefront per row against 16 wavefronts, 256 x
+// 20000 17.2 / 10.0 us, 300 x 20000 18.1 / 15.6, 700 x 20000 22.5 / 26.7, 300 x 9001 9.7
+// / 13.8; against cut rows, 300 x 50001 41 / 36, 384 x 50001 42 / 44, 512 x 50001 44 / 55;
+// int64 300 x 50001 80 / 59, 512 x 50001 86 / 92, 1000 x 5001 (in tiles) 20 / 33.
 #include "kscan.hpp"
 #include "dispatch.hpp"
 #include "launch.hpp"
@@ -94,10 +101,8 @@ __device__ __forceinline__ T group_scan(T v, int G) {
 }
 
 constexpr int kShortBlock = 256;
-// fewer rows than this, longer than that, are cut into tiles: 1024 wavefronts
-// with one chunk each in flight reach about half of HBM's rate (500 x 20000 44
-// us for a wavefront per row, 38 in tiles; at 1024 x 32768 both 113), and a row of
-// up to 4096 elements is two chunks
+// fewer rows than this, longer than that, may take more than a wavefront each (a row
+// of up to 4096 elements is two chunks)
 constexpr int64_t kFewRows = 1024, kLongRow = 4096;
 
 template <class P, bool REV>
@@ -242,6 +247,107 @@ __global__ __launch_bounds__(P::kBlock) void scan_rows_tiles(const typename P::i
     }
 }
 
+// Long rows of binary32 sums: the wavefront form's arithmetic in three launches, so
+// that the order of the additions, and with it every bit, depends on neither timing
+// nor the form (a captured call takes the wavefront form).  A wavefront per chunk of
+// P::kTile elements: the totals of its P::R vector rows; a wavefront per row: their
+// sum so far at the start of every chunk, one addition after another as the carry of
+// the wavefront form runs; a wavefront per chunk: the scan from there.  The input is
+// read twice (mostly from cache for rows that fit it).
+template <class P, bool REV>
+__global__ __launch_bounds__(kWave) void scan_rows_totals(const typename P::in_t* in, int64_t cols,
+                                                          int64_t nch, typename P::acc_t* tot) {
+    using acc_t = typename P::acc_t;
+    using C = typename P::C;
+    const int64_t row = (int64_t)blockIdx.x / nch, ch = (int64_t)blockIdx.x - row * nch;
+    const int64_t b = lane_base<P>(ch);
+    Raw<P> raw;
+    if ((ch + 1) * P::kTile <= cols) tile_load<P, true, true>(in + row * cols, cols, ch, raw);
+    else tile_load<P, false, true>(in + row * cols, cols, ch, raw);
+    acc_t mine = C::id();
+#pragma unroll
+    for (int r = 0; r < P::R; ++r) {
+        acc_t t = C::id();
+#pragma unroll
+        for (int ee = 0; ee < P::E; ++ee) {
+            const int e = REV ? P::E - 1 - ee : ee;
+            const bool in_row = b + (int64_t)r * kWave * P::E + e < cols;
+            t = C::op(t, in_row ? widen<acc_t>(raw[r][e]) : C::id());
+        }
+        const acc_t incl = REV ? wave_inclusive_suffix_scan<C>(t) : wave_inclusive_scan<C>(t);
+        const acc_t all = lane_value(incl, REV ? 0 : kWave - 1);
+        if (lane() == r) mine = all;
+    }
+    if (lane() < P::R) tot[(int64_t)blockIdx.x * P::R + lane()] = mine;
+}
+
+// (A workgroup stages the totals in LDS, in scan order, and its first wavefront adds
+// them up from broadcast reads of four: what bounds it is one dependent addition per
+// 256 elements.  Loads into that wavefront and lane moves: 30 us for a row of 10^6
+// elements; scalar loads, whose latency shows: 48.)
+constexpr int kCarryBlock = 256, kCarryStage = 16 * kCarryBlock;
+
+template <class P, bool REV>
+__global__ __launch_bounds__(kCarryBlock) void scan_rows_carries(const typename P::acc_t* tot,
+                                                                 int64_t nch,
+                                                                 typename P::acc_t* carry) {
+    using acc_t = typename P::acc_t;
+    using C = typename P::C;
+    constexpr int kTurn = 64, kChunks = kTurn / P::R;
+    __shared__ __attribute__((aligned(16))) acc_t s[kCarryStage];
+    const int64_t nb = nch * P::R;
+    tot += blockIdx.x * nb;
+    carry += blockIdx.x * nch;
+    acc_t running = C::id();
+    for (int64_t base = 0; base < nb; base += kCarryStage) {
+        acc_t v[kCarryStage / kCarryBlock];
+#pragma unroll
+        for (int u = 0; u < kCarryStage / kCarryBlock; ++u) {
+            const int64_t i = base + u * kCarryBlock + threadIdx.x;
+            v[u] = i < nb ? tot[REV ? nb - 1 - i : i] : C::id();
+        }
+        __syncthreads();  // the last stage has been read
+#pragma unroll
+        for (int u = 0; u < kCarryStage / kCarryBlock; ++u)
+            s[u * kCarryBlock + threadIdx.x] = v[u];
+        __syncthreads();
+        if (threadIdx.x >= kWave) continue;
+        const int n = nb - base < kCarryStage ? (int)(nb - base) : kCarryStage;
+        for (int t = 0; t < n; t += kTurn) {
+            acc_t mine = C::id();
+#pragma unroll
+            for (int i = 0; i < kTurn; ++i) {
+                if (i % P::R == 0 && lane() == i / P::R) mine = running;
+                running = C::op(running, s[t + i]);
+            }
+            const int64_t c = (base + t) / P::R + lane();
+            if (lane() < kChunks && c < nch) carry[REV ? nch - 1 - c : c] = mine;
+        }
+    }
+}
+
+template <class P, bool REV>
+__global__ __launch_bounds__(kWave) void scan_rows_apply(const typename P::in_t* in,
+                                                         typename P::out_t* out, int64_t cols,
+                                                         int64_t nch,
+                                                         const typename P::acc_t* carry,
+                                                         int exclusive) {
+    const int64_t row = (int64_t)blockIdx.x / nch, ch = (int64_t)blockIdx.x - row * nch;
+    const typename P::in_t* src = in + row * cols;
+    typename P::out_t* dst = out + row * cols;
+    const typename P::acc_t c = carry[blockIdx.x];
+    Raw<P> raw;
+    if ((ch + 1) * P::kTile <= cols) {
+        tile_load<P, true, true>(src, cols, ch, raw);
+        keep_raw_only<P>(raw);
+        tile_scan_store<P, true, REV>(dst, cols, ch, raw, c, exclusive != 0);
+    } else {
+        tile_load<P, false, true>(src, cols, ch, raw);
+        keep_raw_only<P>(raw);
+        tile_scan_store<P, false, REV>(dst, cols, ch, raw, c, exclusive != 0);
+    }
+}
+
 // --------------------------------------------------------------- launchers
 struct RowsCall {
     const void* x;
@@ -291,8 +397,65 @@ skel_status run_tiles(const RowsCall& c, LaunchCtx& lc, bool* done) {
 }
 
 template <int DIN, int DOUT, int OP>
+skel_status run_ordered(const RowsCall& c, LaunchCtx& lc, bool* done) {
+    using P = SPW<DIN, DOUT, OP, 8>;
+    using acc_t = typename P::acc_t;
+    const int64_t nch = (c.cols + P::kTile - 1) / P::kTile, chunks = c.rows * nch;
+    if (capturing(lc) || chunks > max_groups(kWave)) return SKEL_OK;
+    void* mem = nullptr;
+    skel_status e = ws_scratch(lc, (size_t)chunks * (P::R + 1) * sizeof(acc_t), &mem);
+    if (e == SKEL_E_NOMEM) {
+        clear_error();
+        return SKEL_OK;
+    }
+    if (e != SKEL_OK) return e;
+    acc_t* tot = static_cast<acc_t*>(mem);
+    acc_t* carry = tot + chunks * P::R;
+    const auto* in = static_cast<const typename P::in_t*>(c.x);
+    auto* out = static_cast<typename P::out_t*>(c.y);
+    const auto totals = c.rev ? scan_rows_totals<P, true> : scan_rows_totals<P, false>;
+    const auto carries = c.rev ? scan_rows_carries<P, true> : scan_rows_carries<P, false>;
+    const auto apply = c.rev ? scan_rows_apply<P, true> : scan_rows_apply<P, false>;
+    totals<<<(unsigned)chunks, kWave, 0, lc.stream>>>(in, c.cols, nch, tot);
+    if ((e = launch_check("scan_rows_totals")) != SKEL_OK) return e;
+    carries<<<(unsigned)c.rows, kCarryBlock, 0, lc.stream>>>(tot, nch, carry);
+    if ((e = launch_check("scan_rows_carries")) != SKEL_OK) return e;
+    apply<<<(unsigned)chunks, kWave, 0, lc.stream>>>(in, out, c.cols, nch, carry, c.excl);
+    *done = true;
+    return launch_check("scan_rows_apply");
+}
+
+// rows of several workgroups' tiles
+template <int DIN, int DOUT, int OP>
+skel_status run_long(const RowsCall& c, LaunchCtx& lc, bool* done) {
+    using PS = SP<DIN, DOUT, OP, 2, false>;
+    // sums of floating-point numbers keep one order of additions
+    if constexpr (DOUT == SKEL_F32 && OP == SKEL_SUM) {
+        return run_ordered<DIN, DOUT, OP>(c, lc, done);
+    } else {
+        const int64_t tpr = (c.cols + PS::kTile - 1) / PS::kTile;
+        const auto flat = c.rev ? scan_rows_flat<PS, true> : scan_rows_flat<PS, false>;
+        const char *x0 = static_cast<const char*>(c.x), *y0 = static_cast<const char*>(c.y);
+        const int64_t n = c.rows * c.cols;
+        const bool apart = x0 + n * sizeof(typename PS::in_t) <= y0 ||
+                           y0 + n * sizeof(typename PS::out_t) <= x0;
+        if (!apart || c.rows * tpr > kFlatMaxTiles ||
+            c.rows * tpr > resident_slots(reinterpret_cast<const void*>(flat), PS::kBlock, lc))
+            return run_tiles<SP<DIN, DOUT, OP, 16, false>>(c, lc, done);
+        void* status = nullptr;
+        const skel_status e = tile_status(lc, c.rows * tpr, &status);
+        if (e != SKEL_OK || !status) return e;
+        flat<<<(unsigned)(c.rows * tpr), PS::kBlock, 0, lc.stream>>>(
+            static_cast<const typename PS::in_t*>(c.x), static_cast<typename PS::out_t*>(c.y),
+            c.cols, tpr, c.excl, static_cast<u64*>(status), lc.ws->sync);
+        *done = true;
+        return launch_check("scan_rows_flat");
+    }
+}
+
+template <int DIN, int DOUT, int OP>
 skel_status scan_rows_typed(const RowsCall& c, LaunchCtx& lc) {
-    using PS = SP<DIN, DOUT, OP, 2, false>;   // small tiles
+    using PS = SP<DIN, DOUT, OP, 2, false>;
     using PM = SP<DIN, DOUT, OP, 4, false>;
     using PL = SP<DIN, DOUT, OP, 16, false>;
     constexpr int E = PS::E;
@@ -314,29 +477,11 @@ skel_status scan_rows_typed(const RowsCall& c, LaunchCtx& lc) {
     if (c.rows < kFewRows && c.cols > kLongRow) {
         bool done = false;
         skel_status e = SKEL_OK;
-        const int64_t tpr = (c.cols + PS::kTile - 1) / PS::kTile;
-        const auto flat = c.rev ? scan_rows_flat<PS, true> : scan_rows_flat<PS, false>;
-        const char *x0 = static_cast<const char*>(c.x), *y0 = static_cast<const char*>(c.y);
-        const int64_t n = c.rows * c.cols;
-        const bool apart = x0 + n * sizeof(typename PS::in_t) <= y0 ||
-                           y0 + n * sizeof(typename PS::out_t) <= x0;
-        if (apart && c.rows * tpr <= kFlatMaxTiles &&
-            c.rows * tpr <=
-                resident_slots(reinterpret_cast<const void*>(flat), PS::kBlock, lc)) {
-            void* status = nullptr;
-            e = tile_status(lc, c.rows * tpr, &status);
-            if (e == SKEL_OK && status) {
-                flat<<<(unsigned)(c.rows * tpr), PS::kBlock, 0, lc.stream>>>(
-                    static_cast<const typename PS::in_t*>(c.x),
-                    static_cast<typename PS::out_t*>(c.y), c.cols, tpr, c.excl,
-                    static_cast<u64*>(status), lc.ws->sync);
-                done = true;
-                e = launch_check("scan_rows_flat");
-            }
-        } else {
-            e = c.cols <= PM::kTile ? run_tiles<PM>(c, lc, &done)
-                                    : run_tiles<PL>(c, lc, &done);
-        }
+        const bool one_each = c.rows <= lc.dev->cus;  // a workgroup of 16 wavefronts per row
+        if (c.cols <= PM::kTile) e = run_tiles<PM>(c, lc, &done);
+        else if (c.cols <= PL::kTile && one_each) e = run_tiles<PL>(c, lc, &done);
+        else if (c.cols > PL::kTile && 2 * c.rows < 3 * lc.dev->cus)
+            e = run_long<DIN, DOUT, OP>(c, lc, &done);
         if (e != SKEL_OK || done) return e;
     }
     if (c.cols <= 256) return run_wave<DIN, DOUT, OP, 1>(c, lc);

@@ -249,6 +249,45 @@ def test_scan_rows_tiled_form_under_capture(skel):
         c.destroy()
 
 
+def test_scan_rows_f32_sums_keep_their_bits(skel):
+    """binary32 row sums are the same bits on every run and inside a captured graph,
+    whichever form serves the shape (a workgroup per row, rows cut into chunks, a
+    wavefront per row), beside a busy second stream too."""
+    import torch
+    s, other = torch.cuda.Stream(), torch.cuda.Stream()
+    load = torch.randn(2048, 2048, device="cuda")
+    torch.cuda.synchronize()
+    for rows, cols in ((300, 5001), (40, 30000), (1, 32769), (40, 50001), (300, 100001),
+                       (3, 1000003), (1, 5000009)):
+        x = torch.randn(rows, cols, device="cuda")
+        y = torch.empty_like(x)
+        cx, cy = skel.wrap_tensor(x), skel.wrap_tensor(y)
+        torch.cuda.synchronize()
+        for kind in range(4):
+            with torch.cuda.stream(s):
+                skel.skel_scan_rows(cx, cy, kind, skel.SUM, variant=SR1)
+                first = y.clone()
+                for rep in range(6):
+                    with torch.cuda.stream(other):
+                        load.mul_(1.0)
+                    y.fill_(float("nan"))
+                    skel.skel_scan_rows(cx, cy, kind, skel.SUM, variant=SR1)
+                    assert torch.equal(y, first), (rows, cols, kind, rep)
+            torch.cuda.synchronize()
+            g = torch.cuda.CUDAGraph()
+            with torch.cuda.graph(g, stream=s):
+                skel.skel_scan_rows(cx, cy, kind, skel.SUM, variant=SR1)
+            for rep in range(3):
+                y.fill_(float("nan"))
+                torch.cuda.synchronize()
+                g.replay()
+                torch.cuda.synchronize()
+                assert torch.equal(y, first), (rows, cols, kind, "replay", rep)
+        for c in (cx, cy):
+            c.destroy()
+    skel.skel_sync()
+
+
 def test_row_scans_leave_captured_scans_intact(skel):
     """A flat scan captured on a stream replays correctly after row scans on the
     same stream have enlarged the descriptor array: words left on the array that
