@@ -370,11 +370,14 @@ skel_status run_wave(const RowsCall& c, LaunchCtx& lc) {
 
 // the descriptor array for a tiled form, or NULL (the form that needs none then
 // serves the call) where it cannot be allocated, and inside a graph capture: the
-// graph may be replayed beside other calls that use the stream's descriptors
+// graph may be replayed beside other calls that use the stream's descriptors.  A
+// row scan outside a capture uses none that a captured call does, either (the
+// second workspace): a wavefront per row, which shares nothing, would serve it.
 skel_status tile_status(LaunchCtx& lc, int64_t tiles, void** status) {
     *status = nullptr;
     if (capturing(lc)) return SKEL_OK;
-    const skel_status e = ws_status(lc, (size_t)tiles * 16, status);
+    skel_status e = eager_workspace(lc);
+    if (e == SKEL_OK) e = ws_status(lc, (size_t)tiles * 16, status);
     if (e != SKEL_E_NOMEM) return e;
     clear_error();
     return SKEL_OK;
@@ -403,7 +406,8 @@ skel_status run_ordered(const RowsCall& c, LaunchCtx& lc, bool* done) {
     const int64_t nch = (c.cols + P::kTile - 1) / P::kTile, chunks = c.rows * nch;
     if (capturing(lc) || chunks > max_groups(kWave)) return SKEL_OK;
     void* mem = nullptr;
-    skel_status e = ws_scratch(lc, (size_t)chunks * (P::R + 1) * sizeof(acc_t), &mem);
+    skel_status e = eager_workspace(lc);
+    if (e == SKEL_OK) e = ws_scratch(lc, (size_t)chunks * (P::R + 1) * sizeof(acc_t), &mem);
     if (e == SKEL_E_NOMEM) {
         clear_error();
         return SKEL_OK;

@@ -32,6 +32,7 @@ struct Workspace {
     void* status = nullptr;
     size_t status_bytes = 0;
     uint64_t epoch_calls = 0;  // calls that advanced the device epoch since its last reset
+    Workspace* eager = nullptr;  // see eager_workspace
 };
 
 // slots of the sync area, as indices of 64-bit words; each slot has its own
@@ -65,6 +66,10 @@ struct LaunchCtx {
 const DevInfo& device_info();
 skel_status workspace_for(void* stream, Workspace** out);
 skel_status ws_scratch(LaunchCtx& lc, size_t bytes, void** p);
+// Makes lc use the stream's second workspace, which no captured call ever uses: a
+// graph captured on the stream may be replayed on another one beside the call.  Not
+// inside a capture.
+skel_status eager_workspace(LaunchCtx& lc);
 void retire(Workspace* w, void* p);  // free at skel_finalize, not before
 // most workgroups of `block` lanes along one dimension of a launch (work items
 // are numbered with 32 bits)

@@ -128,6 +128,7 @@ std::unordered_map<void*, Workspace*> g_ws;
 std::unordered_map<Workspace*, std::vector<void*>> g_retired;
 
 void free_workspace(Workspace* w) {
+    if (w->eager) free_workspace(w->eager);
     const skel_allocator& a = rt().allocator;
     dev_mfree(a, w->scratch, w->stream);
     dev_mfree(a, w->sync, w->stream);
@@ -135,6 +136,25 @@ void free_workspace(Workspace* w) {
     for (void* p : g_retired[w]) dev_mfree(a, p, w->stream);
     g_retired.erase(w);
     delete w;
+}
+
+// a workspace of `stream` with a zeroed sync area
+skel_status make_workspace(void* stream, Workspace** out) {
+    auto* w = new Workspace();
+    w->stream = stream;
+    size_t sb = SYNC_SLOTS * sizeof(unsigned long long);
+    w->sync = static_cast<unsigned long long*>(dev_malloc(rt().allocator, sb, stream));
+    if (!w->sync) {
+        delete w;
+        return fail(SKEL_E_NOMEM, "workspace allocation failed");
+    }
+    skel_status st = hip_check(hipMemsetAsync(w->sync, 0, sb, S(stream)), "hipMemsetAsync");
+    if (st != SKEL_OK) {
+        free_workspace(w);
+        return st;
+    }
+    *out = w;
+    return SKEL_OK;
 }
 
 }  // namespace
@@ -162,21 +182,22 @@ skel_status workspace_for(void* stream, Workspace** out) {
         return fail(SKEL_E_STATE,
                     "first use of this stream is inside a graph capture; run a call on the "
                     "stream once before capturing (its workspace is cleared by a fill)");
-    auto* w = new Workspace();
-    w->stream = stream;
-    size_t sb = SYNC_SLOTS * sizeof(unsigned long long);
-    w->sync = static_cast<unsigned long long*>(dev_malloc(rt().allocator, sb, stream));
-    if (!w->sync) {
-        delete w;
-        return fail(SKEL_E_NOMEM, "workspace allocation failed");
-    }
-    skel_status st = hip_check(hipMemsetAsync(w->sync, 0, sb, S(stream)), "hipMemsetAsync");
-    if (st != SKEL_OK) {
-        free_workspace(w);
-        return st;
-    }
+    Workspace* w = nullptr;
+    const skel_status st = make_workspace(stream, &w);
+    if (st != SKEL_OK) return st;
     g_ws[stream] = w;
     *out = w;
+    return SKEL_OK;
+}
+
+skel_status eager_workspace(LaunchCtx& lc) {
+    std::lock_guard<std::mutex> lk(g_ws_mu);
+    Workspace* const w = lc.ws;
+    if (!w->eager) {
+        const skel_status st = make_workspace(w->stream, &w->eager);
+        if (st != SKEL_OK) return st;
+    }
+    lc.ws = w->eager;
     return SKEL_OK;
 }
 
@@ -323,20 +344,22 @@ skel_status skel_sync(void* stream) {
         auto it = g_ws.find(stream);
         if (it != g_ws.end()) w = it->second;
     }
-    if (!w) return SKEL_OK;
-    unsigned long long flag = 0;
-    st = hip_check(hipMemcpy(&flag, w->sync + SYNC_ERROR, sizeof flag,
-                             hipMemcpyDeviceToHost),
-                   "hipMemcpy");
-    if (st != SKEL_OK) return st;
-    if (flag) {
-        (void)hipMemset(w->sync + SYNC_ERROR, 0, sizeof flag);
+    unsigned long long flags = 0;
+    for (; w; w = w->eager) {
+        unsigned long long flag = 0;
+        st = hip_check(hipMemcpy(&flag, w->sync + SYNC_ERROR, sizeof flag,
+                                 hipMemcpyDeviceToHost),
+                       "hipMemcpy");
+        if (st != SKEL_OK) return st;
+        if (flag) (void)hipMemset(w->sync + SYNC_ERROR, 0, sizeof flag);
+        flags |= flag;
+    }
+    if (flags)
         return fail(SKEL_E_TIMEOUT,
                     "a bounded inter-workgroup wait expired (flag 0x%llx: 1 = scan "
                     "look-back, 2 = reduce partials); results of the "
                     "calls since the last skel_sync on this stream are invalid",
-                    flag);
-    }
+                    flags);
     return SKEL_OK;
 }
 

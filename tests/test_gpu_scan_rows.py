@@ -330,3 +330,53 @@ def test_row_scans_leave_captured_scans_intact(skel):
         assert torch.equal(yt, torch.cumsum(xt.to(torch.int64), 0).to(torch.int32)), k
     for c in (cx, cy, crx):
         c.destroy()
+
+
+def test_row_scans_beside_replays_of_the_streams_graphs(skel):
+    """A graph captured on a stream and replayed on another one runs beside eager row
+    scans on the first: they share no counters, descriptors or scratch."""
+    import torch
+    a, b = torch.cuda.Stream(), torch.cuda.Stream()
+    n = (1 << 22) + 40961
+    x = torch.randint(0, 1000, (n,), device="cuda", dtype=torch.int32)
+    f = torch.randn(n, device="cuda")
+    y, r = torch.empty_like(x), torch.empty(1, device="cuda")
+    cx, cy, cf, cr = (skel.wrap_tensor(t) for t in (x, y, f, r))
+    rows = [(torch.randint(0, 1000, s, device="cuda", dtype=d), torch.empty(s, device="cuda", dtype=d))
+            for s, d in (((90, 65537), torch.int32), ((3, 1000003), torch.int32))]
+    rows.append((torch.randn(200, 50001, device="cuda"), torch.empty(200, 50001, device="cuda")))
+    crows = [(skel.wrap_tensor(p), skel.wrap_tensor(q)) for p, q in rows]
+    torch.cuda.synchronize()
+
+    def graphed():
+        skel.skel_scan(cx, cy, skel.INCLUSIVE, skel.SUM, variant=2)
+        skel.skel_scan(cx, cy, skel.INCLUSIVE, skel.SUM, variant=3)
+        skel.skel_reduce(skel.SUM, cf, cr, variant=1)
+
+    with torch.cuda.stream(a):
+        graphed()
+        for p, q in crows:
+            skel.skel_scan_rows(p, q, skel.INCLUSIVE, skel.SUM, variant=SR1)
+    torch.cuda.synchronize()
+    want, total = y.clone(), r.clone()
+    wrows = [q.clone() for _, q in rows]
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=a):
+        graphed()
+    for rep in range(20):
+        y.zero_(), r.zero_()
+        for _, q in rows:
+            q.zero_()
+        torch.cuda.synchronize()
+        with torch.cuda.stream(b):
+            g.replay()
+        with torch.cuda.stream(a):
+            for p, q in crows:
+                skel.skel_scan_rows(p, q, skel.INCLUSIVE, skel.SUM, variant=SR1)
+        torch.cuda.synchronize()
+        assert torch.equal(y, want) and torch.equal(r, total), rep
+        for (_, q), w in zip(rows, wrows):
+            assert torch.equal(q, w), rep
+    for c in (cx, cy, cf, cr, *(c for pq in crows for c in pq)):
+        c.destroy()
+    skel.skel_sync(a)
