@@ -431,6 +431,48 @@ def test_mapoverlap2d_march_paths(skel, oracle_mod, edge, ry, rx):
             assert not bad.any(), (edge, ry, rx, shape, list(kw), np.argwhere(bad)[:5])
 
 
+@pytest.mark.parametrize("edge", list(EDGES))
+@pytest.mark.parametrize("ry,rx", [(1, 1), (2, 2), (1, 2), (0, 2), (3, 1)])
+def test_mapoverlap2d_march_ragged(skel, oracle_mod, edge, ry, rx):
+    """Rows that are not whole vectors, strips past a ragged row end, heights below, at
+    and past the 16 rows of a strip."""
+    v = skel.variant_index(skel.SK_MAPOVERLAP2D, "O2e_march")
+    wy, wx = (si.uniform_f32(2 * r + 1, -1.0, 1.0, 44, 10 + r) for r in (ry, rx))
+    w2d = si.uniform_f32((2 * ry + 1) * (2 * rx + 1), -1.0, 1.0, 44, 30).reshape(2 * ry + 1, -1)
+    for rows in (12, 16, 37):
+        for cols in (261, 515, 1001):
+            x = si.uniform_f32(rows * cols, -1.0, 1.0, 45, cols).reshape(rows, cols)
+            for kw in (dict(w2d=w2d), dict(wy=wy, wx=wx)):
+                ref, mag = oracle_mod.mapoverlap2d(x, ry, rx, edge=edge, pad=0.625, **kw)
+                out = skel.Container.empty(skel.F32, rows, cols)
+                skel.skel_mapoverlap2d(cont(skel, x), out, ry=ry, rx=rx, edge=EDGES[edge],
+                                       pad=0.625, variant=v, **kw)
+                got = out.to_numpy().reshape(rows, cols).astype(np.float64)
+                bad = np.abs(got - ref) > 1e-6 * mag + 1e-30
+                assert not bad.any(), (edge, ry, rx, rows, cols, list(kw), np.argwhere(bad)[:5])
+
+
+@pytest.mark.parametrize("variant,r", [("O2c_lds_separable", 2), ("O2c_lds_separable", 8),
+                                       ("O2d_separable_l1", 5), ("O2b_lds_tile", 8)])
+def test_mapoverlap2d_two_row_tile_forms(skel, oracle_mod, variant, r):
+    """The forms with two rows per lane (2^23 pixels and more) and their widest halos,
+    compared with the oracle on bands of rows."""
+    rows, cols = 2900, 2903
+    wy, wx = si.uniform_f32(2 * r + 1, 0.0, 1.0, 53, 1), si.uniform_f32(2 * r + 1, -1.0, 1.0, 53, 2)
+    kw = {"wy": wy, "wx": wx} if "separable" in variant else {"w2d": np.outer(wy, wx)}
+    x = si.uniform_f32(rows * cols, -1.0, 1.0, 53, 4).reshape(rows, cols)
+    out = skel.Container.empty(skel.F32, rows, cols)
+    skel.skel_mapoverlap2d(cont(skel, x), out, ry=r, rx=r, edge=EDGES["cyclic"],
+                           variant=skel.variant_index(skel.SK_MAPOVERLAP2D, variant), **kw)
+    got = out.to_numpy().reshape(rows, cols).astype(np.float64)
+    tol = ((2 * r + 1) ** 2 + 8) * 2.0 ** -24
+    for a, b in ((0, 20), (1440, 1470), (rows - 20, rows)):
+        band = np.take(x, np.arange(a - r, b + r), axis=0, mode="wrap")  # with its halo
+        ref, mag = oracle_mod.mapoverlap2d(band, r, r, edge="cyclic", **kw)
+        bad = np.abs(got[a:b] - ref[r:-r]) > tol * mag[r:-r] + 1e-30
+        assert not bad.any(), (variant, r, a, np.argwhere(bad)[:3])
+
+
 def test_mapoverlap_constant_field_and_impulse(skel):
     g = si.gaussian_weights(4, 2.0)
     sw = math.fsum(float(v) for v in g)
@@ -514,6 +556,80 @@ def test_scan_in_place_and_closed_forms(skel, oracle_mod):
         skel.skel_reduce(skel.SUM, cont(skel, x), red)
         assert inc.to_numpy()[-1] == red.to_numpy()[0]
     skel.skel_sync()
+
+
+# ragged sizes past S3's middle ones, whose tiles are flat: its persistent workgroups
+# loop over tile ids there
+@pytest.mark.parametrize("pair", ["f32", "i32_i32", "i32_i64", "i64_i64"])
+@pytest.mark.parametrize("op", list(RED_OPS))
+def test_scan_persistent_lookback(skel, pair, op):
+    import torch
+    din, dout = {"f32": (torch.float32,) * 2, "i32_i32": (torch.int32,) * 2,
+                 "i32_i64": (torch.int32, torch.int64), "i64_i64": (torch.int64,) * 2}[pair]
+    for n in ((1 << 22) + (1 << 20) + 5, (1 << 23) + 32771, 20 * (1 << 20) + 1):
+        if n < 1 << 23 and din != torch.int64:
+            continue
+        x = (torch.randn(n, device="cuda") if din == torch.float32 else
+             torch.randint(-1000, 1000, (n,), device="cuda", dtype=din))
+        y = torch.empty(n, device="cuda", dtype=dout)
+        cx, cy = skel.wrap_tensor(x), skel.wrap_tensor(y)
+        for kind in range(4):
+            y.fill_(-7)
+            skel.skel_scan(cx, cy, kind, RED_OPS[op], variant=3)
+            v = x.flip(0) if kind >= 2 else x
+            wide = torch.float64 if din == torch.float32 else torch.int64
+            if op == "sum":
+                ref = v.to(wide).cumsum(0)
+                if kind % 2:
+                    ref = ref - v
+            else:
+                ref = (v.to(wide).cummin(0) if op == "min" else v.to(wide).cummax(0)).values
+                if kind % 2:  # the first element is the identity
+                    ref = torch.cat([ref[:1], ref[:-1]])
+            got = y.flip(0) if kind >= 2 else y
+            first = 1 if kind % 2 and op != "sum" else 0
+            if din == torch.float32 and op == "sum":
+                bad = (got - ref).abs() > 1e-5 * v.abs().double().cumsum(0)
+            else:
+                bad = got.to(wide) != ref
+                if dout == torch.int32:
+                    bad = got != ref.to(torch.int32)
+            assert not bool(bad[first:].any()), (pair, op, n, kind)
+        for c in (cx, cy):
+            c.destroy()
+    skel.skel_sync()
+
+
+def test_scan_persistent_lookback_in_a_graph(skel):
+    """The persistent workgroups' counters are reset on the device: replays, with
+    eager calls of the same kind between them, give the eager result."""
+    import torch
+    n = (1 << 23) + 32771
+    x = torch.randint(0, 1000, (n,), device="cuda", dtype=torch.int32)
+    y, z = torch.empty_like(x), torch.empty_like(x)
+    s = torch.cuda.Stream()
+    cx, cy, cz = (skel.wrap_tensor(t, s) for t in (x, y, z))
+    torch.cuda.synchronize()
+    with torch.cuda.stream(s):
+        skel.skel_scan(cx, cy, skel.EXCLUSIVE, skel.SUM, variant=3)
+        torch.cuda.synchronize()
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=s):
+            skel.skel_scan(cx, cy, skel.EXCLUSIVE, skel.SUM, variant=3)
+    torch.cuda.synchronize()
+    for rep in range(4):
+        with torch.cuda.stream(s):
+            x.copy_(torch.randint(0, 1000, (n,), device="cuda", dtype=torch.int32))
+            y.fill_(-1)
+            skel.skel_scan(cx, cz, skel.REVERSE_INCLUSIVE, skel.SUM, variant=3)
+            g.replay()
+        s.synchronize()
+        want = torch.cumsum(x.to(torch.int64), 0)
+        assert torch.equal(y, (want - x).to(torch.int32)), rep
+        assert torch.equal(z, (want[-1] - want + x).to(torch.int32)), rep
+    skel.skel_sync(s)
+    for c in (cx, cy, cz):
+        c.destroy()
 
 
 def test_scan_repeated_calls_reuse_descriptors(skel, oracle_mod):
