@@ -180,6 +180,34 @@ def test_graph_capture_replays(skel, oracle_mod):
     skel.skel_sync(stream)
 
 
+@pytest.mark.parametrize("op", ["sum", "max"])
+def test_reduce_segments_many_empty(skel, op):
+    """Runs of a million empty segments: at the start, inside and at the end of the data, at
+    a chunk's border, and with no data at all."""
+    import torch
+    m = 1_000_000
+    for before, after in ((0, 0), (0, 5), (5, 0), (4096, 4096), (5000, 300), (1, 9000)):
+        lens = np.r_[np.full(int(before > 0), before, np.int64), np.zeros(m, np.int64),
+                     np.full(int(after > 0), after, np.int64)]
+        off = np.r_[0, np.cumsum(lens)]
+        x = si.normal_f32(before + after, 31, before)
+        cx = (skel.Container.from_numpy(x) if x.size else skel.Container.empty(skel.F32, 1, 0))
+        out = skel.Container.empty(skel.F32, lens.size)
+        skel.skel_reduce_segments(skel.SUM if op == "sum" else skel.MAX, cx,
+                                  skel.Container.from_numpy(off), out, variant=1)
+        got = out.to_numpy()
+        ident = np.float32(0 if op == "sum" else -np.inf)
+        full = np.flatnonzero(lens)
+        assert np.all(np.delete(got, full) == ident), (op, before, after)
+        for s in full:
+            part = x[off[s]:off[s + 1]].astype(np.float64)
+            if op == "max":
+                assert got[s] == part.max()
+            else:
+                assert abs(got[s] - part.sum()) <= 1e-5 * np.abs(part).sum()
+    skel.skel_sync()
+
+
 def test_graph_replays_batched_layer_and_persistent_scan(skel, oracle_mod):
     """The batched forms and the persistent scan captured once (a batched-field
     stencil, a row-wise scan, its reverse, the batched transpose, and an S3
