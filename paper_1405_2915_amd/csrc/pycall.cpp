@@ -39,8 +39,9 @@ PyObject* s_handle;
 
 constexpr int kMax = 8;  // operands or parameters of one call
 
-// The converters return false for an argument that is not plain; a Python error
-// met on the way is dropped, since the general path raises its own.
+// The converters return false for an argument that is not plain; an error of a
+// conversion is dropped, since the general path raises its own.  An exception from
+// the query of the current stream (an interrupt, say) stays set and is raised.
 
 bool plain_int(PyObject* o, int64_t* v) {
     if (!PyLong_Check(o)) return false;
@@ -115,10 +116,7 @@ bool stream_of(PyObject* o, void** s) {
         *s = PyLong_AsVoidPtr(o);
     } else {
         PyObject* v = PyObject_CallNoArgs(g_current_stream);
-        if (!v) {
-            PyErr_Clear();
-            return false;
-        }
+        if (!v) return false;
         const bool ok = PyLong_Check(v);
         *s = ok ? PyLong_AsVoidPtr(v) : nullptr;
         Py_DECREF(v);
@@ -191,7 +189,10 @@ PyObject* enter(F&& call) {
             return nullptr; \
         }
 #define SKEL_PLAIN(cond) \
-    if (!(cond)) Py_RETURN_NONE
+    if (!(cond)) { \
+        if (PyErr_Occurred()) return nullptr; \
+        Py_RETURN_NONE; \
+    }
 
 // (op, params, ins, out, variant, stream)
 SKEL_PY(py_map, 6)

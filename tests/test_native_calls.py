@@ -1,0 +1,42 @@
+"""The Python binding's native call module (_skelcall), on the CPU: what it hands on
+and what it leaves to the general path.  Each check runs in a process of its own,
+since the module's state is the process's."""
+import os
+import subprocess
+import sys
+import textwrap
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+
+def run(code):
+    res = subprocess.run([sys.executable, "-c", textwrap.dedent(code)], cwd=ROOT,
+                         capture_output=True, text=True, timeout=120)
+    assert res.returncode == 0, res.stdout + res.stderr
+    return res.stdout
+
+
+def test_exception_of_the_stream_query_is_raised():
+    """An interrupt that arrives while the current stream is queried is not lost."""
+    run("""
+        import ctypes as C
+        import paper_1405_2915_amd as skel
+        lib = skel.load_library()
+        call = skel._call
+        names = [n for n in ("skel_map", "skel_reduce", "skel_mapreduce", "skel_mapoverlap1d",
+                 "skel_mapoverlap1d_backward", "skel_mapoverlap2d_fields",
+                 "skel_mapoverlap2d_fields_backward", "skel_scan", "skel_scan_rows",
+                 "skel_reduce_segments")]
+        def interrupted():
+            raise KeyboardInterrupt
+        class Box:
+            handle = 1
+        call.bind(Box, interrupted, {n: C.cast(getattr(lib, n), C.c_void_p).value for n in names})
+        try:
+            call.reduce(0, Box(), Box(), -1, None)
+        except KeyboardInterrupt:
+            pass
+        else:
+            raise SystemExit("the interrupt was dropped")
+        assert call.reduce("no integer", Box(), Box(), -1, None) is None
+    """)
