@@ -80,7 +80,7 @@ class _Allocator(C.Structure):
 
 
 _lib = None
-_call = None  # _skelcall, bound to the loaded library
+_call = None  # _skelcall, bound to the loaded library, or its stand-in
 _live = weakref.WeakSet()
 _keepalive = []
 # handles of containers collected while a graph capture was running on the
@@ -155,20 +155,32 @@ def load_library(path: str = LIB_PATH):
                               "with `python -m paper_1405_2915_amd.build_lib`") from e
         fn.restype = res
         fn.argtypes = args
-    _bind_calls(lib, path)
+    _bind_calls(lib)
     _lib = lib
     return lib
 
 
-def _bind_calls(lib, path) -> None:
+class _NoNativeCalls:
+    """Stands in for _skelcall where it is not built for this interpreter: every
+    call takes the general path, through ctypes."""
+
+    def __getattr__(self, name):
+        return lambda *args: None
+
+
+def _bind_calls(lib) -> None:
     """Give _skelcall (the skeleton calls without ctypes) the entry points of
     the loaded library."""
     global _call
     try:
         from . import _skelcall
+    except ModuleNotFoundError:
+        _call = _NoNativeCalls()
+        return
     except ImportError as e:
-        raise ImportError(f"_skelcall.so is not built or older than the sources ({e}); rebuild "
-                          "it with `python -m paper_1405_2915_amd.build_lib`") from e
+        raise ImportError(f"_skelcall cannot be loaded ({e}): it is older than the sources or "
+                          "half rebuilt; rebuild it with "
+                          "`python -m paper_1405_2915_amd.build_lib`") from e
     _skelcall.bind(Container, _current_stream,
                    {n: C.cast(getattr(lib, n), C.c_void_p).value
                     for n in ("skel_map", "skel_reduce", "skel_mapreduce", "skel_mapoverlap1d",

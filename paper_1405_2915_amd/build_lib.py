@@ -66,16 +66,20 @@ def build_hip(verbose: bool = False, jobs: int = 8) -> str:
     return LIB
 
 
-CALL_LIB = os.path.join(PKG, "_skelcall.so")
+# named for this interpreter, so that one of another version does not load it
+CALL_LIB = os.path.join(PKG, "_skelcall" + sysconfig.get_config_var("EXT_SUFFIX"))
 
 
 def build_call(verbose: bool = False) -> str:
-    """_skelcall.so: the Python binding's skeleton calls without ctypes."""
+    """_skelcall: the Python binding's skeleton calls without ctypes."""
     tmp = CALL_LIB + ".tmp"
     _run(["g++", "-std=c++17", "-O2", "-fPIC", "-shared", "-Wall", f"-I{INC}",
           "-I" + sysconfig.get_paths()["include"], "-o", tmp,
           os.path.join(CSRC, "pycall.cpp")], verbose)
     os.replace(tmp, CALL_LIB)
+    untagged = os.path.join(PKG, "_skelcall.so")
+    if os.path.exists(untagged):  # of an older build; any interpreter would load it
+        os.remove(untagged)
     return CALL_LIB
 
 

@@ -40,3 +40,33 @@ def test_exception_of_the_stream_query_is_raised():
             raise SystemExit("the interrupt was dropped")
         assert call.reduce("no integer", Box(), Box(), -1, None) is None
     """)
+
+
+def test_module_is_named_for_the_interpreter():
+    out = run("""
+        import sysconfig
+        import paper_1405_2915_amd as skel
+        skel.load_library()
+        print(skel._call.__file__.endswith("_skelcall" + sysconfig.get_config_var("EXT_SUFFIX")))
+    """)
+    assert out.strip() == "True"
+
+
+def test_general_path_without_the_module():
+    """A library built without the module is loaded, and calls reach it through ctypes."""
+    run("""
+        import sys
+        sys.modules["paper_1405_2915_amd._skelcall"] = None  # "not installed"
+        import paper_1405_2915_amd as skel
+        skel.load_library()
+        assert skel._call.scan(1, 2, 3) is None
+        c = skel.Container.__new__(skel.Container)
+        c.handle = 1
+        try:
+            skel.skel_reduce(skel.SUM, c, c)
+        except skel.SkelError as e:
+            assert e.status == skel.E_NOINIT, e
+        else:
+            raise SystemExit("no error")
+        c.handle = None
+    """)
