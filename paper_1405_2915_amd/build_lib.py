@@ -47,23 +47,28 @@ def _run(cmd, verbose):
         print(r.stderr, flush=True)
 
 
-def build_hip(verbose: bool = False, jobs: int = 8) -> str:
+def _compile(jobs_of, verbose, jobs: int = 8) -> None:
+    """Compile (source, object, extra flags) triples side by side."""
     os.makedirs(BUILD, exist_ok=True)
-    objs = []
-    cmds = []
-    for src in HIP_SOURCES:
-        obj = os.path.join(BUILD, src + ".o")
-        objs.append(obj)
-        lang = ["-x", "hip"] if src.endswith(".hip") else []
-        cmds.append([HIPCC] + HIP_FLAGS + lang + ["-c", os.path.join(CSRC, src),
-                                                  "-o", obj])
+    cmds = [[HIPCC] + HIP_FLAGS + flags + (["-x", "hip"] if src.endswith(".hip") else []) +
+            ["-c", os.path.join(CSRC, src), "-o", obj] for src, obj, flags in jobs_of]
     with cf.ThreadPoolExecutor(max_workers=jobs) as ex:
         list(ex.map(lambda c: _run(c, verbose), cmds))
-    tmp = LIB + ".tmp"
-    _run([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", tmp] + objs,
-         verbose)
-    os.replace(tmp, LIB)
-    return LIB
+
+
+def _link(lib, objs, verbose) -> str:
+    _run([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", lib + ".tmp"] + objs, verbose)
+    os.replace(lib + ".tmp", lib)
+    return lib
+
+
+def _objects():
+    return {s: os.path.join(BUILD, s + ".o") for s in HIP_SOURCES}
+
+
+def build_hip(verbose: bool = False, jobs: int = 8) -> str:
+    _compile([(s, o, []) for s, o in _objects().items()], verbose, jobs)
+    return _link(LIB, list(_objects().values()), verbose)
 
 
 # named for this interpreter, so that one of another version does not load it
@@ -103,28 +108,30 @@ def build_hosttest(verbose: bool = False, sanitize: bool = False) -> str:
 SCAN_STRESS_LIB = os.path.join(PKG, "libskel_scan_w2.so")
 
 
+SCAN_STRESS_FLAGS = ["-DSKEL_SCAN_WAVES=2", "-DSKEL_FLAT_PATIENCE=1"]
+SCAN_STRESS_OBJS = {s: os.path.join(BUILD, s + ".w2.o") for s in ("k_scan.hip", "k_scan_rows.hip")}
+
+
 def build_scan_stress(verbose: bool = False) -> str:
     """libskel_scan_w2.so: the library with the scan tiles shrunk to two
     wavefronts (4096 elements for 4-byte inputs instead of 32768), eight times
     as many tiles and a deeper decoupled look-back, and with flat tiles that
     wait for one poll only before they compute the totals they miss, for the
     stress tests of both.  The other objects are those of the product build."""
-    flags = ["-DSKEL_SCAN_WAVES=2", "-DSKEL_FLAT_PATIENCE=1"]
-    own = {s: os.path.join(BUILD, s + ".w2.o") for s in ("k_scan.hip", "k_scan_rows.hip")}
-    with cf.ThreadPoolExecutor(max_workers=len(own)) as ex:
-        list(ex.map(lambda s: _run([HIPCC] + HIP_FLAGS + flags + [
-            "-x", "hip", "-c", os.path.join(CSRC, s), "-o", own[s]], verbose), own))
-    objs = [own.get(s, os.path.join(BUILD, s + ".o")) for s in HIP_SOURCES]
-    tmp = SCAN_STRESS_LIB + ".tmp"
-    _run([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", tmp] + objs, verbose)
-    os.replace(tmp, SCAN_STRESS_LIB)
-    return SCAN_STRESS_LIB
+    _compile([(s, o, SCAN_STRESS_FLAGS) for s, o in SCAN_STRESS_OBJS.items()], verbose)
+    return _link(SCAN_STRESS_LIB, list({**_objects(), **SCAN_STRESS_OBJS}.values()), verbose)
 
 
 def build(verbose: bool = False) -> None:
-    build_hip(verbose)
+    # (the longest sources first; the stress build's beside the product's)
+    todo = [(s, o, SCAN_STRESS_FLAGS) for s, o in SCAN_STRESS_OBJS.items()]
+    todo += [(s, o, []) for s, o in _objects().items()]
+    slow = ("k_scan.hip", "k_overlap.hip", "k_scan_rows.hip")
+    todo.sort(key=lambda t: slow.index(t[0]) if t[0] in slow else len(slow))
+    _compile(todo, verbose)
+    _link(LIB, list(_objects().values()), verbose)
+    _link(SCAN_STRESS_LIB, list({**_objects(), **SCAN_STRESS_OBJS}.values()), verbose)
     build_call(verbose)
-    build_scan_stress(verbose)
     build_hosttest(verbose)
 
 

@@ -164,8 +164,8 @@ int table_rule(const CallContext& c) {
     for (const auto& e : g_table) {
         if (e.skeleton != c.skeleton || e.dtype != (int)c.din || e.cls != cls) continue;
         // the marching window was tuned on images of whole strips; a ragged last
-        // strip costs it more than it wins (9 x 9 Gaussian: 4096^2 34.8 us against
-        // 37.5 for the separable tile, 4000^2 52 / 35, 3000^2 53 / 21)
+        // strip costs it more than it wins (9 x 9 Gaussian: 4096^2 28.8 us against
+        // 28.8 for the separable L1 tile, 4000^2 42.9 / 29.1, 3000^2 49.7 / 20.8)
         if (c.skeleton == SKEL_SK_MAPOVERLAP2D && e.variant == O2E_MARCH && !whole_strips(c.cols))
             continue;
         if (e.log2n <= key && e.log2n > best_k) {
