@@ -328,9 +328,11 @@ skel_status skel_scan(skel_container *in, skel_container *out,
  * (SKEL_SK_SCAN_ROWS): 0 runs one flat single-pass Scan per row (the plan's
  * choice for the row length; selectable only when every row starts 16-byte
  * aligned, i.e. cols * element size is a multiple of 16 for both types); 1
- * scans all rows in a single launch, whatever their alignment, in a form
+ * scans all rows together, whatever their alignment, in a form
  * chosen by the shape: several short rows per wavefront, one wavefront per
- * row, or a few long rows cut into tiles.  The static rule takes 0 for fewer
+ * row, one workgroup per row, or a few long rows cut into tiles (binary32 sums
+ * in three launches, everything else in one).  Its results are the same bits on
+ * every run and inside a captured graph.  The static rule takes 0 for fewer
  * than 64 aligned rows of at least 2^20 elements, else 1. */
 skel_status skel_scan_rows(skel_container *in, skel_container *out,
                            skel_scan_kind kind, skel_reduce_op op, int variant,
@@ -387,7 +389,9 @@ skel_status skel_map_overlap2d_reduce_backward(skel_map_op map_op, const double 
  * Empty segments give the identity.  The plain variant issues one Reduce per
  * segment; variant 1 (B1_persistent) divides the elements, not the segments,
  * over the device in chunks of one size and combines the partials of segments
- * that span chunks in a fixed order (deterministic).  It checks the offsets on
+ * that span chunks in a fixed order (deterministic for a given batch; where a
+ * segment lies relative to the chunks, 4096 elements each, decides how its sum
+ * is grouped, so its last bits may change with what precedes it).  It checks the offsets on
  * the device: if they decrease or leave [0, n] it computes nothing and
  * skel_sync reports SKEL_E_TIMEOUT with flag 4; the per-segment variant
  * reads the offsets on the host and returns SKEL_E_INVAL.  No offsets can
@@ -508,7 +512,8 @@ int skel_select_variant(int skeleton, skel_dtype dtype, int64_t n,
  * size n uses the entry with the largest log2 n <= ceil(log2 n) for its
  * skeleton, input dtype (and class) (sizes beyond the table extrapolate from
  * its last entry, sizes below use its first).  An entry that is not selectable for a call falls back to the
- * static rules.  The whole file is validated before it replaces the current
+ * static rules, and entries that name O2e_march are passed over for images whose
+ * width is not a multiple of 256 (its strips), as if the table had none.  The whole file is validated before it replaces the current
  * table; on error the old table stays.  SKEL_VARIANT_<SKELETON>=<name> in the
  * environment overrides both. */
 skel_status skel_load_plan(const char *path);

@@ -338,8 +338,9 @@ skel_status launch_map_backward(int op, float p0, float p1, const float* x, cons
 // the array is the correlation with the reversed weights, so the forward
 // kernels compute it with a zero pad (CONST edges send nothing back, and for
 // CLAMP this is every element but the ends) or with the cyclic rule (exact).
-// For CLAMP the elements that clamped reads land on are computed by the same
-// launch, from sums of the weights that reach them.
+// For CLAMP the elements that clamped reads land on are computed from sums of the
+// weights that reach them, by the same launch (after the 2D marching form, by one
+// of their own).
 skel_status launch_overlap1d_adjoint(int v, const float* g, float* dx, int64_t n,
                                      const float* w, int r, int edge, LaunchCtx& lc) {
     if (v == A0_GATHER) {

@@ -122,7 +122,8 @@ __global__ __launch_bounds__(kBlock) void ov1_direct(const float* x, float* out,
 // elements, which also collect every read past them:
 //     out[0]   = sum_i lo[i] x[i],         lo[i] = w'[0] + ... of tap i outward
 //     out[n-1] = sum_m hi[m] x[n - 1 - m]
-// with the prefix sums of the forward weights as coefficients (make_ends).
+// with the prefix sums of the forward weights as coefficients
+// (launch_overlap1d_transposed).
 struct Ends1 {
     float lo[SKEL_MAX_RADIUS_1D + 1], hi[SKEL_MAX_RADIUS_1D + 1];
 };

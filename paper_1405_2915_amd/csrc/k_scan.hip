@@ -339,11 +339,11 @@ skel_status scan_typed(int v, int kind, const void* x, void* y, int64_t n, Launc
         void* status = nullptr;
         skel_status e = ws_status(lc, (size_t)nts * 16, &status);
         if (e != SKEL_OK) return e;
-        // up to one tile per CU (which holds eight or more) the tiles of several
-        // launches on as many streams are resident together (HIP runs four queues
-        // at once), and every wait ends without the means to compute a missing
-        // total (5.3 us with them at 2^20 elements, 5.2 without)
-        const bool few = nts <= lc.dev->cus;
+        // up to two tiles per CU, which holds eight or more, the tiles of four
+        // launches on as many streams (HIP runs four queues at once) are resident
+        // together, and every wait ends without the means to compute a missing total
+        // (binary32 2^20 5.3 us with them, 5.2 without; 557293 int64 9.8, 9.4)
+        const bool few = nts <= 2 * (int64_t)lc.dev->cus;
         const auto kern =
             few || !apart ? (rev ? scan_flat<PS, true, false> : scan_flat<PS, false, false>)
                           : (rev ? scan_flat<PS, true, true> : scan_flat<PS, false, true>);

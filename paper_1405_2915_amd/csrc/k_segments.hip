@@ -23,6 +23,8 @@
 //       workgroups' time, and the item table took one workgroup 0.5 ms);
 //       4096 log-uniform segments of 32..2^20 (1.65 GB) 249 us against 277;
 //       20011 of 1000..9000 62 us against 162.
+//       (Empty segments take no elements, so a run of them falls to one
+//       workgroup: a million 2.4 ms, 5.0 with a work item each.)
 // B1 checks the offsets first: if they decrease or leave [0, n] nothing is
 // computed and error flag 4 is raised.
 #include "kcommon.hpp"

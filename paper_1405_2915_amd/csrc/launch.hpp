@@ -113,7 +113,8 @@ skel_status launch_overlap2d(int variant, const float* x, float* out,
                              const float* wy, const float* wx, int ry, int rx,
                              int edge, float pad, LaunchCtx& lc);
 // the transpose of that map applied to g (every field on its own), by the
-// variant the plan's rule gives the flipped correlation, in one launch
+// variant the plan's rule gives the flipped correlation, in one launch (the marching
+// form of a clamped transpose that is not its own map: its border in a second)
 skel_status launch_overlap2d_transposed(const float* g, float* dx, int64_t rows, int64_t cols,
                                         int64_t fields, const float* w2d, const float* wy,
                                         const float* wx, int ry, int rx, int edge, LaunchCtx& lc);
