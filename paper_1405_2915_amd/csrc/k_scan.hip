@@ -176,7 +176,7 @@ __global__ __launch_bounds__(P::kBlock) void scan_lookback_persist(
 }
 
 template <class P, bool REV, bool RESCUE>
-__global__ __launch_bounds__(P::kBlock, flat_waves<P>()) void scan_flat(
+__global__ __launch_bounds__(P::kBlock, (flat_waves<P, RESCUE>())) void scan_flat(
     const typename P::in_t* in, typename P::out_t* out, int64_t n, int64_t ntiles, int exclusive,
     u64* status, u64* sync) {
     const int64_t seq = blockIdx.x;

@@ -2,8 +2,11 @@
 // Scan instances of one length, Section III), in one launch for all rows.  Vectors
 // are accessed at element alignment, so ragged rows cost no more instructions
 // than aligned ones.  Forms, by shape:
-//   short rows   up to 32 vectors: 8, 16 or 32 lanes per row, so that a wavefront
-//                scans several rows at once
+//   short rows   up to 32 vectors, or 64 of many rows: 8, 16, 32 or 64 lanes per row, so
+//                that a wavefront scans several rows at once, and four wavefronts share
+//                a workgroup
+//                (8-byte outputs in unaligned rows of 129 to 256 elements: one element
+//                per lane, 64 at a time)
 //   a wavefront  per row, walking it in chunks of as many vectors per lane as the
 //                row needs (1, 2, 4 or 8 rows of 64 vectors) with a running carry;
 //                the form for many rows
@@ -72,9 +75,9 @@ __global__ __launch_bounds__(kWave) void scan_rows_wave(const typename P::in_t* 
     }
 }
 
-// inclusive scan within groups of G = 8, 16 or 32 lanes (REV: from the group's
-// last lane down): row-of-16 steps that stay inside the group, then for 32 the
-// other half's total
+// inclusive scan within groups of G = 8, 16, 32 or 64 lanes (REV: from the group's
+// last lane down): row-of-16 steps that stay inside the group, then for 32 and 64
+// the totals of the other half
 template <class C, bool REV, class T>
 __device__ __forceinline__ T group_scan(T v, int G) {
     const T id = C::id();
@@ -95,7 +98,11 @@ __device__ __forceinline__ T group_scan(T v, int G) {
     if (G > 16) {
         const T a = lane_value(v, REV ? 16 : 15), b = lane_value(v, REV ? 48 : 47);
         const T t = l < 32 ? a : b;
-        if (p >= 16) v = REV ? C::op(v, t) : C::op(t, v);
+        if ((p & 31) >= 16) v = REV ? C::op(v, t) : C::op(t, v);
+    }
+    if (G > 32) {
+        const T t = lane_value(v, REV ? 32 : 31);
+        if (p >= 32) v = REV ? C::op(v, t) : C::op(t, v);
     }
     return v;
 }
@@ -155,11 +162,45 @@ __global__ __launch_bounds__(kShortBlock) void scan_rows_short(const typename P:
     }
 }
 
+// Rows of up to 256 elements, 64 at a time, one element per lane: 8-byte outputs whose
+// rows are not 16-byte aligned, whose vectors would each cross a line or fill half
+// of one (37329 x 151 int64 22 us in vectors, 16 so; int32 -> int64 17.7, 16.6; up to
+// 128 elements a row of vectors is level or better: 60000 x 65 int32 -> int64 13.3, 17.6)
+template <class P, bool REV>
+__global__ __launch_bounds__(kShortBlock) void scan_rows_single(const typename P::in_t* in,
+                                                                typename P::out_t* out,
+                                                                int64_t rows, int cols,
+                                                                int exclusive, int) {
+    using acc_t = typename P::acc_t;
+    using C = typename P::C;
+    constexpr int K = 4;
+    const int l = lane();
+    const int64_t row = (int64_t)blockIdx.x * (kShortBlock / kWave) + threadIdx.x / kWave;
+    if (row >= rows) return;  // whole wavefronts; no barrier follows
+    const typename P::in_t* src = in + row * cols;
+    typename P::out_t* dst = out + row * cols;
+    typename P::in_t raw[K];
+#pragma unroll
+    for (int k = 0; k < K; ++k) raw[k] = k * kWave + l < cols ? src[k * kWave + l] : 0;
+    acc_t carry = C::id();
+#pragma unroll
+    for (int kk = 0; kk < K; ++kk) {
+        const int k = REV ? K - 1 - kk : kk, c = k * kWave + l;
+        if (k * kWave >= cols) continue;
+        const acc_t x = c < cols ? widen<acc_t>(raw[k]) : C::id();
+        const acc_t incl = REV ? wave_inclusive_suffix_scan<C>(x) : wave_inclusive_scan<C>(x);
+        const acc_t nb = REV ? wave_shift_down(incl, C::id()) : wave_shift_up(incl, C::id());
+        const acc_t base = C::op(carry, l == (REV ? kWave - 1 : 0) ? C::id() : nb);
+        if (c < cols) dst[c] = (typename P::out_t)(exclusive ? base : C::op(base, x));
+        carry = C::op(carry, lane_value(incl, REV ? 0 : kWave - 1));
+    }
+}
+
 // Flat look-back within each row: tile seq = row * tpr + t (t in scan order)
 // publishes its total and reads those of the t tiles before it in its row.  The
 // last workgroup, which advances the epoch, waits for every tile's total.
 template <class P, bool REV>
-__global__ __launch_bounds__(P::kBlock, flat_waves<P>()) void scan_rows_flat(
+__global__ __launch_bounds__(P::kBlock, (flat_waves<P, true>())) void scan_rows_flat(
     const typename P::in_t* in, typename P::out_t* out, int64_t cols, int64_t tpr, int exclusive,
     u64* status, u64* sync) {
     const int64_t row = (int64_t)blockIdx.x / tpr, t = (int64_t)blockIdx.x - row * tpr;
@@ -463,9 +504,18 @@ skel_status scan_rows_typed(const RowsCall& c, LaunchCtx& lc) {
     using PM = SP<DIN, DOUT, OP, 4, false>;
     using PL = SP<DIN, DOUT, OP, 16, false>;
     constexpr int E = PS::E;
-    if (c.cols <= 32 * E) {
-        const int G = c.cols <= 8 * E ? 8 : c.cols <= 16 * E ? 16 : 32;
-        const auto kern = c.rev ? scan_rows_short<PS, true> : scan_rows_short<PS, false>;
+    const bool single = sizeof(typename PS::out_t) == 8 && c.cols > 128 && c.cols <= 256 &&
+                        (c.cols * sizeof(typename PS::in_t)) % 16 != 0;
+    // 64 lanes per row: 20000 x 256 binary32 8.3 us against 9.2 for a wavefront per
+    // workgroup, 60000 x 65 int64 17.9 against 23; but int32 -> int64 15.1 against 13.8,
+    // and 200 x 200 2.92 against 2.81
+    const int lanes = sizeof(typename PS::in_t) == sizeof(typename PS::out_t) &&
+                      c.rows >= 4 * (int64_t)lc.dev->cus ? 64 : 32;
+    if (c.cols <= lanes * E || single) {
+        const int G = c.cols <= 8 * E ? 8 : c.cols <= 16 * E ? 16 : c.cols <= 32 * E ? 32 : 64;
+        auto kern = c.rev ? scan_rows_short<PS, true> : scan_rows_short<PS, false>;
+        if constexpr (sizeof(typename PS::out_t) == 8)
+            if (single) kern = c.rev ? scan_rows_single<PS, true> : scan_rows_single<PS, false>;
         // (2^29 rows at 8 lanes are more work items than one launch numbers)
         const int64_t per_group = kShortBlock / G, most = max_groups(kShortBlock) * per_group;
         for (int64_t r = 0; r < c.rows; r += most) {
@@ -473,7 +523,7 @@ skel_status scan_rows_typed(const RowsCall& c, LaunchCtx& lc) {
             kern<<<(unsigned)((rows + per_group - 1) / per_group), kShortBlock, 0, lc.stream>>>(
                 static_cast<const typename PS::in_t*>(c.x) + r * c.cols,
                 static_cast<typename PS::out_t*>(c.y) + r * c.cols, rows, (int)c.cols, c.excl, G);
-            const skel_status e = launch_check("scan_rows_short");
+            const skel_status e = launch_check(single ? "scan_rows_single" : "scan_rows_short");
             if (e != SKEL_OK) return e;
         }
         return SKEL_OK;

@@ -366,9 +366,11 @@ __device__ __forceinline__ typename P::acc_t flat_prefix(u64* status, int64_t se
     return a;
 }
 
-// wavefronts per SIMD of the flat forms, as without the rescue
-template <class P>
-constexpr int flat_waves() { return sizeof(typename P::in_t) == 4 ? 4 : P::NW <= 1 ? 3 : 2; }
+// wavefronts per SIMD of the flat forms with the rescue: as many as without it
+template <class P, bool RESCUE>
+constexpr int flat_waves() {
+    return !RESCUE ? 1 : sizeof(typename P::in_t) == 4 ? 4 : P::NW <= 1 ? 3 : 2;
+}
 
 // A flat tile: seq of ntiles in scan order, covering data tile `tile` of n elements;
 // descriptors at status.  last: this workgroup advances the epoch, once every one of

@@ -199,6 +199,35 @@ def test_scan_rows_forms(skel, oracle_mod, pair):
     skel.skel_sync()
 
 
+@pytest.mark.parametrize("pair", ["f32", "i32_i32", "i32_i64", "i64_i64"])
+@pytest.mark.parametrize("op", list(RED_OPS))
+def test_scan_rows_around_a_wavefront(skel, oracle_mod, pair, op):
+    """Rows of about 64 vectors, of 64 elements at a time, and their neighbours, aligned and not;
+    more rows than wavefronts of the last workgroup."""
+    din, dout, npd, npo = {"f32": (skel.F32, skel.F32, np.float32, np.float32),
+                           "i32_i32": (skel.I32, skel.I32, np.int32, np.int32),
+                           "i32_i64": (skel.I32, skel.I64, np.int32, np.int64),
+                           "i64_i64": (skel.I64, skel.I64, np.int64, np.int64)}[pair]
+    for rows, cols in ((5, 127), (6, 128), (7, 129), (9, 130), (9, 192), (11, 193), (5, 254),
+                       (6, 255), (7, 256), (5, 257), (1025, 66), (1030, 127), (1025, 129),
+                       (1027, 256)):
+        x = (si.normal_f32(rows * cols, 25, cols).reshape(rows, cols) if pair == "f32"
+             else ints(si.rng(25, cols), (rows, cols), npd))
+        cx = skel.Container.from_numpy(x)
+        for kind, code in KINDS.items():
+            out = skel.Container.empty(dout, rows, cols)
+            skel.skel_scan_rows(cx, out, code, RED_OPS[op], variant=SR1)
+            got = out.to_numpy().reshape(rows, cols)
+            if pair == "f32":
+                ref, mag = oracle_mod.scan_rows(x, kind, op)
+                bad = (np.abs(got.astype(np.float64) - ref) > 1e-5 * mag + 1e-30 if op == "sum"
+                       else got != ref)
+            else:
+                bad = got != oracle_mod.scan_rows(x, kind, op, npo)
+            assert not bad.any(), (pair, op, rows, cols, kind, np.argwhere(bad)[:3])
+    skel.skel_sync()
+
+
 @pytest.mark.parametrize("op", ["min", "max"])
 def test_scan_rows_forms_min_max_in_place(skel, op):
     """In place; a NaN leaves the running minimum or maximum as it is."""
