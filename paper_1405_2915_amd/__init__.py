@@ -82,7 +82,6 @@ class _Allocator(C.Structure):
 _lib = None
 _call = None  # _skelcall, bound to the loaded library, or its stand-in
 _live = weakref.WeakSet()
-_keepalive = []
 # handles of containers collected while a graph capture was running on the
 # current stream: destroying one may wait for the device and frees pinned host
 # memory, which would invalidate the capture, so they are destroyed afterwards
@@ -255,14 +254,15 @@ def skel_init(device: int = 0, allocator: str = "torch", plan: str | None = "def
         skel_load_plan(plan)
 
 
-def _init_device(device: int, allocator: str) -> None:
-    global _device
-    lib = load_library()
-    _device = device
-    if allocator == "torch":
+# one allocator per device, kept for good: every container keeps the addresses of the
+# callbacks it was created with and frees its memory through them, also after the
+# library has been initialised again
+_torch_allocators = {}
+
+
+def _torch_allocator(device: int) -> _Allocator:
+    if device not in _torch_allocators:
         import torch
-        torch.cuda.init()
-        torch.cuda.set_device(device)
 
         def _alloc(nbytes, stream, ctx):
             try:
@@ -274,9 +274,19 @@ def _init_device(device: int, allocator: str) -> None:
             if not _shutting_down:
                 torch.cuda.caching_allocator_delete(ptr)
 
-        a = _Allocator(_ALLOC_FN(_alloc), _FREE_FN(_free), None)
-        _keepalive[:] = [a]
-        _check(lib.skel_init(device, C.byref(a)), "skel_init")
+        _torch_allocators[device] = _Allocator(_ALLOC_FN(_alloc), _FREE_FN(_free), None)
+    return _torch_allocators[device]
+
+
+def _init_device(device: int, allocator: str) -> None:
+    global _device
+    lib = load_library()
+    _device = device
+    if allocator == "torch":
+        import torch
+        torch.cuda.init()
+        torch.cuda.set_device(device)
+        _check(lib.skel_init(device, C.byref(_torch_allocator(device))), "skel_init")
     elif allocator == "hip":
         _check(lib.skel_init(device, None), "skel_init")
     else:

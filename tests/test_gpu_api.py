@@ -277,3 +277,18 @@ def test_plain_and_converted_arguments_agree(skel):
     dead.destroy()
     with pytest.raises(TypeError):
         skel.skel_reduce(skel.SUM, dead, f32(1))
+
+
+def test_containers_outlive_another_init(skel):
+    """A container made before the library was initialised again still frees its memory
+    through the callbacks it was made with."""
+    import gc
+    made = [skel.Container.from_numpy(np.ones(1000 + k, np.float32)) for k in range(8)]
+    for c in made:  # device copies
+        skel.skel_map(skel.MAP_AFFINE, [2.0, 0.0], [c], c)
+    for _ in range(3):
+        skel.skel_init(0, "torch")
+        gc.collect()
+    for c in made:
+        assert np.all(c.to_numpy() == 2.0)
+        c.destroy()

@@ -70,3 +70,24 @@ def test_general_path_without_the_module():
             raise SystemExit("no error")
         c.handle = None
     """)
+
+
+def test_allocator_callbacks_are_kept():
+    """Initialising again hands the library the same callbacks: containers made before
+    still hold their addresses."""
+    run("""
+        import ctypes as C, gc
+        import paper_1405_2915_amd as skel
+        seen = []
+        class Lib:
+            def skel_init(self, device, allocator):
+                a = C.cast(allocator, C.POINTER(skel._Allocator)).contents
+                seen.append((C.cast(a.alloc, C.c_void_p).value, C.cast(a.free, C.c_void_p).value))
+                return skel.OK
+        skel.load_library = lambda: Lib()
+        skel.torch.cuda.init = skel.torch.cuda.set_device = lambda *a: None
+        for _ in range(5):
+            skel._init_device(0, "torch")
+            gc.collect()
+        assert len(set(seen)) == 1, seen
+    """)
